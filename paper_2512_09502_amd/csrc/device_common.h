@@ -135,6 +135,23 @@ __device__ __forceinline__ void wave_hist_add(uint32_t* h, uint32_t bin, bool va
     }
 }
 
+// Every lane's rows [lo, hi] (none when hi < lo) of a first-index array get its
+// value v.  Short runs by the lane itself; a longer one (a stretch of sources
+// without connections) by all lanes of the wave, one run after another: a lane
+// alone stores a few rows per 100 ns.  Call with the whole wave converged.
+__device__ __forceinline__ void fill_rows(uint64_t* row_ptr, int64_t lo, int64_t hi, uint64_t v) {
+    constexpr int64_t LANE_MAX = 8;
+    const bool wide = hi - lo >= LANE_MAX;
+    if (!wide)
+        for (int64_t r = lo; r <= hi; ++r) row_ptr[r] = v;
+    for (uint64_t m = __ballot(wide); m; m &= m - 1) {
+        const int l = __ffsll((unsigned long long)m) - 1;
+        const int64_t a = __shfl(lo, l, 64), b = __shfl(hi, l, 64);
+        const uint64_t x = __shfl(v, l, 64);
+        for (int64_t r = a + (int64_t)(threadIdx.x & 63); r <= b; r += 64) row_ptr[r] = x;
+    }
+}
+
 // ------------------------------------------------------------------ scans
 // Inclusive prefix sum across a wave64 (Hillis-Steele with shuffles).
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {

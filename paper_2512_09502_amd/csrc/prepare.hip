@@ -332,26 +332,31 @@ __global__ __launch_bounds__(XNT) void k_number(const uint64_t* __restrict__ key
         const uint64_t last_lane = __shfl(pk, 63, 64);
         if (lane == 0) pp = last;
         last = last_lane;
-        if (i >= n) continue;
         const uint64_t rank = before + incl[k];                 // images started up to and including i
-        const bool local = pk < M_local;
-        const int64_t src2 = local ? (int64_t)pk : (int64_t)(M_local + rank - 1);
-        o_src[i] = (int32_t)src2;
-        o_tgt[i] = (int32_t)((key[k] >> 16) & tgt_mask);
-        o_delay[i] = (uint16_t)(key[k] & 0xffffu);
-        if constexpr (EARLY_VALS) o_weight[i] = __uint_as_float(val[k]);
-        else o_weight[i] = __uint_as_float(vals[i]);
-        // previous connection's source' (its flag count is rank minus this item's flag)
-        const bool flag_here = (fl >> k) & 1u;
-        int64_t prev2 = -1;
-        if (i > 0) prev2 = pp < M_local ? (int64_t)pp : (int64_t)(M_local + rank - (flag_here ? 1 : 0) - 1);
-        if (flag_here) img_key[rank - 1] = pk - M_local;
-        for (int64_t r = prev2 + 1; r <= src2; ++r) row_ptr[r] = i;
-        if (i + 1 == n) {
-            const int64_t n_rows = (int64_t)M_local + (int64_t)rank;
-            for (int64_t r = src2 + 1; r <= n_rows; ++r) row_ptr[r] = n;
-            *n_img_out = rank;
+        int64_t lo = 0, hi = -1, end_lo = 0, end_hi = -1;       // rows closed here and after the last connection
+        if (i < n) {
+            const bool local = pk < M_local;
+            const int64_t src2 = local ? (int64_t)pk : (int64_t)(M_local + rank - 1);
+            o_src[i] = (int32_t)src2;
+            o_tgt[i] = (int32_t)((key[k] >> 16) & tgt_mask);
+            o_delay[i] = (uint16_t)(key[k] & 0xffffu);
+            if constexpr (EARLY_VALS) o_weight[i] = __uint_as_float(val[k]);
+            else o_weight[i] = __uint_as_float(vals[i]);
+            // previous connection's source' (its flag count is rank minus this item's flag)
+            const bool flag_here = (fl >> k) & 1u;
+            int64_t prev2 = -1;
+            if (i > 0) prev2 = pp < M_local ? (int64_t)pp : (int64_t)(M_local + rank - (flag_here ? 1 : 0) - 1);
+            if (flag_here) img_key[rank - 1] = pk - M_local;
+            lo = prev2 + 1;
+            hi = src2;
+            if (i + 1 == n) {
+                end_lo = src2 + 1;
+                end_hi = (int64_t)M_local + (int64_t)rank;
+                *n_img_out = rank;
+            }
         }
+        fill_rows(row_ptr, lo, hi, i);
+        if (__ballot(end_hi >= end_lo)) fill_rows(row_ptr, end_lo, end_hi, n);
     }
 }
 
@@ -550,30 +555,31 @@ __global__ __launch_bounds__(PNT) void k_set_ranges(const WRange* rg, uint32_t n
 
 // first-index array: row_ptr[r] = first position with source >= r
 // Each thread takes 4 consecutive positions with one 16-byte load; position
-// i closes the rows (src[i-1], src[i]] (position n closes the rest).
+// i closes the rows (src[i-1], src[i]] (position n closes the rest; lanes past
+// it close none).  Whole waves stay in the loop: long runs of rows without
+// connections are filled by the wave together.
 __global__ __launch_bounds__(PNT) void k_csr(const int32_t* src, uint64_t n, uint64_t n_rows, uint64_t* row_ptr) {
     const uint64_t quads = n / 4 + 1;   // the last quad holds the tail and position n
-    for (uint64_t q = (uint64_t)blockIdx.x * PNT + threadIdx.x; q < quads; q += (uint64_t)gridDim.x * PNT) {
-        const uint64_t i0 = q * 4;
-        int64_t v[4];
+    for (uint64_t q0 = (uint64_t)blockIdx.x * PNT; q0 < quads; q0 += (uint64_t)gridDim.x * PNT) {
+        const uint64_t i0 = (q0 + threadIdx.x) * 4;
+        int64_t v[4], prev = (int64_t)n_rows;
         if (i0 + 4 <= n) {
             const int4 x = *reinterpret_cast<const int4*>(src + i0);
             v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
         } else {
             for (int k = 0; k < 4; ++k) v[k] = i0 + k < n ? (int64_t)src[i0 + k] : (int64_t)n_rows;
         }
-        int64_t prev = i0 == 0 ? -1 : (int64_t)src[i0 - 1];
+        if (i0 <= n) prev = i0 == 0 ? -1 : (int64_t)src[i0 - 1];
+#pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const uint64_t i = i0 + k;
-            if (i > n) break;
-            for (int64_t r = prev + 1; r <= v[k]; ++r) row_ptr[r] = i;
+            fill_rows(row_ptr, prev + 1, v[k], i0 + k);   // nothing past position n: prev == v[k] == n_rows
             prev = v[k];
         }
     }
 }
 
-// The same by a binary search per row, for few rows against many connections:
-// a search reads about log2(n) positions where the pass above reads all n.
+// The same by a binary search per row: a search reads about log2(n) positions
+// where the pass above reads all n, and no row waits for its neighbours.
 __global__ void k_csr_search(const int32_t* src, uint64_t n, uint64_t n_rows, uint64_t* row_ptr) {
     const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r > n_rows) return;
@@ -1016,7 +1022,7 @@ void prepare_all(Ctx& c) {
                 const uint64_t n_rows = (uint64_t)M_local + n_img;
                 row_ptr = result<uint64_t>(c, SNNC_ROW_PTR, n_rows + 1);
                 tstart(c, "prep_csr");
-                if (n_rows * 64 < N)   // rows few against connections: search instead of reading every source
+                if (n_rows * 64 < N || n_rows > N)   // rows few against connections, or mostly empty: search
                     hipLaunchKernelGGL(k_csr_search, dim3((unsigned)((n_rows + 1 + 255) / 256)), dim3(256), 0,
                                        c.stream, o_src, N, n_rows, row_ptr);
                 else
