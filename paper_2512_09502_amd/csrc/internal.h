@@ -448,6 +448,7 @@ struct SortPlan {
     bool wide = false;   // some pass has 9-bit digits
 };
 SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits);
+uint32_t hist_grid(uint64_t n);
 // 64 geometric-gap thresholds of a Bernoulli(p) sequence (pairwise Bernoulli rule)
 int sort_variant_count();
 

@@ -997,7 +997,7 @@ void prepare_all(Ctx& c) {
             uint64_t* hist = static_cast<uint64_t*>(tmp(8 * HIST_STRIDE * 8));
             HIPCHK(hipMemsetAsync(hist, 0, 8 * HIST_STRIDE * 8, c.stream));
             tstart(c, "prep_keys");
-            hipLaunchKernelGGL(k_keys, dim3(grid_for(N, 8192)), dim3(PNT), 0, c.stream, L, c.g_src, c.g_tgt, c.g_delay,
+            hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, L, c.g_src, c.g_tgt, c.g_delay,
                                N, mapped ? bits : (const uint32_t*)nullptr, mapped ? word_rank : (const uint64_t*)nullptr,
                                Lmap, M_local, 16 + tbits, plan.n9, dbits, passes, keys0, hist);
             tstop(c);
