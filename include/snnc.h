@@ -558,8 +558,9 @@ snnc_status snnc_tune(snnc_ctx* ctx, const char* key, int64_t value);
  * live in fixed-size blocks of 2^26 connections mapped as calls and admitted
  * requests need them, kept mapped for the next context on the device after
  * Prepare; 0: arrays grown by doubling; set before the first connection,
- * SNNC_EUNSUPPORTED for 1 without support).  Every setting gives the same
- * arrays. */
+ * SNNC_EUNSUPPORTED for 1 without support) and "lookback_spins" (0 .. 2^22,
+ * default 4096: polls of an earlier tile's digit counts before a radix-sort
+ * workgroup counts that tile itself).  Every setting gives the same arrays. */
 
 /* Autotuner of the source-major sort: times every pass algorithm and tile
  * shape (sort_mode x sort_variant) on n synthetic keys with `bits` sorted
@@ -630,14 +631,14 @@ snnc_status snnc_deliver(snnc_ctx* ctx, int32_t kind, const uint32_t* grp, const
  * variant.  keys_tmp/vals_tmp are device scratch of the same sizes.  On
  * return *result_in_tmp says whether the sorted pairs are in (keys, vals)
  * (0) or in (keys_tmp, vals_tmp) (1).  Errors: SNNC_EINVAL for bad bit
- * ranges or null pointers, SNNC_EDEVICE if a device wait exceeded its bound. */
+ * ranges or null pointers, SNNC_EDEVICE. */
 snnc_status snnc_sort_pairs(snnc_ctx* ctx, uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp,
                             uint64_t n, uint32_t bit_lo, uint32_t bit_hi, int32_t* result_in_tmp);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation):
  * snnc_sort_pairs (same arguments, same result) without any allocation.  The
- * digit histograms, tile counters, status word and look-back table live in
+ * digit histograms and look-back table live in
  * one static device array of 16 MiB per GPU owned by the library (set up by
  * the first snnc_init on that GPU and held until the process ends); the
  * caller passes keys, vals and the keys_tmp/vals_tmp ping-pong buffers as

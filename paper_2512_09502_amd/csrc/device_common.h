@@ -126,7 +126,7 @@ __device__ __forceinline__ void wave_hist_add(uint32_t* h, uint32_t bin, bool va
     const uint64_t act = __ballot(valid);
     if (!act) return;
     const int leader = __ffsll((unsigned long long)act) - 1;
-    const uint32_t b0 = __shfl(bin, leader, 64);
+    const uint32_t b0 = __builtin_amdgcn_readlane(bin, leader);
     const uint64_t same = __ballot(valid && bin == b0);
     if (same == act) {
         if ((int)(threadIdx.x & 63) == leader) atomicAdd(&h[b0], (uint32_t)__popcll(act));

@@ -1,6 +1,6 @@
 // Stable LSD radix sort of 64-bit keys with a 32-bit payload, one pass per
-// digit of at most 8 bits, in the single-pass "onesweep" form: every
-// workgroup takes the next tile in launch order, ranks its keys within the
+// digit of at most 9 bits, in the single-pass "onesweep" form: every
+// workgroup takes one tile, ranks its keys within the
 // tile with wave64 ballots, publishes its per-digit count, resolves the
 // counts of all earlier tiles by decoupled look-back, stages the tile in LDS
 // in digit order and writes runs of equal digits with consecutive stores.
@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "device_common.h"
 #include "internal.h"
@@ -26,7 +27,23 @@ constexpr uint64_t FLAG_AGG = 1ull << 62;
 constexpr uint64_t FLAG_INC = 2ull << 62;
 constexpr uint64_t VALUE_MASK = (1ull << 40) - 1;
 constexpr uint32_t EPOCH_MAX = (1u << 22) - 1;
-constexpr uint32_t SPIN_LIMIT = 1u << 22;
+
+// The lanes of the set v that hold the same digit d: one ballot
+// per digit bit (bits above the digit's width are zero in every lane and
+// leave the set unchanged).  With the lane's bit as a mask m of all zeros or
+// ones, peers & ~(ballot ^ m) is one three-operand bit operation per half.
+template <int BITS>
+__device__ __forceinline__ uint64_t digit_peers(uint32_t d, uint64_t v) {
+    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);
+        const uint64_t bb = __ballot(m != 0);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bb, m, 0x90);          // lo & ~(bb ^ m)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bb >> 32), m, 0x90);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
 
 __device__ __forceinline__ uint64_t pack_status(uint64_t flag, uint32_t epoch, uint64_t v) {
     return flag | ((uint64_t)epoch << 40) | (v & VALUE_MASK);
@@ -74,217 +91,214 @@ __global__ __launch_bounds__(HSTRIDE) void k_hist_scan(const uint64_t* hist, uin
     off[blockIdx.x * HSTRIDE + threadIdx.x] = ex;
 }
 
-// LB = true: onesweep (dynamic tile order, decoupled look-back, digit_off =
-// exclusive digit totals).  LB = false: the scatter of a reduce-then-scan pass
+// The tile of onesweep workgroup b of `grid`.  Workgroups go to the eight dies
+// (each with its own L2) in turn by index; the tiles of every 64 are dealt so
+// that a die gets CHUNK = 8 consecutive ones: their runs of equal digits meet
+// inside cache lines, and the die's L2 merges both sides of such a line before
+// it is written.  The tile is known without a ticket from an atomic counter,
+// whose round trip would come before every tile's loads.  Passes over 2^28
+// pairs, eight and nine bits: 2030 and 2221 us with tile = index, 1691 and 1909
+// with tickets and the dealing, 1684 and 1915 as here, 1707 and 1940 with 16
+// tiles to a die; over 2^22 pairs 34 us as here, 42 with tickets.
+constexpr uint32_t DIES = 8, CHUNK = 8;
+
+__device__ __forceinline__ uint32_t pass_tile(uint32_t b, uint32_t grid) {
+    const uint32_t first = b / (DIES * CHUNK) * (DIES * CHUNK), r = b - first;
+    return first + DIES * CHUNK <= grid ? first + r % DIES * CHUNK + r / DIES : b;
+}
+
+// LB = true: onesweep (decoupled look-back, digit_off = exclusive digit totals).
+// A workgroup whose look-back meets a tile without counts waits for spin_limit
+// polls and then counts its digit in that tile itself, so no order in which
+// workgroups start (another kernel may hold a die) can keep it waiting.  LB = false: the scatter of a reduce-then-scan pass
 // (tile = block index, digit_off = exclusive scan of the per-tile counts laid
 // out digit-major, so entry d * tiles + t is the tile's global base for d).
 // RB: buckets of the digit (256, or 512 for 9-bit digits).  SPLIT: stage the
-// keys, then the payloads (with their digits), through one LDS buffer of
-// 8 B per pair that also holds the per-wave digit counts while the tile is
-// ranked: about 70 KB for an 8192-pair tile, so two workgroups share a compute
-// unit and one's ranking and look-back overlap the other's memory traffic.
+// keys, then the payloads, through one LDS buffer of 8 B per pair that also
+// holds the per-wave digit counts while the tile is ranked: about 67 KB for an
+// 8192-pair tile, so two workgroups share a compute unit and one's ranking and
+// look-back overlap the other's memory traffic.  Bound by that overlap: about
+// half the time the vector units rank (4 operations per digit bit and key),
+// the rest waits on memory at 24 B per pair.  2^28 pairs, 8-bit digit: 1787 us
+// (3.6 TB/s) before the ranking's three-operand bit operations, the dealing of
+// tiles and the keys loaded ahead of the payloads, 1668 us (3.9 TB/s) with them.
 template <int NT, int IPT, bool FINAL, bool LB, int RB, bool SPLIT>
 __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                  uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, uint64_t n,
                                                  uint32_t shift, uint32_t dbits, const uint64_t* __restrict__ digit_off,
-                                                 uint64_t* lookback, uint32_t* tile_counter, uint32_t epoch,
-                                                 uint32_t* status, FinalOut fo) {
+                                                 uint64_t* lookback, uint32_t epoch, uint32_t spin_limit, FinalOut fo) {
     constexpr int TILE = NT * IPT;
     constexpr int WAVES = NT / 64;
     static_assert(NT >= RB, "one thread per digit");
     constexpr int STAGE_K = TILE * 8;            // bytes of the staged keys
     constexpr int WH = WAVES * RB * 4;           // bytes of the per-wave digit counts
-    static_assert(!SPLIT || (WH <= STAGE_K && TILE * 6 <= STAGE_K), "split staging layout");
-    __shared__ uint32_t s_tile;
-    __shared__ uint32_t tile_start[RB];          // first LDS slot of each digit in the tile
-    __shared__ uint64_t glob_base[RB];           // global position of the tile's first key of each digit
+    static_assert(!SPLIT || WH <= STAGE_K, "split staging layout");
+    __shared__ uint64_t out_base[RB];            // global position of LDS slot 0 if it held digit d (may wrap below 0)
     __shared__ uint64_t scan_scratch[NT / 64];
     __shared__ __align__(16) unsigned char pool[SPLIT ? STAGE_K : STAGE_K + TILE * 4 + WH];
     auto wave_hist = reinterpret_cast<uint32_t (*)[RB]>(SPLIT ? pool : pool + STAGE_K + TILE * 4);
     uint64_t* stage_k = reinterpret_cast<uint64_t*>(pool);
     uint32_t* stage_v = reinterpret_cast<uint32_t*>(SPLIT ? pool : pool + STAGE_K);
-    uint16_t* stage_d = reinterpret_cast<uint16_t*>(pool + TILE * 4);   // SPLIT: digit of each staged payload
 
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (LB && threadIdx.x == 0) s_tile = atomicAdd(tile_counter, 1u);
     for (uint32_t i = threadIdx.x; i < WAVES * RB; i += NT) (&wave_hist[0][0])[i] = 0;
     __syncthreads();
-    const uint64_t tile = LB ? (uint64_t)s_tile : (uint64_t)blockIdx.x;
+    const uint64_t tile = LB ? pass_tile(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint64_t base = tile * TILE;
     const uint32_t mask = (1u << dbits) - 1;
 
-    // striped load within each wave: item k of lane l is element base + wave*64*IPT + k*64 + l
-    uint64_t key[IPT];
-    uint32_t val[IPT];
-    uint32_t rank[IPT];
-    const uint64_t wbase = base + (uint64_t)wave * 64 * IPT + lane;
-    if (base + TILE <= n) {      // full tile: no per-element guards
+    // full: no per-element guards (every tile but the last)
+    auto run = [&](auto full_tile) {
+        constexpr bool full = decltype(full_tile)::value;
+        // striped load within each wave: item k of lane l is element base + wave*64*IPT + k*64 + l
+        uint64_t key[IPT];
+        uint32_t val[IPT];
+        uint32_t rank[IPT];
+        const uint64_t wbase = base + (uint64_t)wave * 64 * IPT + lane;
+        if constexpr (full) {
 #pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            key[k] = kin[wbase + (uint64_t)k * 64];
-            val[k] = vin[wbase + (uint64_t)k * 64];
-        }
-    } else {
+            for (int k = 0; k < IPT; ++k) key[k] = kin[wbase + (uint64_t)k * 64];
+            __builtin_amdgcn_sched_barrier(0);   // keys first: the ranking below waits for them alone
 #pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            const uint64_t i = wbase + (uint64_t)k * 64;
-            key[k] = i < n ? kin[i] : 0ull;
-            val[k] = i < n ? vin[i] : 0u;
-        }
-    }
-    const uint64_t lt_mask = (1ull << lane) - 1;
-    constexpr int MAXBITS = RB == 512 ? 9 : 8;   // digits of a pass have at most this many bits
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-        const uint64_t i = wbase + (uint64_t)k * 64;
-        const bool valid = i < n;
-        const uint32_t d = valid ? (uint32_t)((key[k] >> shift) & mask) : 0u;
-        // lanes holding the same digit: one ballot per digit bit (bits above
-        // dbits are zero in every lane and leave the set unchanged)
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < MAXBITS; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = __ballot(bit);
-            peers &= bit ? bb : ~bb;
-        }
-        uint32_t r = 0;
-        if (valid) {
-            const uint32_t before = wave_hist[wave][d];
-            r = before + (uint32_t)__popcll(peers & lt_mask);
-            // the highest peer advances the wave's counter of this digit
-            if ((peers >> lane) == 1ull) wave_hist[wave][d] = before + (uint32_t)__popcll(peers);
-        }
-        rank[k] = r;
-        __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-
-    // per digit: tile count, per-wave offsets, look-back over earlier tiles
-    const uint32_t d = threadIdx.x;
-    const bool digit_thread = d < RB;
-    uint32_t cnt = 0;
-    uint32_t woff[WAVES];
-    uint64_t excl = 0;
-    if (digit_thread) {
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            woff[w] = cnt;
-            cnt += wave_hist[w][d];
-        }
-        uint64_t* my = lookback + tile * RB + d;
-        if (!LB) {
-            // offsets known from the reduce-then-scan counts
-        } else if (tile == 0) {
-            __hip_atomic_store(my, pack_status(FLAG_INC, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < IPT; ++k) val[k] = vin[wbase + (uint64_t)k * 64];
+            __builtin_amdgcn_sched_barrier(0);
         } else {
-            __hip_atomic_store(my, pack_status(FLAG_AGG, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int64_t pred = (int64_t)tile - 1;
-            uint32_t spins = 0;
-            while (pred >= 0) {
-                const uint64_t st = __hip_atomic_load(lookback + (uint64_t)pred * RB + d, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t flag = st & (3ull << 62);
-                const uint32_t ep = (uint32_t)((st >> 40) & EPOCH_MAX);
-                if (flag != 0 && ep == epoch) {
-                    excl += st & VALUE_MASK;
-                    if (flag == FLAG_INC) break;
-                    --pred;
-                    continue;
-                }
-                if (++spins > SPIN_LIMIT || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                    atomicOr(status, 1u);   // bounded wait exceeded: flag the failure and finish the tile
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            __hip_atomic_store(my, pack_status(FLAG_INC, epoch, excl + cnt), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    // digit start within the tile (exclusive scan over digits)
-    uint64_t tot;
-    const uint32_t start = (uint32_t)block_excl_scan<NT, uint64_t>((uint64_t)cnt, scan_scratch, &tot);
-    if (digit_thread) {
-        tile_start[d] = start;
-        glob_base[d] = LB ? digit_off[d] + excl : digit_off[(uint64_t)d * ((n + TILE - 1) / TILE) + tile];
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) wave_hist[w][d] = start + woff[w];
-    }
-    __syncthreads();
-
-    const uint32_t tile_n = (uint32_t)min((uint64_t)TILE, n - base);
-    if constexpr (SPLIT) {
-        // slots first: the counts share the staging buffer
+            for (int k = 0; k < IPT; ++k) {
+                const uint64_t i = wbase + (uint64_t)k * 64;
+                key[k] = i < n ? kin[i] : 0ull;
+                val[k] = i < n ? vin[i] : 0u;
+            }
+        }
+        constexpr int MAXBITS = RB == 512 ? 9 : 8;   // digits of a pass have at most this many bits
 #pragma unroll
         for (int k = 0; k < IPT; ++k) {
-            const uint32_t dd = (uint32_t)((key[k] >> shift) & mask);
-            rank[k] += wave_hist[wave][dd];
+            const bool valid = full || wbase + (uint64_t)k * 64 < n;
+            const uint32_t d = (uint32_t)(key[k] >> shift) & mask;
+            const uint64_t peers = digit_peers<MAXBITS>(d, full ? ~0ull : __ballot(valid));
+            uint32_t r = 0;
+            if (valid) {
+                const uint32_t before = wave_hist[wave][d];
+                r = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+                // the highest peer advances the wave's counter of this digit
+                if ((peers >> lane) == 1ull) wave_hist[wave][d] = r + 1;
+            }
+            rank[k] = r;
+            __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
+
+        // per digit: tile count, per-wave offsets, look-back over earlier tiles
+        const uint32_t d = threadIdx.x;
+        const bool digit_thread = d < RB;
+        uint32_t cnt = 0;
+        uint32_t woff[WAVES];
+        uint64_t excl = 0;
+        if (digit_thread) {
 #pragma unroll
-        for (int k = 0; k < IPT; ++k)
-            if (wbase + (uint64_t)k * 64 < n) stage_k[rank[k]] = key[k];
-        __syncthreads();
-#pragma unroll 4
-        for (uint32_t s = threadIdx.x; s < tile_n; s += NT) {
-            const uint64_t k = stage_k[s];
-            const uint32_t dd = (uint32_t)((k >> shift) & mask);
-            const uint64_t g = glob_base[dd] + (s - tile_start[dd]);
-            if constexpr (FINAL) {
-                fo.src[g] = (int32_t)(k >> fo.tgt_shift);
-                fo.tgt[g] = (int32_t)((k >> 16) & fo.tgt_mask);
-                fo.delay[g] = (uint16_t)(k & 0xffffu);
+            for (int w = 0; w < WAVES; ++w) {
+                woff[w] = cnt;
+                cnt += wave_hist[w][d];
+            }
+            uint64_t* my = lookback + tile * RB + d;
+            if (!LB) {
+                // offsets known from the reduce-then-scan counts
+            } else if (tile == 0) {
+                __hip_atomic_store(my, pack_status(FLAG_INC, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             } else {
-                kout[g] = k;
+                __hip_atomic_store(my, pack_status(FLAG_AGG, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int64_t pred = (int64_t)tile - 1;
+                uint32_t spins = 0;
+                while (pred >= 0) {
+                    const uint64_t st = __hip_atomic_load(lookback + (uint64_t)pred * RB + d, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+                    const uint64_t flag = st & (3ull << 62);
+                    const uint32_t ep = (uint32_t)((st >> 40) & EPOCH_MAX);
+                    if (flag != 0 && ep == epoch) {
+                        excl += st & VALUE_MASK;
+                        if (flag == FLAG_INC) break;
+                        --pred;
+                        continue;
+                    }
+                    if (spins++ >= spin_limit) {   // its keys are all there: every tile before the last is full
+                        const uint64_t* pk = kin + (uint64_t)pred * TILE;
+                        uint32_t c = 0;
+#pragma unroll 1
+                        for (int i = 0; i < TILE; ++i) c += ((uint32_t)(pk[i] >> shift) & mask) == d ? 1u : 0u;
+                        excl += c;
+                        --pred;
+                        continue;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                __hip_atomic_store(my, pack_status(FLAG_INC, epoch, excl + cnt), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
             }
         }
+        // digit start within the tile (exclusive scan over digits)
+        uint32_t tot;
+        const uint32_t start = block_excl_scan<NT, uint32_t>(cnt, reinterpret_cast<uint32_t*>(scan_scratch), &tot);
+        if (digit_thread) {
+            out_base[d] = (LB ? digit_off[d] + excl : digit_off[(uint64_t)d * ((n + TILE - 1) / TILE) + tile]) - start;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) wave_hist[w][d] = start + woff[w];
+        }
         __syncthreads();
+
+        const uint32_t tile_n = (uint32_t)min((uint64_t)TILE, n - base);
+        // slots (with SPLIT the counts share the staging buffer: all slots first)
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) rank[k] += wave_hist[wave][(uint32_t)(key[k] >> shift) & mask];
+        if constexpr (SPLIT) __syncthreads();
 #pragma unroll
         for (int k = 0; k < IPT; ++k)
-            if (wbase + (uint64_t)k * 64 < n) {
-                stage_v[rank[k]] = val[k];
-                stage_d[rank[k]] = (uint16_t)((key[k] >> shift) & mask);
+            if (full || wbase + (uint64_t)k * 64 < n) {
+                stage_k[rank[k]] = key[k];
+                if constexpr (!SPLIT) stage_v[rank[k]] = val[k];
             }
         __syncthreads();
-#pragma unroll 4
-        for (uint32_t s = threadIdx.x; s < tile_n; s += NT) {
-            const uint32_t dd = stage_d[s];
-            const uint64_t g = glob_base[dd] + (s - tile_start[dd]);
-            if constexpr (FINAL) fo.weight[g] = __uint_as_float(stage_v[s]);
-            else vout[g] = stage_v[s];
-        }
-        return;
-    }
-
-    // stage in digit order
+        // every thread writes slots tid, tid + NT, ...: equal digits go to consecutive positions
+        uint32_t dd[IPT];   // digits of the thread's slots, kept for the payloads
 #pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-        const uint64_t i = wbase + (uint64_t)k * 64;
-        if (i < n) {
-            const uint32_t dd = (uint32_t)((key[k] >> shift) & mask);
-            const uint32_t slot = wave_hist[wave][dd] + rank[k];
-            stage_k[slot] = key[k];
-            stage_v[slot] = val[k];
+        for (int k = 0; k < IPT; ++k) {
+            const uint32_t s = threadIdx.x + (uint32_t)k * NT;
+            dd[k] = 0;
+            if (full || s < tile_n) {
+                const uint64_t x = stage_k[s];
+                dd[k] = (uint32_t)(x >> shift) & mask;
+                const uint64_t g = out_base[dd[k]] + s;
+                if constexpr (FINAL) {
+                    fo.src[g] = (int32_t)(x >> fo.tgt_shift);
+                    fo.tgt[g] = (int32_t)((x >> 16) & fo.tgt_mask);
+                    fo.delay[g] = (uint16_t)(x & 0xffffu);
+                } else {
+                    kout[g] = x;
+                }
+                if constexpr (!SPLIT) {
+                    if constexpr (FINAL) fo.weight[g] = __uint_as_float(stage_v[s]);
+                    else vout[g] = stage_v[s];
+                }
+            }
         }
-    }
-    __syncthreads();
-
-#pragma unroll 4
-    for (uint32_t s = threadIdx.x; s < tile_n; s += NT) {
-        const uint64_t k = stage_k[s];
-        const uint32_t dd = (uint32_t)((k >> shift) & mask);
-        const uint64_t g = glob_base[dd] + (s - tile_start[dd]);
-        if constexpr (FINAL) {
-            fo.src[g] = (int32_t)(k >> fo.tgt_shift);
-            fo.tgt[g] = (int32_t)((k >> 16) & fo.tgt_mask);
-            fo.delay[g] = (uint16_t)(k & 0xffffu);
-            fo.weight[g] = __uint_as_float(stage_v[s]);
-        } else {
-            kout[g] = k;
-            vout[g] = stage_v[s];
+        if constexpr (SPLIT) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < IPT; ++k)
+                if (full || wbase + (uint64_t)k * 64 < n) stage_v[rank[k]] = val[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) {
+                const uint32_t s = threadIdx.x + (uint32_t)k * NT;
+                if (full || s < tile_n) {
+                    const uint64_t g = out_base[dd[k]] + s;
+                    if constexpr (FINAL) fo.weight[g] = __uint_as_float(stage_v[s]);
+                    else vout[g] = stage_v[s];
+                }
+            }
         }
-    }
+    };
+    if (base + TILE <= n) run(std::true_type{});
+    else run(std::false_type{});
 }
 
 __global__ void k_unpack(const uint64_t* keys, const uint32_t* vals, uint64_t n, FinalOut fo) {
@@ -306,9 +320,8 @@ struct PassArgs {
     uint32_t shift, dbits;
     const uint64_t* off;
     uint64_t* lookback;
-    uint32_t* counter;
     uint32_t epoch;
-    uint32_t* status;
+    uint32_t spin_limit;
     FinalOut fo;
     int mode;   // 0: onesweep, 1: reduce-then-scan
 };
@@ -356,19 +369,19 @@ void launch_pass(Ctx& c, const PassArgs& a, bool final) {
         off = scanned;
         if (final)
             hipLaunchKernelGGL((k_onesweep<NT, IPT, true, false, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream,
-                               a.kin, a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.counter, a.epoch,
-                               a.status, a.fo);
+                               a.kin, a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch,
+                               a.spin_limit, a.fo);
         else
             hipLaunchKernelGGL((k_onesweep<NT, IPT, false, false, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream,
-                               a.kin, a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.counter, a.epoch,
-                               a.status, a.fo);
+                               a.kin, a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch,
+                               a.spin_limit, a.fo);
     } else if (final) {
         hipLaunchKernelGGL((k_onesweep<NT, IPT, true, true, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
-                           a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.counter, a.epoch, a.status,
+                           a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.spin_limit,
                            a.fo);
     } else {
         hipLaunchKernelGGL((k_onesweep<NT, IPT, false, true, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
-                           a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.counter, a.epoch, a.status,
+                           a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.spin_limit,
                            a.fo);
     }
     HIPCHK(hipGetLastError());
@@ -521,14 +534,12 @@ void fill_words(Ctx& c, uint64_t* p, uint64_t n) {
     HIPCHK(hipGetLastError());
 }
 
-// Scratch of a sort that allocates nothing: digit histograms and offsets,
-// tile counters, a status word and the look-back table, all at fixed
-// addresses; the look-back epoch persists with the table.
+// Scratch of a sort that allocates nothing: digit histograms and offsets and
+// the look-back table, all at fixed addresses; the look-back epoch persists
+// with the table.
 struct FixedScratch {
     uint64_t* hist;
     uint64_t* off;
-    uint32_t* counter;
-    uint32_t* status;
     void* lookback;
     size_t lookback_bytes;
     uint32_t* epoch;
@@ -549,11 +560,10 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
         raise(SNNC_EINVAL, "sort of " + std::to_string(n) + " keys needs a look-back table of " +
                                std::to_string((size_t)tiles * rb * 8) + " bytes, above the " +
                                std::to_string(fs->lookback_bytes) + " of the static scratch");
-    void* temps[3] = {nullptr, nullptr, nullptr};
+    void* temps[2] = {nullptr, nullptr};
     auto cleanup = [&] {
         for (void* p : temps) dfree(c, p);
     };
-    uint32_t* status = fs ? fs->status : c.d_status;
     void* lookback = fs ? fs->lookback : c.lookback;
     uint32_t& epoch = fs ? *fs->epoch : c.sort_epoch;
     const size_t lookback_bytes = fs ? fs->lookback_bytes : 0;
@@ -600,15 +610,6 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
                 lookback = c.lookback;
             }
         }
-        uint32_t* counter;
-        if (fs) {
-            counter = fs->counter;
-            fill_words(c, reinterpret_cast<uint64_t*>(counter), 4);   // 8 tile counters
-        } else {
-            counter = dalloc_n<uint32_t>(c, std::max<uint32_t>(passes, 1));
-            temps[2] = counter;
-            HIPCHK(hipMemsetAsync(counter, 0, std::max<uint32_t>(passes, 1) * 4, c.stream));
-        }
         // passes whose digit is the same for every key leave the order unchanged
         uint32_t live[8];
         uint32_t n_live = 0;
@@ -631,7 +632,7 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
             const bool last = (li + 1 == n_live) && final_out;
             const uint32_t width = pass_bits(bit_lo, bit_hi, plan.n9, dbits, p);
             PassArgs a{kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], n, pass_shift(bit_lo, plan.n9, dbits, p), width,
-                       off + (size_t)p * HSTRIDE, (uint64_t*)lookback, counter + p, epoch, status,
+                       off + (size_t)p * HSTRIDE, (uint64_t*)lookback, epoch, c.lookback_spins,
                        final_out ? *final_out : FinalOut{}, mode};
             tstart(c, sort_timer(c, last ? "pass_final" : "pass").c_str());
             launch_variant(c, variant, a, last, width > 8);
@@ -785,9 +786,7 @@ extern "C" snnc_status snnc_sort_pairs(snnc_ctx* ctx, uint64_t* keys, uint32_t* 
     try {
         HIPCHK(hipSetDevice(ctx->device));
         *result_in_tmp = radix_sort(*ctx, keys, vals, keys_tmp, vals_tmp, n, bit_lo, bit_hi, nullptr, nullptr);
-        uint32_t status = 0;
-        download(*ctx, &status, ctx->d_status, 4);
-        if (status) raise(SNNC_EDEVICE, "a device wait exceeded its bound");
+        HIPCHK(hipStreamSynchronize(ctx->stream));
         return SNNC_OK;
     } catch (const Error& e) {
         ctx->last_error = e.msg;
@@ -798,8 +797,7 @@ extern "C" snnc_status snnc_sort_pairs(snnc_ctx* ctx, uint64_t* keys, uint32_t* 
 // ------------------------------------------------------------------ allocation-free sort
 // One static scratch array per GPU, for callers that cannot allocate device
 // memory.  Layout: digit histograms (8 passes x 512 u64), their offsets
-// (same), 8 tile counters and a status word (256 B), then the look-back
-// table.  Host code reaches it only through the address that
+// (same), then the look-back table.  Host code reaches it only through the address that
 // hipGetSymbolAddress gives for the current device.
 namespace snnc {
 namespace {
@@ -807,9 +805,7 @@ namespace {
 constexpr size_t NA_BYTES = 16u << 20;
 constexpr size_t NA_HIST = 0;
 constexpr size_t NA_OFF = NA_HIST + 8 * HSTRIDE * 8;
-constexpr size_t NA_CNT = NA_OFF + 8 * HSTRIDE * 8;
-constexpr size_t NA_STATUS = NA_CNT + 8 * 4;
-constexpr size_t NA_LB = NA_CNT + 256;
+constexpr size_t NA_LB = NA_OFF + 8 * HSTRIDE * 8 + 256;   // (256 B spare)
 constexpr size_t NA_LB_BYTES = NA_BYTES - NA_LB;
 constexpr int NA_MAX_DEVICES = 64;
 
@@ -867,11 +863,9 @@ extern "C" snnc_status snnc_sort_pairs_noalloc(snnc_ctx* ctx, uint64_t* keys, ui
         NoallocDevice& d = na_devices()[ctx->device];
         if (!d.ptr) raise(SNNC_ESTATE, "static scratch not set up on this device");
         FixedScratch fs{reinterpret_cast<uint64_t*>(d.ptr + NA_HIST), reinterpret_cast<uint64_t*>(d.ptr + NA_OFF),
-                        reinterpret_cast<uint32_t*>(d.ptr + NA_CNT), reinterpret_cast<uint32_t*>(d.ptr + NA_STATUS),
                         d.ptr + NA_LB, NA_LB_BYTES, &d.epoch};
         const int saved_timing = ctx->timing;
         ctx->timing = 0;   // timing brackets would create events
-        fill_words(*ctx, reinterpret_cast<uint64_t*>(d.ptr + NA_CNT), 32);   // counters and status word
         int which = 0;
         try {
             which = radix_sort_impl(*ctx, keys, vals, keys_tmp, vals_tmp, n, bit_lo, bit_hi, nullptr, nullptr, true,
@@ -881,9 +875,7 @@ extern "C" snnc_status snnc_sort_pairs_noalloc(snnc_ctx* ctx, uint64_t* keys, ui
             throw;
         }
         ctx->timing = saved_timing;
-        uint32_t status = 0;
-        download(*ctx, &status, d.ptr + NA_STATUS, 4);
-        if (status) raise(SNNC_EDEVICE, "a device wait exceeded its bound");
+        HIPCHK(hipStreamSynchronize(ctx->stream));
         *result_in_tmp = which;
         return SNNC_OK;
     } catch (const Error& e) {
