@@ -120,18 +120,18 @@ __device__ __forceinline__ uint32_t fastdiv(uint32_t x, const FastDiv& f) {
 }
 
 // Add 1 to bin `bin` of an LDS histogram for every valid lane; when the
-// whole wave hits one bin (common for the high digits of sorted-ish data) a
-// single atomic adds the wave's count.  Call with the whole wave converged.
+// valid lanes of the wave all hit one bin (common for the high digits of
+// sorted-ish data) a single atomic adds their count.
 __device__ __forceinline__ void wave_hist_add(uint32_t* h, uint32_t bin, bool valid) {
-    const uint64_t act = __ballot(valid);
-    if (!act) return;
-    const int leader = __ffsll((unsigned long long)act) - 1;
-    const uint32_t b0 = __builtin_amdgcn_readlane(bin, leader);
-    const uint64_t same = __ballot(valid && bin == b0);
-    if (same == act) {
-        if ((int)(threadIdx.x & 63) == leader) atomicAdd(&h[b0], (uint32_t)__popcll(act));
-    } else if (valid) {
-        atomicAdd(&h[bin], 1u);
+    if (valid) {
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+        const uint64_t act = __ballot(1), same = __ballot(bin == b0);
+        if (same == act) {
+            if (__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u)) == 0)
+                atomicAdd(&h[b0], (uint32_t)__popcll(act));
+        } else {
+            atomicAdd(&h[bin], 1u);
+        }
     }
 }
 

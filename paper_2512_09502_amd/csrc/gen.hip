@@ -1410,6 +1410,21 @@ uint64_t runs_elems(const std::vector<TChunk>& v, uint64_t per_unit) {
     return v.empty() ? 0 : v.back().out_begin + (uint64_t)v.back().n * per_unit;
 }
 
+// Runs of a one-to-one call on `host`.  A run is all autapses (its self
+// position is its target ordinal) or none: with autapses excluded the former
+// are dropped, so the count is known and element g of the kept runs is at g.
+std::vector<TChunk> one_to_one_runs(const Call& cl, uint32_t host) {
+    std::vector<TChunk> kept;
+    uint64_t items = 0;
+    for (TChunk ch : unit_runs(cl.T, cl.autapses ? nullptr : &cl.S, host, 1, MAX_RUN_ELEMS)) {
+        if (!cl.autapses && ch.self_base >= 0 && (uint64_t)ch.self_base == ch.t_ord) continue;
+        ch.out_begin = items;
+        items += ch.n;
+        kept.push_back(ch);
+    }
+    return kept;
+}
+
 SynD syn_of(const Call& cl) {
     SynD s{};
     s.w_mean = cl.w.mean;
@@ -1837,19 +1852,8 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
             break;
         }
         case SNNC_ONE_TO_ONE: {
-            auto runs = unit_runs(cl.T, cl.autapses ? nullptr : &cl.S, host, 1, MAX_RUN_ELEMS);
-            // a run is all autapses (its self position is its target ordinal) or none:
-            // drop those runs on the host, so the count is known and one launch writes
-            // element g of the kept runs at position g
-            std::vector<TChunk> kept;
-            uint64_t items = 0;
-            for (const TChunk& ch : runs) {
-                if (!cl.autapses && ch.self_base >= 0 && (uint64_t)ch.self_base == ch.t_ord) continue;
-                TChunk k = ch;
-                k.out_begin = items;
-                items += ch.n;
-                kept.push_back(k);
-            }
+            const std::vector<TChunk> kept = one_to_one_runs(cl, host);
+            const uint64_t items = runs_elems(kept, 1);
             result = items;
             if (!items) {
                 if (!mark) reserve(0);
@@ -2110,17 +2114,8 @@ bool fused_desc(Ctx& c, Call& cl, FusedReq& q, std::vector<TChunk>& chunks, size
         return true;
     }
     case SNNC_ONE_TO_ONE: {
-        auto runs = unit_runs(cl.T, cl.autapses ? nullptr : &cl.S, host, 1, MAX_RUN_ELEMS);
-        std::vector<TChunk> kept;   // runs that are all autapses are dropped (as in run_call)
-        uint64_t items = 0;
-        for (const TChunk& ch : runs) {
-            if (!cl.autapses && ch.self_base >= 0 && (uint64_t)ch.self_base == ch.t_ord) continue;
-            TChunk k = ch;
-            k.out_begin = items;
-            items += ch.n;
-            kept.push_back(k);
-        }
-        if (items != cl.gen_count) return false;
+        const std::vector<TChunk> kept = one_to_one_runs(cl, host);
+        if (runs_elems(kept, 1) != cl.gen_count) return false;
         q.kind = F_ONE_TO_ONE;
         q.o2o = OneToOne{batch_tab(kept, chunks, chunk_at), 1u};   // autapse runs are gone
         return true;
@@ -2282,8 +2277,15 @@ void flush_batch(Ctx& c, const std::vector<uint32_t>& ids, hipEvent_t done) {
     HIPCHK(hipEventRecord(done, c.stream));
 }
 
-std::vector<TChunk> target_chunks(const Call& cl, uint32_t host, uint64_t K, uint64_t max_elems) {
-    return unit_runs(cl.T, cl.autapses ? nullptr : &cl.S, host, K, max_elems);
+bool target_runs(const Ctx& c, const Call& cl, std::vector<TargetRun>& out) {
+    const bool in = cl.rule == SNNC_FIXED_INDEGREE;
+    if (!in && cl.rule != SNNC_ONE_TO_ONE) return false;
+    const uint64_t K = in ? cl.n : 1;
+    const std::vector<TChunk> runs = in ? unit_runs(cl.T, nullptr, c.P_local, K, MAX_RUN_ELEMS)
+                                        : one_to_one_runs(cl, c.P_local);
+    if (runs_elems(runs, K) != cl.gen_count) return false;
+    for (const TChunk& r : runs) out.push_back(TargetRun{cl.gen_begin + r.out_begin, r.local_first, r.n, (uint32_t)K});
+    return true;
 }
 
 }  // namespace snnc

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <array>
 #include <map>
 #include <memory>
@@ -383,7 +384,6 @@ int fused_grid_tuned(int device);
 bool gen_blocks_supported(int device);
 
 // host-side helpers shared by the planner files
-std::vector<TChunk> target_chunks(const Call& cl, uint32_t host, uint64_t K, uint64_t max_elems);
 bool set_lookup_host(const HostSet& s, uint64_t ord, uint32_t& host, uint32_t& local);
 
 // device-wide scans (scan.hip)
@@ -411,12 +411,15 @@ uint64_t scan_u64_u64(Ctx& c, const uint64_t* in, uint64_t* out, uint64_t n, boo
 // arrays instead (see sort.hip).
 struct FinalOut {
     int32_t* src;
+    uint64_t* prefix64;   // set: the source prefix as 64 bits goes here instead of src
     int32_t* tgt;
     uint16_t* delay;
     float* weight;
     uint32_t tgt_shift;   // key = src << tgt_shift | tgt << 16 | delay
     uint64_t tgt_mask;
 };
+// called for the last pass, with the buffer (0 or 1) it reads
+using FinalOutFn = std::function<FinalOut(int)>;
 // wait_for_plan: read the digit histograms back to skip passes whose digit is
 // the same for every key (a wait on the stream); false runs every pass
 // without waiting (the result is the same: such a pass keeps the order).
@@ -425,7 +428,7 @@ struct FinalOut {
 void noalloc_setup(Ctx& c);
 int radix_sort(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, uint32_t* vals1, uint64_t n,
                uint32_t bit_lo, uint32_t bit_hi, const uint64_t* digit_hist /* may be null */,
-               const FinalOut* final_out, bool wait_for_plan = true);
+               const FinalOutFn& final_out, bool wait_for_plan = true);
 // digit histograms for all passes of a sort (radix 256, D bits per pass)
 // digit histograms: entries per pass (buckets of digits up to 9 bits)
 constexpr int HIST_STRIDE = 512;
@@ -452,6 +455,16 @@ SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits);
 uint32_t hist_grid(uint64_t n);
 // 64 geometric-gap thresholds of a Bernoulli(p) sequence (pairwise Bernoulli rule)
 int sort_variant_count();
+
+void ensure_lookback(Ctx& c, size_t need);
+void next_epoch(Ctx& c);
+// the call's runs of targets on P_local, in generation order: target first + t
+// (t < n) has the K connections at begin + t K; false for rules without such runs
+struct TargetRun {
+    uint64_t begin;
+    uint32_t first, n, K;
+};
+bool target_runs(const Ctx& c, const Call& cl, std::vector<TargetRun>& out);
 
 // prepare pipeline (prepare.hip)
 void prepare_all(Ctx& c);

@@ -4,13 +4,14 @@
 //     read; the source prefix is the local id of a local source, and
 //     M_local + (alpha+1) G + global id of a remote one (global id = host
 //     base + local id), an order that agrees with (alpha+1, sigma, source);
-//  2. source-major radix sort;
-//  3. without remote sources the last pass unpacks the result arrays; with
-//     them, one scan over the sorted keys numbers the images: the first
-//     connection of every distinct remote prefix starts the next image after
-//     the local neurons (the sorted-unique map R of every (alpha+1, sigma) and
-//     the remap of the paper's flag/compact/sort/search/append steps in one
-//     pass), and the same pass unpacks the arrays;
+//     where every call gives each target a run of connections the keys are
+//     written in target order, and the source bits alone remain to be sorted;
+//  2. source-major radix sort to the unpacked arrays;
+//  3. with remote sources, one scan over the sorted prefixes numbers the
+//     images: the first connection of every distinct remote prefix starts the
+//     next image after the local neurons (the sorted-unique map R of every
+//     (alpha+1, sigma) and the remap of the paper's flag/compact/sort/search/
+//     append steps in one pass);
 //  4. R, its per-(alpha+1, sigma) offsets and a bit set of the images;
 //  5. first-index array from the sorted sources;
 //  6. point-to-point send lists: regenerate alpha = -1 draws per target host,
@@ -38,14 +39,11 @@ struct CallD {
     uint32_t flag;   // 1: only the sources its local connections use get images
     uint32_t uniform;   // 1: all source segments have the same length (segment = ordinal / length)
     FastDiv seg_div;
-    const int64_t* seg_base;   // per segment: bit of its first neuron minus its first ordinal
-    uint64_t local_lo;         // bit of P_local's neuron 0 in this call's map index
 };
 
 // segment lookup by division when every source segment of the call has the same length
 CallD make_calld(const Call& cl, uint32_t order, uint32_t flag) {
-    CallD d{cl.gen_begin, cl.dS, (uint32_t)cl.S.seg.size(), (uint32_t)(cl.alpha + 1), order, flag, 0, FastDiv{},
-            nullptr, 0};
+    CallD d{cl.gen_begin, cl.dS, (uint32_t)cl.S.seg.size(), (uint32_t)(cl.alpha + 1), order, flag, 0, FastDiv{}};
     const auto& seg = cl.S.seg;
     bool uniform = seg.size() > 1 && seg[0].n > 0 && cl.S.total < (1ull << 31);
     for (const auto& g : seg) uniform = uniform && g.n == seg[0].n;
@@ -129,40 +127,131 @@ __device__ __forceinline__ void block_range(uint64_t n, uint64_t& lo, uint64_t& 
     hi = lo + per < n ? lo + per : n;
 }
 
+// Source ordinal of a call -> sort prefix (local id, or M_local + (alpha+1) G +
+// global id of a remote source): prefix = ordinal + addend of its segment.
+struct SrcMap {
+    int64_t add;             // the only segment's addend (nS == 1)
+    const int64_t* seg_add;  // per segment
+    const SegD* S;
+    uint64_t div_m;          // equal segment lengths: segment = ordinal * div_m >> div_shift; else 0
+    uint32_t div_shift;
+    uint32_t nS;
+};
+
+// Target-major order.  When every call gives each of its targets a run of K
+// consecutive connections (fixed in-degree, one-to-one), the connections in
+// order of (target, call, element) are known in closed form: the targets fall
+// into intervals covered by the same calls, and inside an interval every
+// target has the same D connections.  With the keys written in that order, a
+// stable sort by the source alone gives the order by (source, target,
+// generation): the target's bits take no passes.
+struct TInterval {
+    uint64_t q0, q1;         // target-major positions [q0, q1)
+    uint32_t first, D;       // first target, connections per target
+    FastDiv div;             // by D (q1 - q0 < 2^31)
+    uint32_t e0, ne;         // its entries
+};
+
+struct TEntry {              // a call's share of an interval: offsets [o, end) of each target's D
+    uint32_t o, end, K, call;
+    int64_t base;            // generation index = base + (target - first) K + offset
+    int64_t add;             // of a call with one source segment
+    uint32_t nS, pad;
+};
+
+struct GenSource {
+    const uint32_t* src;
+    const uint32_t* tgt;
+    const uint16_t* delay;
+    const uint32_t* weight;
+    const SrcMap* maps;            // per call with connections
+    const uint64_t* call_begin;    // [ncalls + 1], the last one N
+    uint32_t ncalls;
+    uint32_t n_iv;
+    const TInterval* iv;
+    const TEntry* ent;
+    const uint32_t* bits;          // images numbered before the sort: their bit set, ranks and indices
+    const uint64_t* word_rank;
+    const int32_t* Lmap;
+    uint32_t M_local, tgt_shift;
+};
+
+// the last of n ascending values at or below x (v[0] <= x)
+__device__ __forceinline__ uint32_t last_at_or_below(const uint64_t* v, uint32_t n, uint64_t x) {
+    uint32_t a = 0, b = n;
+    while (b - a > 1) {
+        const uint32_t m = (a + b) >> 1;
+        if (v[m] <= x) a = m; else b = m;
+    }
+    return a;
+}
+
 __device__ __forceinline__ uint64_t rank_of(const uint32_t* bits, const uint64_t* word_rank, uint64_t bit) {
     const uint64_t w = bit >> 5;
     return word_rank[w] + (uint64_t)__popc(bits[w] & ((1u << (bit & 31)) - 1u));
 }
 
-// source' and the sort key (source' << tgt_shift | target << 16 | delay),
-// with the digit histograms of all radix passes
-__global__ __launch_bounds__(PNT) void k_keys(Lookup L, const uint32_t* g_src, const uint32_t* g_tgt,
-                                              const uint16_t* g_delay, uint64_t n, const uint32_t* bits,
-                                              const uint64_t* word_rank, const int32_t* Lmap, uint32_t M_local,
-                                              uint32_t tgt_shift, uint32_t n9,
-                                              uint32_t dbits, uint32_t passes, uint64_t* keys, uint64_t* hist) {
+__device__ __forceinline__ int64_t segment_add(const SrcMap& m, uint32_t ord) {
+    if (m.nS == 1) return m.add;
+    uint32_t j;
+    if (m.div_m) {
+        j = (uint32_t)(((uint64_t)ord * m.div_m) >> m.div_shift);
+    } else {
+        uint32_t a = 0, b = m.nS;
+        while (b - a > 1) {
+            const uint32_t x = (a + b) >> 1;
+            if (m.S[x].ord_begin <= ord) a = x; else b = x;
+        }
+        j = a;
+    }
+    return m.seg_add[j];
+}
+
+// sort key (source' << tgt_shift | target << 16 | delay).  Remote sources: the
+// image index L when the images were numbered before the sort, else the global
+// prefix (images are numbered after the sort).
+__device__ __forceinline__ uint64_t conn_key(const GenSource& g, int64_t add, uint32_t ord, uint32_t tgt, uint32_t delay) {
+    uint64_t p = (uint64_t)(add + (int64_t)ord);
+    if (g.bits && p >= g.M_local) p = (uint64_t)g.Lmap[rank_of(g.bits, g.word_rank, p - g.M_local)];
+    return (p << g.tgt_shift) | ((uint64_t)tgt << 16) | delay;
+}
+
+// the digits of one key per lane (valid lanes) into the workgroup's histograms; bits above the key's top are zero
+__device__ __forceinline__ void key_digits(uint32_t* h, uint64_t key, bool valid, uint32_t bit_lo, uint32_t n9,
+                                           uint32_t dbits, uint32_t passes) {
+    for (uint32_t p = 0; p < passes; ++p)
+        wave_hist_add(&h[p * HIST_STRIDE],
+                      (uint32_t)(key >> pass_shift(bit_lo, n9, dbits, p)) & (p < n9 ? 0x1ffu : (1u << dbits) - 1), valid);
+}
+
+// Sort keys in generation order, with the digit histograms of all radix
+// passes: 10 B read and 8 B written per connection.
+__global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t bit_lo, uint32_t n9, uint32_t dbits,
+                                              uint32_t passes, uint64_t* keys, uint64_t* hist) {
     __shared__ uint32_t h[8 * HIST_STRIDE];
     for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT) h[i] = 0;
     __syncthreads();
     uint64_t lo, hi;
     block_range(n, lo, hi);
-    // call of the current window (a workgroup's range crosses few calls)
-    uint64_t call_lo = 1, call_hi = 0;
-    CallD cd{};
-    uint32_t last_sidx = ~0u;   // segment whose base is cached (single-segment calls load it once)
-    int64_t last_base = 0;
     constexpr int KU = 4;   // independent elements per thread per step: their table loads overlap
+    uint64_t call_end = 0;  // end of the call that holds the step's first element
+    SrcMap m{};
     for (uint64_t base = lo; base < hi; base += (uint64_t)PNT * KU) {
-        uint32_t ord[KU], tg[KU];
-        uint16_t dl[KU];
+        uint32_t ord[KU], tg[KU], dl[KU];
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
             const uint64_t i = base + (uint64_t)u * PNT + threadIdx.x;
+            ord[u] = tg[u] = dl[u] = 0;
             if (i < hi) {
-                ord[u] = g_src[i];
-                tg[u] = g_tgt[i];
-                dl[u] = g_delay[i];
+                ord[u] = g.src[i];
+                tg[u] = g.tgt[i];
+                dl[u] = g.delay[i];
             }
+        }
+        if (base >= call_end) {   // the same in every thread
+            const uint32_t c = last_at_or_below(g.call_begin, g.ncalls, base);
+            call_end = g.call_begin[c + 1];
+            m = g.maps[c];
         }
         uint64_t key[KU];
 #pragma unroll
@@ -170,45 +259,99 @@ __global__ __launch_bounds__(PNT) void k_keys(Lookup L, const uint32_t* g_src, c
             const uint64_t i = base + (uint64_t)u * PNT + threadIdx.x;
             key[u] = 0;
             if (i >= hi) continue;
-            if (i < call_lo || i >= call_hi) {
-                const uint32_t k = find_call(L.calls, L.ncalls, i);
-                cd = L.calls[k];
-                call_lo = cd.gen_begin;
-                call_hi = k + 1 < L.ncalls ? L.calls[k + 1].gen_begin : ~0ull;
-                last_sidx = ~0u;
-            }
-            uint32_t sidx;
-            if (cd.uniform) {
-                sidx = fastdiv(ord[u], cd.seg_div);
-            } else {
-                uint32_t a = 0, b = cd.nS;
-                while (b - a > 1) {
-                    const uint32_t m = (a + b) >> 1;
-                    if (cd.S[m].ord_begin <= ord[u]) a = m; else b = m;
-                }
-                sidx = a;
-            }
-            if (sidx != last_sidx) {
-                last_base = cd.seg_base[sidx];
-                last_sidx = sidx;
-            }
-            const uint64_t bit = (uint64_t)(last_base + (int64_t)ord[u]);
-            const uint64_t rel = bit - cd.local_lo;   // the local neuron, when below M_local
-            // remote sources: the image index L when the images were numbered before the sort,
-            // else the global prefix M_local + bit (images are numbered after the sort)
-            const uint64_t src2 = rel < M_local ? rel
-                                  : bits        ? (uint64_t)Lmap[rank_of(bits, word_rank, bit)]
-                                                : (uint64_t)M_local + bit;
-            key[u] = (src2 << tgt_shift) | ((uint64_t)tg[u] << 16) | dl[u];
+            const int64_t add = i < call_end ? segment_add(m, ord[u])
+                                             : segment_add(g.maps[last_at_or_below(g.call_begin, g.ncalls, i)], ord[u]);
+            key[u] = conn_key(g, add, ord[u], tg[u], dl[u]);
             keys[i] = key[u];
         }
 #pragma unroll
-        for (int u = 0; u < KU; ++u) {
-            const bool valid = base + (uint64_t)u * PNT + threadIdx.x < hi;
-            for (uint32_t p = 0; p < passes; ++p)   // bits above the key's top are zero
-                wave_hist_add(&h[p * HIST_STRIDE],
-                              (uint32_t)((key[u] >> pass_shift(16, n9, dbits, p)) & ((p < n9 ? 0x1ffu : (1u << dbits) - 1))),
-                              valid);
+        for (int u = 0; u < KU; ++u)
+            key_digits(h, key[u], base + (uint64_t)u * PNT + threadIdx.x < hi, bit_lo, n9, dbits, passes);
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT)
+        if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
+}
+
+// The same in target-major order, with the weights moved along: 10 B read
+// (source, delay, weight) and 12 B written per connection.  A wave takes TM_UNIT
+// consecutive positions; it walks the runs of a call in them one after
+// another (all their parameters the same in every lane, so scalar) and each
+// run by 64 lanes x 4.  The alternative of letting the first radix pass gather
+// its own connections was slower: the pass ranks 16 keys a lane at 16 waves a
+// compute unit, and waits for the gather (multi-area: first pass 10.3 ms
+// instead of 4.1, against 3.3 for this kernel).
+constexpr uint32_t TM_UNIT = 2048;
+
+__global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, uint32_t bit_lo, uint32_t n9,
+                                                     uint32_t dbits, uint32_t passes, uint64_t* keys, uint32_t* vals,
+                                                     uint64_t* hist) {
+    __shared__ uint32_t h[8 * HIST_STRIDE];
+    for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT) h[i] = 0;
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (uint64_t unit = (uint64_t)blockIdx.x * (PNT / 64) + wave; unit * TM_UNIT < n;
+         unit += (uint64_t)gridDim.x * (PNT / 64)) {
+        uint64_t q = unit * TM_UNIT;
+        const uint64_t end = q + TM_UNIT < n ? q + TM_UNIT : n;
+        uint32_t a = 0, b = g.n_iv;
+        while (b - a > 1) {
+            const uint32_t m = (a + b) >> 1;
+            if (g.iv[m].q0 <= q) a = m; else b = m;
+        }
+        TInterval v = g.iv[a];
+        uint32_t t = fastdiv((uint32_t)(q - v.q0), v.div);
+        uint32_t r = (uint32_t)(q - v.q0) - t * v.D;
+        uint32_t e = v.e0, f = v.e0 + v.ne;
+        while (f - e > 1) {
+            const uint32_t m = (e + f) >> 1;
+            if (g.ent[m].o <= r) e = m; else f = m;
+        }
+        while (q < end) {   // one call's run of one target, or what of it lies in the unit
+            const TEntry en = g.ent[e];
+            const uint32_t len = (uint32_t)min((uint64_t)(en.end - r), end - q);
+            const uint64_t i0 = (uint64_t)(en.base + (int64_t)((uint64_t)t * en.K) + r);
+            const uint32_t tgt = v.first + t;
+            constexpr int KU = 4;
+            for (uint32_t x0 = 0; x0 < len; x0 += 64 * KU) {
+                uint32_t ord[KU], dl[KU], w[KU];
+#pragma unroll
+                for (int u = 0; u < KU; ++u) {
+                    const uint32_t x = x0 + u * 64 + lane;
+                    ord[u] = dl[u] = w[u] = 0;
+                    if (x < len) {
+                        ord[u] = g.src[i0 + x];
+                        dl[u] = g.delay[i0 + x];
+                        w[u] = g.weight[i0 + x];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < KU; ++u) {
+                    if (x0 + u * 64 >= len) break;   // the same in every lane
+                    const uint32_t x = x0 + u * 64 + lane;
+                    uint64_t key = 0;
+                    if (x < len) {
+                        const int64_t add = en.nS == 1 ? en.add : segment_add(g.maps[en.call], ord[u]);
+                        key = conn_key(g, add, ord[u], tgt, dl[u]);
+                        keys[q + x] = key;
+                        vals[q + x] = w[u];
+                    }
+                    key_digits(h, key, x < len, bit_lo, n9, dbits, passes);
+                }
+            }
+            q += len;
+            r += len;
+            ++e;
+            if (r == v.D) {   // next target, or the next interval's first
+                r = 0;
+                ++t;
+                if (q == v.q1 && q < end) {
+                    v = g.iv[++a];
+                    t = 0;
+                }
+                e = v.e0;
+            }
         }
     }
     __syncthreads();
@@ -217,37 +360,28 @@ __global__ __launch_bounds__(PNT) void k_keys(Lookup L, const uint32_t* g_src, c
 }
 
 // ---- image numbering after the sort (networks with remote sources)
-// The keys were sorted with source prefix p = local id (local source) or
-// M_local + (alpha+1) G + global id (remote source); both orders agree with
-// (alpha+1, sigma, s).  One pass over the sorted keys numbers the images: the
-// first key of every distinct remote prefix starts a new image, and a scan of
-// these flags (decoupled look-back across tiles) gives each connection its
-// image index.  The same pass unpacks the connection arrays, records each
-// image's prefix and writes the first-index array.
-// Tile shapes (threads, items per thread; whether the payload is loaded with
-// the keys, before the look-back).  Measured on the 6.4e8- and 2.25e9-connection
-// remote-source networks: larger tiles win (fewer look-back steps per element)
-// and loading the payload early hides its latency behind the look-back; 1024
-// threads x 10 items with the early payload is the fastest shape that does
-// not spill (variant 10, the default).
+// The connections were sorted with source prefix p = local id (local source)
+// or M_local + (alpha+1) G + global id (remote source); both orders agree with
+// (alpha+1, sigma, s).  One pass over the sorted prefixes numbers the images:
+// the first connection of every distinct remote prefix starts a new image, and
+// a scan of these flags (decoupled look-back across tiles) gives each
+// connection its source'.  The same pass records each image's prefix and writes
+// the first-index array.  4 B read and written per connection (the last radix
+// pass has written the other arrays).
+// Tile shapes: threads, items per thread.
 struct NumberShape {
     int nt, ipt;
-    bool early_vals;
 };
-constexpr NumberShape NUMBER_SHAPES[] = {{1024, 12, false}, {512, 12, false}, {256, 12, false},
-                                         {512, 12, true},   {256, 12, true},  {256, 16, true},
-                                         {256, 8, true},    {256, 6, true},   {512, 8, true},
-                                         {1024, 12, true},  {1024, 10, true}, {1024, 8, true}};
+constexpr NumberShape NUMBER_SHAPES[] = {{1024, 12}, {512, 12}, {256, 12}, {512, 12}, {256, 12}, {256, 16},
+                                         {256, 8}, {256, 6}, {512, 8}, {1024, 12}, {1024, 10}, {1024, 8}};
 constexpr int NUMBER_VARIANTS = (int)(sizeof(NUMBER_SHAPES) / sizeof(NUMBER_SHAPES[0]));
 constexpr uint64_t XFLAG_AGG = 1ull << 62, XFLAG_INC = 2ull << 62, XVALUE = (1ull << 40) - 1;
 constexpr uint32_t XEPOCH_MAX = (1u << 22) - 1;
 
-template <int XNT, int XIPT, bool EARLY_VALS>
-__global__ __launch_bounds__(XNT) void k_number(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals,
-                                                uint64_t n, uint32_t tgt_shift, uint64_t tgt_mask, uint32_t M_local,
+template <int XNT, int XIPT, class P>
+__global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, uint64_t n, uint32_t M_local,
                                                 uint64_t* lookback, uint32_t* tile_counter, uint32_t epoch,
-                                                uint32_t* status, int32_t* o_src, int32_t* o_tgt, uint16_t* o_delay,
-                                                float* o_weight, uint64_t* img_key, uint64_t* row_ptr,
+                                                uint32_t* status, int32_t* o_src, uint64_t* img_key, uint64_t* row_ptr,
                                                 uint64_t* n_img_out) {
     __shared__ uint32_t s_tile;
     __shared__ uint64_t wave_tot[XNT / 64];
@@ -258,30 +392,30 @@ __global__ __launch_bounds__(XNT) void k_number(const uint64_t* __restrict__ key
     const uint64_t tile = s_tile;
     constexpr uint64_t XTILE = (uint64_t)XNT * XIPT;
     const uint64_t wbase = tile * XTILE + (uint64_t)wave * 64 * XIPT;
-    // element of item k on this lane: wbase + k*64 + lane (wave-striped, so loads and stores coalesce);
-    // the keys stay in registers for the second half (a reload would come from HBM again)
-    uint64_t key[XIPT];
-    uint32_t val[EARLY_VALS ? XIPT : 1];
+    // element of item k on this lane: wbase + k*64 + lane (wave-striped, so loads and stores coalesce)
+    P key[XIPT];
     uint32_t incl[XIPT];          // flags up to and including the item, within the wave
     uint32_t fl = 0;              // bit k: item k starts a new image
-    const uint64_t before_wave = wbase > 0 && wbase - 1 < n ? (keys[wbase - 1] >> tgt_shift) : ~0ull;
-    uint64_t last = before_wave;  // prefix before the wave
+    const P before_wave = wbase > 0 && wbase - 1 < n ? prefix[wbase - 1] : ~(P)0;
+    P last = before_wave;         // prefix before the wave
     uint32_t carry = 0;
 #pragma unroll
     for (int k = 0; k < XIPT; ++k) {
         const uint64_t i = wbase + (uint64_t)k * 64 + lane;
-        key[k] = i < n ? keys[i] : ~0ull;
-        if constexpr (EARLY_VALS) val[k] = i < n ? vals[i] : 0u;
-        const uint64_t pk = i < n ? key[k] >> tgt_shift : ~0ull;
-        uint64_t prev = __shfl_up(pk, 1, 64);
-        const uint64_t last_lane = __shfl(pk, 63, 64);
+        key[k] = i < n ? prefix[i] : ~(P)0;
+    }
+    const uint64_t upto = ~0ull >> (63 - lane);   // lanes up to and including this one
+#pragma unroll
+    for (int k = 0; k < XIPT; ++k) {
+        const uint64_t i = wbase + (uint64_t)k * 64 + lane;
+        P prev = __shfl_up(key[k], 1, 64);
         if (lane == 0) prev = last;
-        last = last_lane;
-        const uint32_t f = (i < n && pk >= M_local && (i == 0 || pk != prev)) ? 1u : 0u;
-        fl |= f << k;
-        const uint32_t s = wave_incl_scan(f);
-        incl[k] = carry + s;
-        carry += __shfl(s, 63, 64);
+        last = __shfl(key[k], 63, 64);
+        const bool f = i < n && key[k] >= M_local && (i == 0 || key[k] != prev);
+        fl |= (f ? 1u : 0u) << k;
+        const uint64_t m = __ballot(f);
+        incl[k] = carry + (uint32_t)__popcll(m & upto);
+        carry += (uint32_t)__popcll(m);
     }
     if (lane == 63) wave_tot[wave] = carry;
     __syncthreads();
@@ -326,27 +460,19 @@ __global__ __launch_bounds__(XNT) void k_number(const uint64_t* __restrict__ key
 #pragma unroll
     for (int k = 0; k < XIPT; ++k) {
         const uint64_t i = wbase + (uint64_t)k * 64 + lane;
-        const uint64_t pk = key[k] >> tgt_shift;
-        // prefix of the previous connection, again from the neighbouring lane
-        uint64_t pp = __shfl_up(pk, 1, 64);
-        const uint64_t last_lane = __shfl(pk, 63, 64);
+        P pp = __shfl_up(key[k], 1, 64);     // prefix of the previous connection
         if (lane == 0) pp = last;
-        last = last_lane;
+        last = __shfl(key[k], 63, 64);
         const uint64_t rank = before + incl[k];                 // images started up to and including i
         int64_t lo = 0, hi = -1, end_lo = 0, end_hi = -1;       // rows closed here and after the last connection
         if (i < n) {
-            const bool local = pk < M_local;
-            const int64_t src2 = local ? (int64_t)pk : (int64_t)(M_local + rank - 1);
+            const int64_t src2 = key[k] < M_local ? (int64_t)key[k] : (int64_t)(M_local + rank - 1);
             o_src[i] = (int32_t)src2;
-            o_tgt[i] = (int32_t)((key[k] >> 16) & tgt_mask);
-            o_delay[i] = (uint16_t)(key[k] & 0xffffu);
-            if constexpr (EARLY_VALS) o_weight[i] = __uint_as_float(val[k]);
-            else o_weight[i] = __uint_as_float(vals[i]);
             // previous connection's source' (its flag count is rank minus this item's flag)
             const bool flag_here = (fl >> k) & 1u;
             int64_t prev2 = -1;
             if (i > 0) prev2 = pp < M_local ? (int64_t)pp : (int64_t)(M_local + rank - (flag_here ? 1 : 0) - 1);
-            if (flag_here) img_key[rank - 1] = pk - M_local;
+            if (flag_here) img_key[rank - 1] = (uint64_t)key[k] - M_local;
             lo = prev2 + 1;
             hi = src2;
             if (i + 1 == n) {
@@ -821,6 +947,81 @@ void place_memory_level(Ctx& c, uint32_t M_local) {
         to_host(c, id);
 }
 
+// Intervals of targets covered by the same calls, and the calls' entries in
+// them (see TInterval), from the calls' runs (in call order).  False when some
+// call has no such runs, or they are short (fewer than 16 connections a run on
+// average: a run takes at least one step of a wave), or the tables would be long.
+bool target_major(const Ctx& c, const std::vector<uint32_t>& with_conns, const std::vector<SrcMap>& maps,
+                  std::vector<TInterval>& iv, std::vector<TEntry>& ent) {
+    constexpr size_t MAX_ENTRIES = 1u << 16;
+    struct Run {
+        TargetRun r;
+        uint32_t call;
+    };
+    std::vector<Run> runs;
+    std::vector<TargetRun> tmp;
+    for (uint32_t k = 0; k < with_conns.size(); ++k) {
+        tmp.clear();
+        if (!target_runs(c, c.calls[with_conns[k]], tmp)) return false;
+        for (auto& r : tmp)
+            if (r.n && r.K) runs.push_back(Run{r, k});
+        if (runs.size() > MAX_ENTRIES) return false;
+    }
+    std::vector<uint64_t> cuts;
+    for (auto& x : runs) {
+        cuts.push_back(x.r.first);
+        cuts.push_back((uint64_t)x.r.first + x.r.n);
+    }
+    std::sort(cuts.begin(), cuts.end());
+    cuts.erase(std::unique(cuts.begin(), cuts.end()), cuts.end());
+    std::sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.r.first < b.r.first; });
+    std::map<uint32_t, TargetRun> active;   // by call: a set lists a neuron once, so one run per call
+    size_t next = 0;
+    uint64_t q = 0, n_runs = 0;
+    for (size_t i = 0; i + 1 < cuts.size(); ++i) {
+        for (auto it = active.begin(); it != active.end();)
+            it = (uint64_t)it->second.first + it->second.n <= cuts[i] ? active.erase(it) : std::next(it);
+        for (; next < runs.size() && runs[next].r.first <= cuts[i]; ++next) active[runs[next].call] = runs[next].r;
+        if (active.empty()) continue;
+        if (ent.size() + active.size() > MAX_ENTRIES) return false;
+        uint64_t D = 0;
+        for (auto& kv : active) D += kv.second.K;
+        if (D > 0x7fffffffull) return false;
+        const uint64_t max_n = 0x7fffffffull / D;   // positions inside an interval stay below 2^31
+        for (uint64_t t = cuts[i]; t < cuts[i + 1];) {
+            const uint64_t n = std::min(max_n, cuts[i + 1] - t);
+            if (ent.size() + active.size() > MAX_ENTRIES) return false;
+            TInterval v{};
+            v.q0 = q;
+            v.q1 = q + n * D;
+            v.first = (uint32_t)t;
+            v.D = (uint32_t)D;
+            v.div = make_fastdiv((uint32_t)D);
+            v.e0 = (uint32_t)ent.size();
+            v.ne = (uint32_t)active.size();
+            uint64_t o = 0;
+            for (auto& kv : active) {
+                const TargetRun& r = kv.second;
+                TEntry e{};
+                e.o = (uint32_t)o;
+                e.end = (uint32_t)(o + r.K);
+                e.K = r.K;
+                e.call = kv.first;
+                e.base = (int64_t)(r.begin + (t - r.first) * r.K) - (int64_t)o;
+                e.add = maps[kv.first].add;
+                e.nS = maps[kv.first].nS;
+                ent.push_back(e);
+                o += r.K;
+            }
+            iv.push_back(v);
+            q = v.q1;
+            n_runs += n * active.size();
+            t += n;
+        }
+    }
+    return q == c.n_gen && n_runs * 16 <= q;
+}
+
 }  // namespace
 
 int number_variant_count() { return NUMBER_VARIANTS; }
@@ -851,29 +1052,30 @@ void prepare_all(Ctx& c) {
         std::vector<uint8_t> flag_local(n_calls);
         for (uint32_t k = 0; k < n_calls; ++k) flag_local[k] = flag_sources(c, c.calls[k], PL) ? 1 : 0;
         std::vector<CallD> calls;
-        std::vector<int64_t> seg_base;   // all calls' segment tables, concatenated
+        std::vector<uint32_t> with_conns;   // calls with connections on this host
+        std::vector<SrcMap> maps;
+        std::vector<uint64_t> call_begin;
+        std::vector<int64_t> seg_add;       // all calls' segment tables, concatenated
         std::vector<size_t> seg_at;
         for (uint32_t k = 0; k < n_calls; ++k) {
             const Call& cl = c.calls[k];
             if (!cl.gen_count) continue;
-            CallD d = make_calld(cl, k, flag_local[k]);
-            const uint64_t a = (uint64_t)(cl.alpha + 1);
-            seg_at.push_back(seg_base.size());
-            for (size_t j = 0; j < cl.S.seg.size(); ++j)
-                seg_base.push_back((int64_t)(a * G + host_base[cl.S.seg[j].host] + cl.S.seg[j].first) -
-                                   (int64_t)cl.S.ord_begin[j]);
-            d.local_lo = a * G + host_base[PL];
+            const CallD d = make_calld(cl, k, flag_local[k]);
             calls.push_back(d);
+            const uint64_t a = (uint64_t)(cl.alpha + 1);
+            seg_at.push_back(seg_add.size());
+            for (size_t j = 0; j < cl.S.seg.size(); ++j) {
+                const snnc_segment& g = cl.S.seg[j];
+                const uint64_t remote = M_local + a * G + host_base[g.host] + g.first;
+                seg_add.push_back((int64_t)(g.host == PL ? g.first : remote) - (int64_t)cl.S.ord_begin[j]);
+            }
+            maps.push_back(SrcMap{seg_add[seg_at.back()], nullptr, cl.dS, d.uniform ? d.seg_div.m : 0, d.seg_div.shift, d.nS});
+            with_conns.push_back(k);
+            call_begin.push_back(cl.gen_begin);
         }
-        int64_t* d_seg_base = static_cast<int64_t*>(tmp(std::max<size_t>(seg_base.size(), 1) * 8));
-        upload(c, d_seg_base, seg_base.data(), seg_base.size() * 8);
-        for (size_t k = 0; k < calls.size(); ++k) calls[k].seg_base = d_seg_base + seg_at[k];
-        if (calls.empty()) calls.push_back(CallD{0, nullptr, 0, 0, 0, 0, 0, FastDiv{}, nullptr, 0});
-        CallD* d_calls = static_cast<CallD*>(tmp(calls.size() * sizeof(CallD)));
-        upload(c, d_calls, calls.data(), calls.size() * sizeof(CallD));
+        call_begin.push_back(N);
         uint64_t* d_hb = static_cast<uint64_t*>(tmp((P + 1) * 8));
         upload(c, d_hb, host_base.data(), (P + 1) * 8);
-        Lookup L{d_calls, (uint32_t)calls.size(), d_hb, P, PL, G};
 
         // ---------------------------------------------------------- 1-5 image map, keys, sort, first index
         // Default policy: without remote sources the keys hold final sources and
@@ -900,6 +1102,9 @@ void prepare_all(Ctx& c) {
                 bool any_flagged = false;
                 for (auto& cd : calls) any_flagged |= (cd.flag && cd.nS > 0);
                 if (N && remote_net && any_flagged) {
+                    CallD* d_calls = static_cast<CallD*>(tmp(calls.size() * sizeof(CallD)));
+                    upload(c, d_calls, calls.data(), calls.size() * sizeof(CallD));
+                    const Lookup L{d_calls, (uint32_t)calls.size(), d_hb, P, PL, G};
                     tstart(c, "prep_first_use");
                     hipLaunchKernelGGL(k_first_use, dim3(grid_for(N, 8192)), dim3(PNT), 0, c.stream, L, c.g_src, N, fc);
                     tstop(c);
@@ -984,22 +1189,65 @@ void prepare_all(Ctx& c) {
         const uint32_t sbits = bits_for(prefix_span);
         c.key_bits = sbits + tbits;
         if (sbits + tbits > 48) raise(SNNC_EUNSUPPORTED, "source and target ids need more than 48 key bits");
-        const SortPlan plan = plan_sort(c, N, sbits + tbits);   // the sort below takes the same plan
-        const uint32_t passes = plan.passes, dbits = plan.dbits;
-        const bool unpack_in_sort = !remote_net || mapped;
         int32_t* o_src = nullptr;
         uint64_t* row_ptr = nullptr;
-        uint64_t* keys0 = nullptr;
-        uint64_t* keys1 = nullptr;
-        uint32_t* vals1 = nullptr;
         if (N) {
-            keys0 = static_cast<uint64_t*>(tmp(N * 8));
+            // the source maps and, where it exists, the target-major order: one block, one copy
+            std::vector<TInterval> iv;
+            std::vector<TEntry> ent;
+            const bool by_source = target_major(c, with_conns, maps, iv, ent);
+            if (!by_source) {
+                iv.clear();
+                ent.clear();
+            }
+            auto up16 = [](size_t b) { return (b + 15) & ~(size_t)15; };
+            const size_t b_maps = up16(maps.size() * sizeof(SrcMap)), b_call = up16(call_begin.size() * 8);
+            const size_t b_seg = up16(seg_add.size() * 8), b_iv = up16(iv.size() * sizeof(TInterval));
+            const size_t b_ent = up16(ent.size() * sizeof(TEntry));
+            std::vector<char> tab(b_maps + b_call + b_seg + b_iv + b_ent);
+            char* d_tab = static_cast<char*>(tmp(tab.size()));
+            const int64_t* d_seg = reinterpret_cast<const int64_t*>(d_tab + b_maps + b_call);
+            for (size_t k = 0; k < maps.size(); ++k) maps[k].seg_add = d_seg + seg_at[k];
+            memcpy(tab.data(), maps.data(), maps.size() * sizeof(SrcMap));
+            memcpy(tab.data() + b_maps, call_begin.data(), call_begin.size() * 8);
+            memcpy(tab.data() + b_maps + b_call, seg_add.data(), seg_add.size() * 8);
+            if (!iv.empty()) {
+                memcpy(tab.data() + b_maps + b_call + b_seg, iv.data(), iv.size() * sizeof(TInterval));
+                memcpy(tab.data() + b_maps + b_call + b_seg + b_iv, ent.data(), ent.size() * sizeof(TEntry));
+            }
+            upload(c, d_tab, tab.data(), tab.size());
+            GenSource gs{};
+            gs.src = c.g_src;
+            gs.tgt = c.g_tgt;
+            gs.delay = c.g_delay;
+            gs.weight = reinterpret_cast<const uint32_t*>(c.g_weight);
+            gs.maps = reinterpret_cast<const SrcMap*>(d_tab);
+            gs.call_begin = reinterpret_cast<const uint64_t*>(d_tab + b_maps);
+            gs.ncalls = (uint32_t)maps.size();
+            if (by_source) {
+                gs.n_iv = (uint32_t)iv.size();
+                gs.iv = reinterpret_cast<const TInterval*>(d_tab + b_maps + b_call + b_seg);
+                gs.ent = reinterpret_cast<const TEntry*>(d_tab + b_maps + b_call + b_seg + b_iv);
+            }
+            gs.bits = mapped ? bits : nullptr;
+            gs.word_rank = mapped ? word_rank : nullptr;
+            gs.Lmap = Lmap;
+            gs.M_local = M_local;
+            gs.tgt_shift = 16 + tbits;
+            const uint32_t bit_lo = by_source ? 16 + tbits : 16, bit_hi = 16 + sbits + tbits;
+            const SortPlan pl = plan_sort(c, N, bit_hi - bit_lo);   // the sort below takes the same plan
+            uint64_t* keys0 = static_cast<uint64_t*>(tmp(N * 8));
+            uint32_t* weights = reinterpret_cast<uint32_t*>(c.g_weight);
+            uint32_t* moved = by_source ? static_cast<uint32_t*>(tmp(N * 4)) : nullptr;
             uint64_t* hist = static_cast<uint64_t*>(tmp(8 * HIST_STRIDE * 8));
             HIPCHK(hipMemsetAsync(hist, 0, 8 * HIST_STRIDE * 8, c.stream));
             tstart(c, "prep_keys");
-            hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, L, c.g_src, c.g_tgt, c.g_delay,
-                               N, mapped ? bits : (const uint32_t*)nullptr, mapped ? word_rank : (const uint64_t*)nullptr,
-                               Lmap, M_local, 16 + tbits, plan.n9, dbits, passes, keys0, hist);
+            if (by_source)
+                hipLaunchKernelGGL(k_keys_tmajor, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, gs, N, bit_lo, pl.n9,
+                                   pl.dbits, pl.passes, keys0, moved, hist);
+            else
+                hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, gs, N, bit_lo, pl.n9, pl.dbits,
+                                   pl.passes, keys0, hist);
             tstop(c);
             HIPCHK(hipGetLastError());
             // the source ordinals, targets and delays now live in the keys (released in stream order)
@@ -1008,17 +1256,29 @@ void prepare_all(Ctx& c) {
                 dfree(c, c.g_tgt); c.g_tgt = nullptr;
                 dfree(c, c.g_delay); c.g_delay = nullptr;
             }
-            keys1 = static_cast<uint64_t*>(tmp(N * 8));
-            vals1 = static_cast<uint32_t*>(tmp(N * 4));
-            // outputs allocated only now, so they reuse the memory just released
+            uint64_t* keys1 = static_cast<uint64_t*>(tmp(N * 8));
+            uint32_t* vals0 = by_source ? moved : weights;
+            uint32_t* vals1 = by_source ? weights : static_cast<uint32_t*>(tmp(N * 4));
+            // outputs allocated only now, so they reuse the memory just released.  With images still to be
+            // numbered the last pass writes the source prefixes, into the key buffer it does not read,
+            // in place of the sources
             o_src = result<int32_t>(c, SNNC_SRC, N);
-            int32_t* o_tgt = result<int32_t>(c, SNNC_TGT, N);
-            uint16_t* o_delay = result<uint16_t>(c, SNNC_DELAY, N);
-            float* o_weight = result<float>(c, SNNC_WEIGHT, N);
-            FinalOut fo{o_src, o_tgt, o_delay, o_weight, 16 + tbits, tbits ? (1ull << tbits) - 1 : 0};
+            FinalOut fo{o_src, nullptr, result<int32_t>(c, SNNC_TGT, N), result<uint16_t>(c, SNNC_DELAY, N),
+                        result<float>(c, SNNC_WEIGHT, N), 16 + tbits, tbits ? (1ull << tbits) - 1 : 0};
+            const bool unpack_in_sort = !remote_net || mapped;
+            const bool wide_prefix = !unpack_in_sort && sbits > 32;
+            uint64_t* prefix = nullptr;
+            radix_sort(
+                c, keys0, vals0, keys1, vals1, N, bit_lo, bit_hi, hist,
+                [&](int in) {
+                    if (unpack_in_sort) return fo;
+                    prefix = in ? keys0 : keys1;
+                    if (wide_prefix) fo.prefix64 = prefix;
+                    else fo.src = reinterpret_cast<int32_t*>(prefix);
+                    return fo;
+                },
+                N > (1u << 22));   // the wait for the histograms pays where a skipped pass would be long
             if (unpack_in_sort) {
-                radix_sort(c, keys0, reinterpret_cast<uint32_t*>(c.g_weight), keys1, vals1, N, 16, 16 + sbits + tbits,
-                           hist, &fo);
                 const uint64_t n_rows = (uint64_t)M_local + n_img;
                 row_ptr = result<uint64_t>(c, SNNC_ROW_PTR, n_rows + 1);
                 tstart(c, "prep_csr");
@@ -1031,8 +1291,6 @@ void prepare_all(Ctx& c) {
                 tstop(c);
                 HIPCHK(hipGetLastError());
             } else {
-                const int which = radix_sort(c, keys0, reinterpret_cast<uint32_t*>(c.g_weight), keys1, vals1, N, 16,
-                                             16 + sbits + tbits, hist, nullptr);
                 const uint64_t max_img = std::min<uint64_t>(N, n_bits);
                 uint64_t* img_key = static_cast<uint64_t*>(tmp(max_img * 8 + 8));
                 row_ptr = result<uint64_t>(c, SNNC_ROW_PTR, (uint64_t)M_local + max_img + 1);
@@ -1040,34 +1298,34 @@ void prepare_all(Ctx& c) {
                 const NumberShape shape = NUMBER_SHAPES[c.number_variant];
                 const uint64_t xtile = (uint64_t)shape.nt * shape.ipt;
                 const uint64_t tiles = (N + xtile - 1) / xtile;
-                if (c.lookback_bytes < tiles * 8) raise(SNNC_EDEVICE, "look-back table too small");
-                if (++c.sort_epoch > XEPOCH_MAX) {
-                    HIPCHK(hipMemsetAsync(c.lookback, 0, c.lookback_bytes, c.stream));
-                    c.sort_epoch = 1;
-                }
+                ensure_lookback(c, tiles * 8);
+                next_epoch(c);
                 uint32_t* counter = static_cast<uint32_t*>(tmp(4));
                 HIPCHK(hipMemsetAsync(counter, 0, 4, c.stream));
-                const uint32_t* vsorted = which ? vals1 : reinterpret_cast<uint32_t*>(c.g_weight);
                 tstart(c, "prep_number");
-                auto number = [&](auto kern, int nt) {
-                    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(nt), 0, c.stream, which ? keys1 : keys0,
-                                   vsorted, N, 16 + tbits, fo.tgt_mask, M_local, (uint64_t*)c.lookback, counter,
-                                   c.sort_epoch, c.d_status, o_src, o_tgt, o_delay, o_weight, img_key, row_ptr, d_nimg);
+                auto number = [&](auto kern32, auto kern64, int nt) {
+                    if (wide_prefix)
+                        hipLaunchKernelGGL(kern64, dim3((unsigned)tiles), dim3(nt), 0, c.stream,
+                                           (const uint64_t*)prefix, N, M_local, (uint64_t*)c.lookback,
+                                           counter, c.sort_epoch, c.d_status, o_src, img_key, row_ptr, d_nimg);
+                    else
+                        hipLaunchKernelGGL(kern32, dim3((unsigned)tiles), dim3(nt), 0, c.stream,
+                                           reinterpret_cast<const uint32_t*>(prefix), N, M_local, (uint64_t*)c.lookback,
+                                           counter, c.sort_epoch, c.d_status, o_src, img_key, row_ptr, d_nimg);
                 };
-                switch (c.number_variant) {
-                case 0: number(k_number<1024, 12, false>, 1024); break;
-                case 1: number(k_number<512, 12, false>, 512); break;
-                case 2: number(k_number<256, 12, false>, 256); break;
-                case 3: number(k_number<512, 12, true>, 512); break;
-                case 4: number(k_number<256, 12, true>, 256); break;
-                case 5: number(k_number<256, 16, true>, 256); break;
-                case 6: number(k_number<256, 8, true>, 256); break;
-                case 7: number(k_number<256, 6, true>, 256); break;
-                case 8: number(k_number<512, 8, true>, 512); break;
-                case 9: number(k_number<1024, 12, true>, 1024); break;
-                case 10: number(k_number<1024, 10, true>, 1024); break;
-                default: number(k_number<1024, 8, true>, 1024); break;
+#define NUMBER(nt, ipt) number(k_number<nt, ipt, uint32_t>, k_number<nt, ipt, uint64_t>, nt)
+                switch (shape.nt * 100 + shape.ipt) {
+                case 102412: NUMBER(1024, 12); break;
+                case 51212: NUMBER(512, 12); break;
+                case 25612: NUMBER(256, 12); break;
+                case 25616: NUMBER(256, 16); break;
+                case 25608: NUMBER(256, 8); break;
+                case 25606: NUMBER(256, 6); break;
+                case 51208: NUMBER(512, 8); break;
+                case 102410: NUMBER(1024, 10); break;
+                default: NUMBER(1024, 8); break;
                 }
+#undef NUMBER
                 tstop(c);
                 HIPCHK(hipGetLastError());
                 download(c, &n_img, d_nimg, 8);

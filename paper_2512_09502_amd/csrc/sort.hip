@@ -268,7 +268,8 @@ __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ ki
                 dd[k] = (uint32_t)(x >> shift) & mask;
                 const uint64_t g = out_base[dd[k]] + s;
                 if constexpr (FINAL) {
-                    fo.src[g] = (int32_t)(x >> fo.tgt_shift);
+                    if (fo.prefix64) fo.prefix64[g] = x >> fo.tgt_shift;
+                else fo.src[g] = (int32_t)(x >> fo.tgt_shift);
                     fo.tgt[g] = (int32_t)((x >> 16) & fo.tgt_mask);
                     fo.delay[g] = (uint16_t)(x & 0xffffu);
                 } else {
@@ -305,7 +306,8 @@ __global__ void k_unpack(const uint64_t* keys, const uint32_t* vals, uint64_t n,
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const uint64_t k = keys[i];
-    fo.src[i] = (int32_t)(k >> fo.tgt_shift);
+    if (fo.prefix64) fo.prefix64[i] = k >> fo.tgt_shift;
+    else fo.src[i] = (int32_t)(k >> fo.tgt_shift);
     fo.tgt[i] = (int32_t)((k >> 16) & fo.tgt_mask);
     fo.delay[i] = (uint16_t)(k & 0xffffu);
     fo.weight[i] = __uint_as_float(vals[i]);
@@ -350,6 +352,13 @@ __global__ __launch_bounds__(NT) void k_tile_counts(const uint64_t* __restrict__
     for (uint32_t d = threadIdx.x; d < RB; d += NT) counts[(uint64_t)d * tiles + blockIdx.x] = h[d];
 }
 
+template <int NT, int IPT, bool FINAL, bool LB, int RB, bool SPLIT>
+void launch_onesweep(Ctx& c, const PassArgs& a, const uint64_t* off) {
+    const uint64_t tiles = (a.n + (uint64_t)NT * IPT - 1) / ((uint64_t)NT * IPT);
+    hipLaunchKernelGGL((k_onesweep<NT, IPT, FINAL, LB, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
+                       a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.spin_limit, a.fo);
+}
+
 template <int NT, int IPT, int RB, bool SPLIT = false>
 void launch_pass(Ctx& c, const PassArgs& a, bool final) {
     constexpr int TILE = NT * IPT;
@@ -362,27 +371,17 @@ void launch_pass(Ctx& c, const PassArgs& a, bool final) {
         temps.push_back(counts);
         uint64_t* scanned = dalloc_n<uint64_t>(c, tiles * RB + 1);
         temps.push_back(scanned);
-        hipLaunchKernelGGL((k_tile_counts<NT, IPT, RB>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin, a.n,
-                           a.shift, a.dbits, counts);
+        hipLaunchKernelGGL((k_tile_counts<NT, IPT, RB>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
+                           a.n, a.shift, a.dbits, counts);
         HIPCHK(hipGetLastError());
         scan_u32_u64(c, counts, scanned, tiles * RB, false);
         off = scanned;
-        if (final)
-            hipLaunchKernelGGL((k_onesweep<NT, IPT, true, false, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream,
-                               a.kin, a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch,
-                               a.spin_limit, a.fo);
-        else
-            hipLaunchKernelGGL((k_onesweep<NT, IPT, false, false, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream,
-                               a.kin, a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch,
-                               a.spin_limit, a.fo);
+        if (final) launch_onesweep<NT, IPT, true, false, RB, SPLIT>(c, a, off);
+        else launch_onesweep<NT, IPT, false, false, RB, SPLIT>(c, a, off);
     } else if (final) {
-        hipLaunchKernelGGL((k_onesweep<NT, IPT, true, true, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
-                           a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.spin_limit,
-                           a.fo);
+        launch_onesweep<NT, IPT, true, true, RB, SPLIT>(c, a, off);
     } else {
-        hipLaunchKernelGGL((k_onesweep<NT, IPT, false, true, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
-                           a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.spin_limit,
-                           a.fo);
+        launch_onesweep<NT, IPT, false, true, RB, SPLIT>(c, a, off);
     }
     HIPCHK(hipGetLastError());
     for (void* p : temps) dfree(c, p);   // stream-ordered release
@@ -457,6 +456,25 @@ void launch_variant(Ctx& c, int v, const PassArgs& a, bool final, bool wide) {
 }
 
 }  // namespace
+
+// look-back table of the lane: tiles x buckets status words, zeroed once when (re)allocated
+void ensure_lookback(Ctx& c, size_t need) {
+    if (c.lookback_bytes >= need) return;
+    dfree(c, c.lookback);
+    c.lookback = nullptr;
+    c.lookback_bytes = 0;
+    c.lookback = dalloc(c, need);
+    c.lookback_bytes = need;
+    HIPCHK(hipMemsetAsync(c.lookback, 0, need, c.stream));
+    c.sort_epoch = 0;
+}
+
+void next_epoch(Ctx& c) {
+    if (++c.sort_epoch > EPOCH_MAX) {
+        HIPCHK(hipMemsetAsync(c.lookback, 0, c.lookback_bytes, c.stream));
+        c.sort_epoch = 1;
+    }
+}
 
 int sort_variant_count() { return N_VARIANTS; }
 
@@ -534,6 +552,19 @@ void fill_words(Ctx& c, uint64_t* p, uint64_t n) {
     HIPCHK(hipGetLastError());
 }
 
+// passes whose digit differs between keys (the others leave the order unchanged);
+// hh: their digit histograms, or null when they were not read back
+uint32_t live_passes(const uint64_t* hh, uint32_t passes, uint64_t n, uint32_t* live) {
+    uint32_t n_live = 0;
+    for (uint32_t p = 0; p < passes; ++p) {
+        bool trivial = false;
+        for (int b = 0; hh && b < HSTRIDE; ++b)
+            if (hh[(size_t)p * HSTRIDE + b] == n) trivial = true;
+        if (!trivial) live[n_live++] = p;
+    }
+    return n_live;
+}
+
 // Scratch of a sort that allocates nothing: digit histograms and offsets and
 // the look-back table, all at fixed addresses; the look-back epoch persists
 // with the table.
@@ -546,7 +577,7 @@ struct FixedScratch {
 };
 
 int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, uint32_t* vals1, uint64_t n,
-                    uint32_t bit_lo, uint32_t bit_hi, const uint64_t* digit_hist, const FinalOut* final_out,
+                    uint32_t bit_lo, uint32_t bit_hi, const uint64_t* digit_hist, const FinalOutFn& final_out,
                     bool wait_for_plan, const FixedScratch* fs) {
     const SortPlan plan = plan_sort(c, n, bit_hi > bit_lo ? bit_hi - bit_lo : 0);
     const uint32_t passes = plan.passes, dbits = plan.dbits;
@@ -570,7 +601,6 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
     int cur = 0;
     try {
         uint64_t hh[8 * HSTRIDE];
-        memset(hh, 0, sizeof hh);
         uint64_t* off = nullptr;
         if (passes && n) {
             uint64_t* hist = const_cast<uint64_t*>(digit_hist);
@@ -597,43 +627,29 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
             tstop(c);
             HIPCHK(hipGetLastError());
             if (wait_for_plan) download(c, hh, hist, (size_t)passes * HSTRIDE * 8);
-            // look-back table: tiles x buckets status words, zeroed once when (re)allocated
-            const size_t need = (size_t)tiles * rb * 8;
-            if (!fs && c.lookback_bytes < need) {
-                dfree(c, c.lookback);
-                c.lookback = nullptr;
-                c.lookback_bytes = 0;
-                c.lookback = dalloc(c, need);
-                c.lookback_bytes = need;
-                HIPCHK(hipMemsetAsync(c.lookback, 0, need, c.stream));
-                c.sort_epoch = 0;
+            if (!fs) {
+                ensure_lookback(c, (size_t)tiles * rb * 8);
                 lookback = c.lookback;
             }
         }
-        // passes whose digit is the same for every key leave the order unchanged
         uint32_t live[8];
-        uint32_t n_live = 0;
-        for (uint32_t p = 0; p < passes; ++p) {
-            bool trivial = false;
-            for (int b = 0; b < HSTRIDE; ++b)
-                if (hh[(size_t)p * HSTRIDE + b] == n) trivial = true;
-            if (!trivial) live[n_live++] = p;
-        }
+        const uint32_t n_live = live_passes(wait_for_plan && passes && n ? hh : nullptr, passes, n, live);
         c.sort_passes = n_live;
         uint64_t* kb[2] = {keys0, keys1};
         uint32_t* vb[2] = {vals0, vals1};
         for (uint32_t li = 0; li < n_live; ++li) {
             const uint32_t p = live[li];
-            if (++epoch > EPOCH_MAX) {
-                if (fs) fill_words(c, static_cast<uint64_t*>(lookback), lookback_bytes / 8);
-                else HIPCHK(hipMemsetAsync(c.lookback, 0, c.lookback_bytes, c.stream));
+            if (!fs) {
+                next_epoch(c);
+            } else if (++epoch > EPOCH_MAX) {
+                fill_words(c, static_cast<uint64_t*>(lookback), lookback_bytes / 8);
                 epoch = 1;
             }
             const bool last = (li + 1 == n_live) && final_out;
             const uint32_t width = pass_bits(bit_lo, bit_hi, plan.n9, dbits, p);
             PassArgs a{kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], n, pass_shift(bit_lo, plan.n9, dbits, p), width,
                        off + (size_t)p * HSTRIDE, (uint64_t*)lookback, epoch, c.lookback_spins,
-                       final_out ? *final_out : FinalOut{}, mode};
+                       last ? final_out(cur) : FinalOut{}, mode};
             tstart(c, sort_timer(c, last ? "pass_final" : "pass").c_str());
             launch_variant(c, variant, a, last, width > 8);
             tstop(c);
@@ -643,7 +659,7 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
         if (final_out && !n_live && n) {
             tstart(c, sort_timer(c, "unpack").c_str());
             hipLaunchKernelGGL(k_unpack, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c.stream, kb[cur], vb[cur], n,
-                               *final_out);
+                               final_out(cur));
             tstop(c);
             HIPCHK(hipGetLastError());
         }
@@ -658,7 +674,7 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
 }  // namespace
 
 int radix_sort(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, uint32_t* vals1, uint64_t n,
-               uint32_t bit_lo, uint32_t bit_hi, const uint64_t* digit_hist, const FinalOut* final_out,
+               uint32_t bit_lo, uint32_t bit_hi, const uint64_t* digit_hist, const FinalOutFn& final_out,
                bool wait_for_plan) {
     return radix_sort_impl(c, keys0, vals0, keys1, vals1, n, bit_lo, bit_hi, digit_hist, final_out, wait_for_plan,
                            nullptr);
