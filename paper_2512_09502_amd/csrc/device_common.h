@@ -13,6 +13,11 @@ namespace snnc {
 
 enum : uint32_t { PURPOSE_IDX = 0, PURPOSE_SYN = 1, PURPOSE_BERN = 2 };
 
+// a ^ b ^ c in one operation
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 32x32->64 products of counter words 0 and 2 with the round multipliers,
 // the high halves xor-ed with the other counter words and the key; the key
@@ -26,7 +31,7 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1) {
         }
         const uint64_t a = (uint64_t)0xD2511F53u * c.x;
         const uint64_t b = (uint64_t)0xCD9E8D57u * c.z;
-        c = make_uint4((uint32_t)(b >> 32) ^ c.y ^ k0, (uint32_t)b, (uint32_t)(a >> 32) ^ c.w ^ k1, (uint32_t)a);
+        c = make_uint4(xor3((uint32_t)(b >> 32), c.y, k0), (uint32_t)b, xor3((uint32_t)(a >> 32), c.w, k1), (uint32_t)a);
     }
     return c;
 }
@@ -43,17 +48,27 @@ __device__ __forceinline__ uint32_t uniform_index(uint32_t lo, uint32_t hi, uint
     return (uint32_t)(p_hi >> 32);
 }
 
-// fp32 weight N(mean, sd): Box-Muller, cosine branch, in double precision,
+// fp32 weights N(mean, sd): Box-Muller, cosine branch, in double precision,
 // u1 = (w0 + 1) / 2^32, u2 = w1 / 2^32, one rounding to fp32.  ln u1 and
 // cos(2pi_d u2) come from the argument-exact helpers of bm_math.h (within two
 // double ulp of the library functions).  Contraction is off so that the
 // final product and sum round as written.
-__device__ __forceinline__ float normal_weight(uint32_t w0, uint32_t w1, double mean, double sd) {
+template <int N>
+__device__ __forceinline__ void normal_weights(const uint32_t (&w0)[N], const uint32_t (&w1)[N], double mean, double sd,
+                                               float (&out)[N]) {
 #pragma clang fp contract(off)
-    const double radius = sqrt(-2.0 * log_u32_frac((uint64_t)w0 + 1));
-    const double z = radius * cos_2pi_u32(w1);
-    const double scaled = sd * z;
-    return (float)(mean + scaled);
+    uint64_t v[N];
+    double x[N], radius[N], c[N];
+    SNNC_UNROLL for (int i = 0; i < N; ++i) v[i] = (uint64_t)w0[i] + 1;
+    log_u32_fracs<N>(v, x);
+    SNNC_UNROLL for (int i = 0; i < N; ++i) x[i] = -2.0 * x[i];
+    square_roots<N>(x, radius);
+    cos_2pi_u32s<N>(w1, c);
+    SNNC_UNROLL for (int i = 0; i < N; ++i) {
+        const double z = radius[i] * c[i];
+        const double scaled = sd * z;
+        out[i] = (float)(mean + scaled);
+    }
 }
 
 // Delay step from the threshold table: k_lo + #{k : w >= t_k}.  The guide
@@ -69,16 +84,36 @@ __device__ __forceinline__ uint16_t delay_step(const uint32_t* tab, const uint32
     return (uint16_t)(klo + a);
 }
 
-__device__ __forceinline__ void syn_values(const SynD& s, uint32_t seed, uint32_t call, uint64_t e,
-                                           float& w, uint16_t& d) {
-    if (s.w_normal | s.d_normal) {
-        const uint4 b = draw(seed, call, e, PURPOSE_SYN);
-        w = s.w_normal ? normal_weight(b.x, b.y, s.w_mean, s.w_sd) : s.w_const;
-        d = s.d_normal ? delay_step(s.dtab, s.dguide, s.d_klo, b.z) : (uint16_t)s.d_const;
-    } else {
-        w = s.w_const;
-        d = (uint16_t)s.d_const;
+// Weights and delays of N elements (in lockstep, see bm_math.h).
+template <int N>
+__device__ __forceinline__ void syn_values(const SynD& s, uint32_t seed, uint32_t call, const uint64_t (&e)[N],
+                                           float (&w)[N], uint16_t (&d)[N]) {
+    SNNC_UNROLL for (int i = 0; i < N; ++i) {
+        w[i] = s.w_const;
+        d[i] = (uint16_t)s.d_const;
     }
+    if (s.w_normal | s.d_normal) {
+        uint32_t b0[N], b1[N], b2[N];
+        SNNC_UNROLL for (int i = 0; i < N; ++i) {
+            const uint4 b = draw(seed, call, e[i], PURPOSE_SYN);
+            b0[i] = b.x;
+            b1[i] = b.y;
+            b2[i] = b.z;
+        }
+        if (s.w_normal) normal_weights<N>(b0, b1, s.w_mean, s.w_sd, w);
+        if (s.d_normal)
+            SNNC_UNROLL for (int i = 0; i < N; ++i) d[i] = delay_step(s.dtab, s.dguide, s.d_klo, b2[i]);
+    }
+}
+
+__device__ __forceinline__ void syn_values(const SynD& s, uint32_t seed, uint32_t call, uint64_t e, float& w,
+                                           uint16_t& d) {
+    const uint64_t ea[1] = {e};
+    float wa[1];
+    uint16_t da[1];
+    syn_values<1>(s, seed, call, ea, wa, da);
+    w = wa[0];
+    d = da[0];
 }
 
 // Ordinal -> (host, local id) in a node set (segments sorted by ordinal).

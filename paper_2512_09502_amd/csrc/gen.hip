@@ -47,6 +47,25 @@ struct WriteSink {
         delay[i] = d;
         weight[i] = w;
     }
+    // results r[k] at positions pos[k] for the k with ok[k]
+    template <int N>
+    __device__ __forceinline__ void put_all(const uint64_t (&pos)[N], const Res (&r)[N], const bool (&ok)[N]) const {
+        uint64_t e[N];
+        float w[N];
+        uint16_t d[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) e[k] = r[k].e;
+        syn_values<N>(syn, seed, call, e, w, d);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if (!ok[k]) continue;
+            const uint64_t i = base + pos[k];
+            src[i] = r[k].src;
+            tgt[i] = r[k].tgt;
+            delay[i] = d[k];
+            weight[i] = w[k];
+        }
+    }
     __device__ __forceinline__ void mark(const Res&) const {}
 };
 
@@ -107,13 +126,30 @@ struct ChunkTab {
         if (n <= CH_INLINE) {
             TChunk c = in[0];
 #pragma unroll
-            for (uint32_t k = 1; k < CH_INLINE; ++k)
-                if (k < n && in[k].out_begin <= g) c = in[k];
+            for (uint32_t k = 1; k < CH_INLINE; ++k) {   // field by field: selects, no copy in memory
+                const bool here = k < n && in[k].out_begin <= g;
+                c.t_ord = here ? in[k].t_ord : c.t_ord;
+                c.out_begin = here ? in[k].out_begin : c.out_begin;
+                c.self_base = here ? in[k].self_base : c.self_base;
+                c.local_first = here ? in[k].local_first : c.local_first;
+                c.n = here ? in[k].n : c.n;
+            }
             return c;
         }
         return d[find_chunk(d, n, g)];
     }
 };
+
+// A run and the end of its items (per_unit items a unit).
+struct Run {
+    TChunk c;
+    uint64_t end;
+};
+
+__device__ __forceinline__ Run run_at(const ChunkTab& t, uint64_t g, uint64_t per_unit) {
+    const TChunk c = t.at(g);
+    return Run{c, c.out_begin + (uint64_t)c.n * per_unit};
+}
 
 // ------------------------------------------------------------------ rules
 // Fixed in-degree with multapses: element e = t_ord K + j draws its source
@@ -126,13 +162,11 @@ struct InDegree {
     FastDiv fk;
     uint32_t n_s;
     uint32_t seed, call;
-    __device__ __forceinline__ int eval(uint64_t g, Res* r) const {
-        const TChunk c = ch.at(g);
+    __device__ __forceinline__ Run run(uint64_t g) const { return run_at(ch, g, K); }
+    __device__ __forceinline__ int eval_in(const TChunk& c, uint64_t g, Res* r) const {
         const uint32_t rel = (uint32_t)(g - c.out_begin);
         const uint32_t t_rel = fastdiv(rel, fk);
-        const uint32_t j = rel - t_rel * K;
-        const uint64_t t_ord = c.t_ord + t_rel;
-        const uint64_t e = t_ord * K + j;
+        const uint64_t e = c.t_ord * K + rel;            // = t_ord K + j
         const bool skip = c.self_base >= 0;
         const uint4 b = draw(seed, call, e, PURPOSE_IDX);
         uint32_t s = uniform_index(b.x, b.y, n_s - (skip ? 1u : 0u));
@@ -140,6 +174,7 @@ struct InDegree {
         r[0] = Res{s, c.local_first + t_rel, e};
         return 1;
     }
+    __device__ __forceinline__ int eval(uint64_t g, Res* r) const { return eval_in(ch.at(g), g, r); }
 };
 
 // Fixed out-degree with multapses: element e = s_ord K + j draws a target
@@ -154,13 +189,12 @@ struct OutDegree {
     uint32_t nT;
     uint32_t host;
     uint32_t seed, call;
-    __device__ __forceinline__ int eval(uint64_t g, Res* r) const {
-        const TChunk c = ch.at(g);
+    __device__ __forceinline__ Run run(uint64_t g) const { return run_at(ch, g, K); }
+    __device__ __forceinline__ int eval_in(const TChunk& c, uint64_t g, Res* r) const {
         const uint32_t rel = (uint32_t)(g - c.out_begin);
         const uint32_t s_rel = fastdiv(rel, fk);
-        const uint32_t j = rel - s_rel * K;
         const uint64_t s_ord = c.t_ord + s_rel;
-        const uint64_t e = s_ord * K + j;
+        const uint64_t e = c.t_ord * K + rel;            // = s_ord K + j
         const bool skip = c.self_base >= 0;
         const uint4 b = draw(seed, call, e, PURPOSE_IDX);
         uint32_t t = uniform_index(b.x, b.y, n_t - (skip ? 1u : 0u));
@@ -171,6 +205,7 @@ struct OutDegree {
         r[0] = Res{(uint32_t)s_ord, l, e};
         return 1;
     }
+    __device__ __forceinline__ int eval(uint64_t g, Res* r) const { return eval_in(ch.at(g), g, r); }
 };
 
 // Fixed total number: candidate c draws (source, target) ordinals from the
@@ -186,6 +221,8 @@ struct Total {
     uint32_t autapses;
     const uint8_t* first;   // null when multapses are allowed
     uint32_t seed, call;
+    __device__ __forceinline__ Run run(uint64_t) const { return Run{TChunk{}, ~0ull}; }
+    __device__ __forceinline__ int eval_in(const TChunk&, uint64_t cand, Res* r) const { return eval(cand, r); }
     __device__ __forceinline__ int eval(uint64_t cand, Res* r, uint32_t* th_out = nullptr) const {
         const uint4 b = draw(seed, call, cand, PURPOSE_IDX);
         const uint32_t s = uniform_index(b.x, b.y, n_s);
@@ -213,6 +250,8 @@ struct Assigned {
     const SegD* T;
     uint32_t nT;
     uint32_t host;
+    __device__ __forceinline__ Run run(uint64_t) const { return Run{TChunk{}, ~0ull}; }
+    __device__ __forceinline__ int eval_in(const TChunk&, uint64_t i, Res* r) const { return eval(i, r); }
     __device__ __forceinline__ int eval(uint64_t i, Res* r) const {
         uint32_t h, l;
         set_lookup(T, nT, tgt_pos[i], h, l);
@@ -419,15 +458,40 @@ struct OneToOne {
     static constexpr int R = 1;
     ChunkTab ch;
     uint32_t autapses;
-    __device__ __forceinline__ int eval(uint64_t g, Res* r) const {
-        const TChunk c = ch.at(g);
+    __device__ __forceinline__ Run run(uint64_t g) const { return run_at(ch, g, 1); }
+    __device__ __forceinline__ int eval_in(const TChunk& c, uint64_t g, Res* r) const {
         const uint32_t rel = (uint32_t)(g - c.out_begin);
         const uint64_t i = c.t_ord + rel;
         if (!autapses && c.self_base >= 0 && (uint64_t)c.self_base + rel == i) return 0;
         r[0] = Res{(uint32_t)i, c.local_first + rel, i};
         return 1;
     }
+    __device__ __forceinline__ int eval(uint64_t g, Res* r) const { return eval_in(ch.at(g), g, r); }
 };
+
+// Items [first, end) of a tile written at their own index.  A thread takes its
+// IPT items together: their draws are independent, and the coefficients of the
+// Box-Muller polynomials are loaded once for all of them.  The runs that the
+// tile meets (nearly always one) are taken one after another, each the same in
+// every lane, so that its parameters stay in scalar registers.
+template <class Rule, class Sink>
+__device__ __forceinline__ void direct_tile(const Rule& rule, const Sink& sink, uint64_t first, uint64_t end) {
+    for (uint64_t g = first; g < end;) {
+        const Run run = rule.run(g);
+        const uint64_t stop = run.end < end ? run.end : end;
+        uint64_t pos[IPT];
+        Res r[IPT];
+        bool ok[IPT];
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            pos[k] = first + (uint64_t)k * NT + threadIdx.x;
+            r[k] = Res{};
+            ok[k] = pos[k] >= g && pos[k] < stop && rule.eval_in(run.c, pos[k], &r[k]) != 0;
+        }
+        sink.put_all(pos, r, ok);
+        g = stop;
+    }
+}
 
 // ------------------------------------------------------------------ generic kernel
 template <class Rule, class Sink, int MODE>
@@ -436,6 +500,10 @@ __global__ __launch_bounds__(NT) void k_gen(Rule rule, Sink sink, uint64_t n_ite
     __shared__ uint32_t scratch[NT / 64];
     const uint64_t tile = tile0 + blockIdx.x;
     const uint64_t base = tile * TILE;
+    if constexpr (MODE == DIRECT) {
+        direct_tile(rule, sink, base, min(base + TILE, n_items));
+        return;
+    }
     uint64_t running = 0;
     if constexpr (MODE == WRITE) running = tile_offsets[tile];
     uint32_t counted = 0;
@@ -445,9 +513,7 @@ __global__ __launch_bounds__(NT) void k_gen(Rule rule, Sink sink, uint64_t n_ite
         Res r[Rule::R];
         int n = 0;
         if (item < n_items) n = rule.eval(item, r);
-        if constexpr (MODE == DIRECT) {
-            if (n) sink.put(item, r[0]);
-        } else if constexpr (MODE == MARK) {
+        if constexpr (MODE == MARK) {
             for (int k = 0; k < n; ++k) sink.mark(r[k]);
         } else if constexpr (MODE == COUNT) {
             counted += (uint32_t)n;
@@ -684,19 +750,25 @@ uint64_t count_and_write(Ctx& c, const char* name, const Rule& rule, Provider pr
 // Synapse values of a call written unit by unit (K elements per unit, in the
 // order of the unit runs): position p of the call holds element (t_ord + rel)
 // K + j of its run, rel = unit within the run, j = rank within the unit.
-__global__ __launch_bounds__(NT) void k_syn_fill(ChunkTab ch, uint32_t K, FastDiv fK,
-                                                 uint64_t items, SynD syn, uint32_t seed, uint32_t call,
+__global__ __launch_bounds__(NT) void k_syn_fill(ChunkTab ch, uint32_t K, uint64_t items, SynD syn, uint32_t seed, uint32_t call,
                                                  uint16_t* delay, float* weight, uint64_t base) {
-    for (uint64_t p = (uint64_t)blockIdx.x * NT + threadIdx.x; p < items; p += (uint64_t)gridDim.x * NT) {
-        const TChunk c = ch.at(p);
-        const uint64_t off = p - c.out_begin;
-        const uint32_t rel = fastdiv((uint32_t)off, fK);   // a run holds fewer than 2^32 elements
-        const uint32_t j = (uint32_t)off - rel * K;
-        float w;
-        uint16_t d;
-        syn_values(syn, seed, call, (c.t_ord + rel) * (uint64_t)K + j, w, d);
-        delay[base + p] = d;
-        weight[base + p] = w;
+    for (uint64_t first = (uint64_t)blockIdx.x * TILE; first < items; first += (uint64_t)gridDim.x * TILE) {
+        uint64_t p[IPT], e[IPT];
+        float w[IPT];
+        uint16_t d[IPT];
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            p[k] = first + (uint64_t)k * NT + threadIdx.x;
+            const TChunk c = ch.at(p[k] < items ? p[k] : first);
+            e[k] = c.t_ord * (uint64_t)K + (p[k] - c.out_begin);   // (t_ord + rel) K + j
+        }
+        syn_values<IPT>(syn, seed, call, e, w, d);
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            if (p[k] >= items) continue;
+            delay[base + p[k]] = d[k];
+            weight[base + p[k]] = w[k];
+        }
     }
 }
 
@@ -1098,9 +1170,9 @@ void launch_floyd_direct(Ctx& c, const FloydArgs& a, const WriteSink& ws, uint64
     if (!(a.K <= FLOYD_SMALL && defer_floyd_small(c, a, ws))) launch_floyd<IdSink, DIRECT>(c, a, ids, nullptr, nullptr);
     if (!items) return;
     if (defer_syn_fill(c, a, ws, items)) return;   // the batch's fused launch writes them
-    const uint32_t grid = (uint32_t)std::min<uint64_t>((items + NT - 1) / NT, 1u << 20);
+    const uint32_t grid = (uint32_t)std::min<uint64_t>((items + TILE - 1) / TILE, 1u << 20);
     tstart(c, "gen_floyd");
-    hipLaunchKernelGGL(k_syn_fill, dim3(grid), dim3(NT), 0, c.stream, a.ch, a.K, make_fastdiv(a.K), items,
+    hipLaunchKernelGGL(k_syn_fill, dim3(grid), dim3(NT), 0, c.stream, a.ch, a.K, items,
                        ws.syn, ws.seed, ws.call, ws.delay, ws.weight, ws.base);
     tstop(c);
     HIPCHK(hipGetLastError());
