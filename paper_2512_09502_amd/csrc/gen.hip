@@ -60,8 +60,10 @@ struct WriteSink {
         for (int k = 0; k < N; ++k) {
             if (!ok[k]) continue;
             const uint64_t i = base + pos[k];
-            src[i] = r[k].src;
-            tgt[i] = r[k].tgt;
+            if (src) {   // null: the sources and targets are written elsewhere
+                src[i] = r[k].src;
+                tgt[i] = r[k].tgt;
+            }
             delay[i] = d[k];
             weight[i] = w[k];
         }
@@ -101,6 +103,11 @@ struct MarkSink {
         if (!(bits[l >> 5] & m)) atomicOr(bits + (l >> 5), m);
     }
     __device__ __forceinline__ void put(uint64_t, const Res& r) const { mark(r); }
+    template <int N>
+    __device__ __forceinline__ void put_all(const uint64_t (&)[N], const Res (&r)[N], const bool (&ok)[N]) const {
+        for (int k = 0; k < N; ++k)
+            if (ok[k]) mark(r[k]);
+    }
 };
 
 __device__ __forceinline__ uint32_t find_chunk(const TChunk* ch, uint32_t nch, uint64_t g) {
@@ -389,7 +396,24 @@ __global__ __launch_bounds__(NT) void k_bern(BernPair r, Sink sink, uint64_t n_i
             hits[pre++] = (uint16_t)(threadIdx.x * IPT * 4 + b);
         }
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < tot; i += NT) {
+        uint32_t i0 = 0;
+        for (; i0 + 3 * NT < tot; i0 += 4 * NT) {   // four a thread while most of them exist
+            uint64_t pos[4];
+            Res rr[4];
+            bool ok[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t i = i0 + (uint32_t)k * NT + threadIdx.x;
+                ok[k] = i < tot;
+                const uint32_t h = hits[ok[k] ? i : 0];
+                BernItem it{};
+                (void)bern_item(r, base + (h >> 2), it);
+                pos[k] = running + i;
+                rr[k] = bern_res(it, h & 3u);
+            }
+            sink.put_all(pos, rr, ok);
+        }
+        for (uint32_t i = i0 + threadIdx.x; i < tot; i += NT) {
             const uint32_t h = hits[i];
             BernItem it{};
             (void)bern_item(r, base + (h >> 2), it);
@@ -469,29 +493,53 @@ struct OneToOne {
     __device__ __forceinline__ int eval(uint64_t g, Res* r) const { return eval_in(ch.at(g), g, r); }
 };
 
-// Items [first, end) of a tile written at their own index.  A thread takes its
+// The thread's IPT items of the tile that starts at item `first`, as far as they
+// lie in [g, end) and in the run that holds g; returns where that run or the
+// range ends.  pos: the item's index within the call (whose items start at
+// `origin`).  The run is the same in every lane, so that its parameters stay in
+// scalar registers; a tile nearly always meets one.
+template <class Rule>
+__device__ __forceinline__ uint64_t eval_tile(const Rule& rule, uint64_t first, uint64_t g, uint64_t end, uint64_t origin,
+                                              uint64_t (&pos)[IPT], Res (&r)[IPT], bool (&ok)[IPT]) {
+    const Run run = rule.run(g - origin);
+    const uint64_t stop = run.end < end - origin ? run.end + origin : end;
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+        const uint64_t item = first + (uint64_t)k * NT + threadIdx.x;
+        pos[k] = item - origin;
+        r[k] = Res{};
+        ok[k] = item >= g && item < stop && rule.eval_in(run.c, pos[k], &r[k]) != 0;
+    }
+    return stop;
+}
+
+// Items [first, end) of a tile, each written at its index.  A thread takes its
 // IPT items together: their draws are independent, and the coefficients of the
-// Box-Muller polynomials are loaded once for all of them.  The runs that the
-// tile meets (nearly always one) are taken one after another, each the same in
-// every lane, so that its parameters stay in scalar registers.
+// Box-Muller polynomials are loaded once for all of them.
 template <class Rule, class Sink>
 __device__ __forceinline__ void direct_tile(const Rule& rule, const Sink& sink, uint64_t first, uint64_t end) {
     for (uint64_t g = first; g < end;) {
-        const Run run = rule.run(g);
-        const uint64_t stop = run.end < end ? run.end : end;
         uint64_t pos[IPT];
         Res r[IPT];
         bool ok[IPT];
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            pos[k] = first + (uint64_t)k * NT + threadIdx.x;
-            r[k] = Res{};
-            ok[k] = pos[k] >= g && pos[k] < stop && rule.eval_in(run.c, pos[k], &r[k]) != 0;
-        }
+        g = eval_tile(rule, first, g, end, 0, pos, r, ok);
         sink.put_all(pos, r, ok);
-        g = stop;
     }
 }
+
+// Elements written unit by unit (K elements per unit, in the order of the unit
+// runs), as a rule of which only the element index counts: position p holds
+// element (t_ord + rel) K + j of its run, rel = unit within the run, j = rank
+// within the unit.
+struct UnitElems {
+    const ChunkTab& ch;
+    uint32_t K;
+    __device__ __forceinline__ Run run(uint64_t g) const { return run_at(ch, g, K); }
+    __device__ __forceinline__ int eval_in(const TChunk& c, uint64_t g, Res* r) const {
+        r[0] = Res{0, 0, c.t_ord * (uint64_t)K + (g - c.out_begin)};
+        return 1;
+    }
+};
 
 // ------------------------------------------------------------------ generic kernel
 template <class Rule, class Sink, int MODE>
@@ -639,12 +687,16 @@ __global__ __launch_bounds__(NT) void k_total_dist(Total rule, uint32_t host, Si
         }
         uint32_t tot;
         uint64_t rank = vrun + block_excl_scan<NT>(nv, scratch, &tot);
+        uint64_t pos[IPT];
+        bool ok[IPT];
 #pragma unroll
         for (int k = 0; k < IPT; ++k) {
-            if (!((vmask >> k) & 1u)) continue;
-            if (rank < limit) sink.put(rank, rr[k]);
-            ++rank;
+            const bool v = (vmask >> k) & 1u;
+            pos[k] = rank;
+            ok[k] = v && rank < limit;
+            rank += v ? 1u : 0u;
         }
+        sink.put_all(pos, rr, ok);
         return;
     }
     if constexpr (MODE == CNT_VALID) {
@@ -747,29 +799,10 @@ uint64_t count_and_write(Ctx& c, const char* name, const Rule& rule, Provider pr
     return std::min(total, limit);
 }
 
-// Synapse values of a call written unit by unit (K elements per unit, in the
-// order of the unit runs): position p of the call holds element (t_ord + rel)
-// K + j of its run, rel = unit within the run, j = rank within the unit.
-__global__ __launch_bounds__(NT) void k_syn_fill(ChunkTab ch, uint32_t K, uint64_t items, SynD syn, uint32_t seed, uint32_t call,
-                                                 uint16_t* delay, float* weight, uint64_t base) {
-    for (uint64_t first = (uint64_t)blockIdx.x * TILE; first < items; first += (uint64_t)gridDim.x * TILE) {
-        uint64_t p[IPT], e[IPT];
-        float w[IPT];
-        uint16_t d[IPT];
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            p[k] = first + (uint64_t)k * NT + threadIdx.x;
-            const TChunk c = ch.at(p[k] < items ? p[k] : first);
-            e[k] = c.t_ord * (uint64_t)K + (p[k] - c.out_begin);   // (t_ord + rel) K + j
-        }
-        syn_values<IPT>(syn, seed, call, e, w, d);
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            if (p[k] >= items) continue;
-            delay[base + p[k]] = d[k];
-            weight[base + p[k]] = w[k];
-        }
-    }
+__global__ __launch_bounds__(NT) void k_syn_fill(ChunkTab ch, uint32_t K, uint64_t items, WriteSink sink) {
+    const UnitElems rule{ch, K};
+    for (uint64_t first = (uint64_t)blockIdx.x * TILE; first < items; first += (uint64_t)gridDim.x * TILE)
+        direct_tile(rule, sink, first, min(first + TILE, items));
 }
 
 // ------------------------------------------------------------------ Floyd's sampling
@@ -1173,7 +1206,7 @@ void launch_floyd_direct(Ctx& c, const FloydArgs& a, const WriteSink& ws, uint64
     const uint32_t grid = (uint32_t)std::min<uint64_t>((items + TILE - 1) / TILE, 1u << 20);
     tstart(c, "gen_floyd");
     hipLaunchKernelGGL(k_syn_fill, dim3(grid), dim3(NT), 0, c.stream, a.ch, a.K, items,
-                       ws.syn, ws.seed, ws.call, ws.delay, ws.weight, ws.base);
+                       WriteSink{nullptr, nullptr, ws.delay, ws.weight, ws.base, ws.syn, ws.seed, ws.call});
     tstop(c);
     HIPCHK(hipGetLastError());
 }
@@ -2051,39 +2084,36 @@ __device__ __forceinline__ uint32_t find_req(const FusedReq* reqs, uint32_t lo, 
     return lo;
 }
 
-// one item of the fused launch, generated by its call's descriptor q; fx is
-// the thread's first slot of the small Floyd sampler's LDS values
-__device__ __forceinline__ void fused_item(const FusedReq* __restrict__ q, const FusedHdr& h, uint64_t item,
-                                           uint32_t* fx) {
-    const uint64_t local = item - q->item_begin;
+// Items [g, end) of a fused tile that starts at item `first`, all of the call
+// with descriptor q (the same in every lane: scalar loads, uniform branches);
+// fx is the thread's first slot of the small Floyd sampler's LDS values.
+__device__ __forceinline__ void fused_items(const FusedReq* __restrict__ q, const FusedHdr& h, uint64_t first,
+                                            uint64_t g, uint64_t end, uint32_t* fx) {
+    const uint64_t origin = q->item_begin;
     if (q->kind == F_FLOYD_SMALL) {
         const IdSink ids{h.src, h.tgt, q->out_base};
-        floyd_small_unit<IdSink, DIRECT>(q->fl, local, fx, NT, ids, nullptr, nullptr);
+#pragma unroll 1
+        for (int it = 0; it < IPT; ++it) {
+            const uint64_t item = first + (uint64_t)it * NT + threadIdx.x;
+            if (item >= g && item < end)
+                floyd_small_unit<IdSink, DIRECT>(q->fl, item - origin, fx, NT, ids, nullptr, nullptr);
+        }
         return;
     }
-    if (q->kind == F_SYN_FILL) {
-        const TChunk ck = q->ind.ch.at(local);
-        const uint64_t off = local - ck.out_begin;
-        const uint32_t rel = fastdiv((uint32_t)off, q->ind.fk);   // a run holds fewer than 2^32 elements
-        const uint32_t j = (uint32_t)off - rel * q->ind.K;
-        float w;
-        uint16_t d;
-        syn_values(q->syn, h.seed, q->call, (ck.t_ord + rel) * (uint64_t)q->ind.K + j, w, d);
-        h.delay[q->out_base + local] = d;
-        h.weight[q->out_base + local] = w;
-        return;
-    }
-    Res r[1];
-    int n = 0;
-    switch (q->kind) {
-    case F_INDEGREE: n = q->ind.eval(local, r); break;
-    case F_TOTAL: n = q->tot.eval(local, r); break;
-    case F_OUTDEGREE: n = q->outd.eval(local, r); break;
-    default: n = q->o2o.eval(local, r); break;
-    }
-    if (n) {
-        const WriteSink ws{h.src, h.tgt, h.delay, h.weight, q->out_base, q->syn, h.seed, q->call};
-        ws.put(local, r[0]);
+    const bool fill = q->kind == F_SYN_FILL;
+    const WriteSink ws{fill ? nullptr : h.src, h.tgt, h.delay, h.weight, q->out_base, q->syn, h.seed, q->call};
+    while (g < end) {
+        uint64_t pos[IPT];
+        Res r[IPT];
+        bool ok[IPT];
+        switch (q->kind) {
+        case F_INDEGREE: g = eval_tile(q->ind, first, g, end, origin, pos, r, ok); break;
+        case F_TOTAL: g = eval_tile(q->tot, first, g, end, origin, pos, r, ok); break;
+        case F_OUTDEGREE: g = eval_tile(q->outd, first, g, end, origin, pos, r, ok); break;
+        case F_SYN_FILL: g = eval_tile(UnitElems{q->ind.ch, q->ind.K}, first, g, end, origin, pos, r, ok); break;
+        default: g = eval_tile(q->o2o, first, g, end, origin, pos, r, ok); break;
+        }
+        ws.put_all(pos, r, ok);
     }
 }
 
@@ -2094,33 +2124,21 @@ __global__ __launch_bounds__(NT) void k_fused(const FusedReq* __restrict__ reqs,
     uint32_t* const my_fx = fx + threadIdx.x;
     const FusedHdr h = *hdr;
     for (uint64_t tile = blockIdx.x; tile * TILE < h.total; tile += gridDim.x) {
-        // the descriptors of the tile's first and last items, found once: the
-        // items' own searches then run over that range only
+        // the descriptors of the tile's first and last items, found once
+        const uint64_t first = tile * TILE, end = min(first + TILE, h.total);
         if (threadIdx.x == 0) {
-            const uint64_t first = tile * TILE, last = min(first + TILE, h.total) - 1;
             const uint32_t lo = find_req(reqs, 0, (uint32_t)h.n_req, first);
             s_range[0] = lo;
-            s_range[1] = find_req(reqs, lo, (uint32_t)h.n_req, last) + 1;
+            s_range[1] = find_req(reqs, lo, (uint32_t)h.n_req, end - 1) + 1;
         }
         __syncthreads();
-        const uint32_t r_lo = __builtin_amdgcn_readfirstlane(s_range[0]);
-        const uint32_t r_hi = __builtin_amdgcn_readfirstlane(s_range[1]);
+        const uint32_t r_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_range[0]);
+        const uint32_t r_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_range[1]);
         __syncthreads();   // read before thread 0 writes the next tile's range
-        if (r_hi - r_lo == 1) {
-            // the usual case, one call for the whole tile: its descriptor is
-            // the same for every lane (scalar loads, uniform branches)
-            const FusedReq* q = reqs + r_lo;
-#pragma unroll 1
-            for (int it = 0; it < IPT; ++it) {
-                const uint64_t item = tile * TILE + (uint64_t)it * NT + threadIdx.x;
-                if (item < h.total) fused_item(q, h, item, my_fx);
-            }
-        } else {
-#pragma unroll 1
-            for (int it = 0; it < IPT; ++it) {
-                const uint64_t item = tile * TILE + (uint64_t)it * NT + threadIdx.x;
-                if (item < h.total) fused_item(reqs + find_req(reqs, r_lo, r_hi, item), h, item, my_fx);
-            }
+        // usually one call; the calls of a tile one after another otherwise
+        for (uint32_t k = r_lo; k < r_hi; ++k) {
+            const uint64_t g = k == r_lo ? first : reqs[k].item_begin;
+            fused_items(reqs + k, h, first, g, k + 1 < r_hi ? reqs[k + 1].item_begin : end, my_fx);
         }
     }
 }
