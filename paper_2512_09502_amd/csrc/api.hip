@@ -1447,9 +1447,6 @@ snnc_status snnc_init(snnc_ctx** out, uint32_t P, uint32_t P_local, uint32_t see
         c->dl_pin = static_cast<char*>(pinned_take(c->dl_pin_bytes, hipHostMallocDefault));
         c->tot_pin = static_cast<uint64_t*>(pinned_take(4 * sizeof(uint64_t), hipHostMallocMapped));
         HIPCHK(hipHostGetDevicePointer((void**)&c->tot_pin_dev, c->tot_pin, 0));
-        c->d_status = dalloc_n<uint32_t>(*c, 1);
-        HIPCHK(hipMemsetAsync(c->d_status, 0, 4, c->stream));
-        sync(*c);
         noalloc_setup(*c);   // device address of the allocation-free sort's static scratch
         c->gen_vmm = gen_blocks_supported(c->device);
         const int tuned = fused_grid_tuned(c->device);   // the fused-launch autotuner's choice, if any
@@ -1607,13 +1604,7 @@ snnc_status snnc_prepare(snnc_ctx* c) {
     return guarded(c, [&] {
         if (c->prepared) raise(SNNC_ESTATE, "prepare called twice");
         flush_pending(*c);
-        if (c->conn_started) {   // the connect phase ends where prepare's work begins
-            HIPCHK(hipEventRecord(c->conn_last, c->stream));
-            HIPCHK(hipEventSynchronize(c->conn_last));
-            float cms = 0.f;
-            HIPCHK(hipEventElapsedTime(&cms, c->conn_first, c->conn_last));
-            c->ms_connect = cms;
-        }
+        if (c->conn_started) HIPCHK(hipEventRecord(c->conn_last, c->stream));   // the connect phase ends here
         HIPCHK(hipEventRecord(c->phase_a, c->stream));
         try {
             for (auto& cl : c->calls) {   // per-call launch tables are no longer needed (stream order)
@@ -1628,12 +1619,13 @@ snnc_status snnc_prepare(snnc_ctx* c) {
         HIPCHK(hipEventRecord(c->phase_b, c->stream));
         HIPCHK(hipEventSynchronize(c->phase_b));
         float ms = 0.f;
+        if (c->conn_started) {
+            HIPCHK(hipEventElapsedTime(&ms, c->conn_first, c->conn_last));
+            c->ms_connect = ms;
+        }
         HIPCHK(hipEventElapsedTime(&ms, c->phase_a, c->phase_b));
         c->ms_prepare = ms;
-        uint32_t status = 0;
-        download(*c, &status, c->d_status, 4);
         gen_release(*c);   // the stream has drained: the generation store goes back, still mapped
-        if (status) raise(SNNC_EDEVICE, "a device wait exceeded its bound (status " + std::to_string(status) + ")");
         c->prepared = true;
     });
 }

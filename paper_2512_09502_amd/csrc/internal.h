@@ -227,8 +227,6 @@ struct Ctx {
     double ms_connect = 0.0, ms_prepare = 0.0;
     hipEvent_t phase_a = nullptr, phase_b = nullptr;
 
-    // device status word for bounded waits (0 = fine)
-    uint32_t* d_status = nullptr;
     // radix-sort look-back epoch (never reset, so status tables need no clearing)
     uint32_t sort_epoch = 0;             // per lane
     void* lookback = nullptr;            // per lane
@@ -237,7 +235,7 @@ struct Ctx {
     bool mark_in_lds = true;             // regeneration marks bit rows in LDS when they fit (tunable)
     int number_variant = 10;             // tile shape of the image-numbering pass (tunable; 1024 x 10, payload early)
     int sort_mode = 0;                   // 0: onesweep (look-back), 1: reduce-then-scan (tunable)
-    uint32_t lookback_spins = 4096;      // polls of an earlier tile before a radix pass counts it itself (tunable)
+    uint32_t lookback_spins = 4096;      // polls of an earlier tile before a pass counts it itself (tunable)
     bool sort_pinned = false;            // set by hand: the autotuner's process-wide choice is not used
     int digit_bits = 0;                  // 0: 9-bit digits when they save a pass; 8 or 9: forced
     // map policy: image numbering (0 canonical, 1 call order), image sources

@@ -376,20 +376,16 @@ constexpr NumberShape NUMBER_SHAPES[] = {{1024, 12}, {512, 12}, {256, 12}, {512,
                                          {256, 8}, {256, 6}, {512, 8}, {1024, 12}, {1024, 10}, {1024, 8}};
 constexpr int NUMBER_VARIANTS = (int)(sizeof(NUMBER_SHAPES) / sizeof(NUMBER_SHAPES[0]));
 constexpr uint64_t XFLAG_AGG = 1ull << 62, XFLAG_INC = 2ull << 62, XVALUE = (1ull << 40) - 1;
-constexpr uint32_t XEPOCH_MAX = (1u << 22) - 1;
+constexpr uint32_t XEPOCH_MASK = (1u << 22) - 1;
 
 template <int XNT, int XIPT, class P>
 __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, uint64_t n, uint32_t M_local,
-                                                uint64_t* lookback, uint32_t* tile_counter, uint32_t epoch,
-                                                uint32_t* status, int32_t* o_src, uint64_t* img_key, uint64_t* row_ptr,
-                                                uint64_t* n_img_out) {
-    __shared__ uint32_t s_tile;
+                                                uint64_t* lookback, uint32_t epoch, uint32_t spin_limit, int32_t* o_src,
+                                                uint64_t* img_key, uint64_t* row_ptr, uint64_t* n_img_out) {
     __shared__ uint64_t wave_tot[XNT / 64];
     __shared__ uint64_t s_excl;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) s_tile = atomicAdd(tile_counter, 1u);
-    __syncthreads();
-    const uint64_t tile = s_tile;
+    const uint64_t tile = blockIdx.x;
     constexpr uint64_t XTILE = (uint64_t)XNT * XIPT;
     const uint64_t wbase = tile * XTILE + (uint64_t)wave * 64 * XIPT;
     // element of item k on this lane: wbase + k*64 + lane (wave-striped, so loads and stores coalesce)
@@ -425,34 +421,50 @@ __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, ui
         if (w < (int)wave) wave_excl += wave_tot[w];
         tile_tot += wave_tot[w];
     }
-    if (threadIdx.x == 0) {
+    if (wave == 0) {
         uint64_t* my = lookback + tile;
+        const uint64_t ep = (uint64_t)epoch << 40;
         uint64_t excl = 0;
-        if (tile == 0) {
-            __hip_atomic_store(my, XFLAG_INC | ((uint64_t)epoch << 40) | tile_tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            __hip_atomic_store(my, XFLAG_AGG | ((uint64_t)epoch << 40) | tile_tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int64_t pred = (int64_t)tile - 1;
-            uint32_t spins = 0;
-            while (pred >= 0) {
-                const uint64_t st = __hip_atomic_load(lookback + pred, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t flag = st & (3ull << 62);
-                if (flag != 0 && (uint32_t)((st >> 40) & XEPOCH_MAX) == epoch) {
-                    excl += st & XVALUE;
-                    if (flag == XFLAG_INC) break;
-                    --pred;
-                    continue;
-                }
-                if (++spins > (1u << 22) || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                    atomicOr(status, 2u);   // bounded wait exceeded: flag the failure and finish the tile
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            __hip_atomic_store(my, XFLAG_INC | ((uint64_t)epoch << 40) | (excl + tile_tot), __ATOMIC_RELAXED,
+        if (lane == 0)
+            __hip_atomic_store(my, (tile == 0 ? XFLAG_INC : XFLAG_AGG) | ep | tile_tot, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
+        // the wave reads 64 earlier tiles at a time, nearest first, up to one with its inclusive count
+        int64_t pred = (int64_t)tile - 1;
+        uint32_t spins = 0;
+        while (pred >= 0) {
+            const int64_t t = pred - lane;
+            const uint64_t st = t >= 0 ? __hip_atomic_load(lookback + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                       : XFLAG_INC | ep;
+            const bool ready = (st >> 62) != 0 && ((st >> 40) & XEPOCH_MASK) == epoch;
+            const uint64_t m_ready = __ballot(ready), m_inc = __ballot(ready && (st >> 62) == 2);
+            const uint32_t stop = m_inc ? (uint32_t)__ffsll((unsigned long long)m_inc) : 64u;   // lanes to take
+            const uint64_t need = ~0ull >> (64 - stop);
+            const uint64_t missing = need & ~m_ready;
+            if (missing && spins++ < spin_limit) {
+                __builtin_amdgcn_s_sleep(1);
+                continue;
+            }
+            // a tile that stays without counts (its workgroup may not have started): the wave counts it
+            const uint32_t take = missing ? (uint32_t)__ffsll((unsigned long long)missing) - 1 : stop;
+            uint64_t v = lane < take ? st & XVALUE : 0;
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            excl += v;
+            pred -= take;
+            if (!missing) {
+                if (m_inc) break;
+                continue;
+            }
+            for (uint64_t i0 = (uint64_t)pred * XTILE; i0 < ((uint64_t)pred + 1) * XTILE; i0 += 64) {
+                const uint64_t i = i0 + lane;   // every tile before the last is full
+                excl += (uint64_t)__popcll(__ballot(prefix[i] >= M_local && (i == 0 || prefix[i] != prefix[i - 1])));
+            }
+            --pred;
         }
-        s_excl = excl;
+        if (lane == 0) {
+            if (tile)
+                __hip_atomic_store(my, XFLAG_INC | ep | (excl + tile_tot), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_excl = excl;
+        }
     }
     __syncthreads();
     const uint64_t before = s_excl + wave_excl;   // images started before this wave
@@ -717,9 +729,30 @@ __global__ void k_csr_search(const int32_t* src, uint64_t n, uint64_t n_rows, ui
     row_ptr[r] = lo;
 }
 
-__global__ void k_fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+// Constant result arrays (no image, no send list, no group), all in one launch.
+struct Fills {
+    static constexpr int MAX = 8;
+    uint64_t* p[MAX];
+    uint64_t n[MAX], v[MAX];
+    int count = 0;
+    void add(uint64_t* ptr, uint64_t len, uint64_t value) {
+        p[count] = ptr;
+        n[count] = len;
+        v[count] = value;
+        ++count;
+    }
+};
+
+__global__ __launch_bounds__(PNT) void k_fills(Fills f) {
+    for (int k = 0; k < f.count; ++k)
+        for (uint64_t i = (uint64_t)blockIdx.x * PNT + threadIdx.x; i < f.n[k]; i += (uint64_t)gridDim.x * PNT)
+            f.p[k][i] = f.v[k];
+}
+
+// offsets of the send rows: rank of every row's first word
+__global__ void k_row_offsets(const uint64_t* row_rank, uint32_t P, uint32_t words_per_row, uint64_t* s_off) {
+    const uint32_t tau = blockIdx.x * blockDim.x + threadIdx.x;
+    if (tau <= P) s_off[tau] = row_rank[(uint64_t)tau * words_per_row];
 }
 
 // ---- point-to-point lists
@@ -892,25 +925,31 @@ __global__ void k_img_rows(const uint64_t* row_ptr, uint32_t M_local, uint64_t n
     }
 }
 
-// Moves a result array into pinned host memory that kernels can read.
-void to_host(Ctx& c, int32_t id) {
-    auto it = c.arrays.find(id);
-    if (it == c.arrays.end() || it->second.host) return;
-    DevArray& a = it->second;
-    void* h = nullptr;
-    HIPCHK(hipHostMalloc(&h, std::max<size_t>(a.bytes, 1), hipHostMallocMapped));
-    void* d = nullptr;
-    if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipHostFree(h);
-        raise(SNNC_EDEVICE, "pinned host memory without a device address");
+// Moves result arrays into pinned host memory that kernels can read: all the
+// copies, then one wait.
+void to_host(Ctx& c, std::initializer_list<int32_t> ids) {
+    std::vector<void*> old;
+    for (int32_t id : ids) {
+        auto it = c.arrays.find(id);
+        if (it == c.arrays.end() || it->second.host) continue;
+        DevArray& a = it->second;
+        void* h = nullptr;
+        HIPCHK(hipHostMalloc(&h, std::max<size_t>(a.bytes, 1), hipHostMallocMapped));
+        void* d = nullptr;
+        if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(h);
+            raise(SNNC_EDEVICE, "pinned host memory without a device address");
+        }
+        old.push_back(a.p);
+        const void* from = a.p;
+        a.p = h;
+        a.dev = d;
+        a.host = true;
+        if (a.bytes) HIPCHK(hipMemcpyAsync(h, from, a.bytes, hipMemcpyDeviceToHost, c.stream));
     }
-    if (a.bytes) HIPCHK(hipMemcpyAsync(h, a.p, a.bytes, hipMemcpyDeviceToHost, c.stream));
-    HIPCHK(hipStreamSynchronize(c.stream));
-    dfree(c, a.p);
-    a.p = h;
-    a.dev = d;
-    a.host = true;
+    sync(c);
+    for (void* p : old) dfree(c, p);
 }
 
 // GPU memory levels (Methods, GPU memory levels subsection).  Levels 0 and 1:
@@ -942,9 +981,8 @@ void place_memory_level(Ctx& c, uint32_t M_local) {
     uint64_t* nrp = result<uint64_t>(c, SNNC_ROW_PTR, keep);
     HIPCHK(hipMemcpyAsync(nrp, old.p, keep * 8, hipMemcpyDeviceToDevice, c.stream));
     free_array(c, old);
-    for (int32_t id : {SNNC_IMG_FIRST, SNNC_IMG_COUNT, SNNC_R_OFF, SNNC_R_VAL, SNNC_IMG_BASE, SNNC_L_VAL, SNNC_H_OFF,
-                       SNNC_H_VAL, SNNC_I_VAL})
-        to_host(c, id);
+    to_host(c, {SNNC_IMG_FIRST, SNNC_IMG_COUNT, SNNC_R_OFF, SNNC_R_VAL, SNNC_IMG_BASE, SNNC_L_VAL, SNNC_H_OFF,
+                SNNC_H_VAL, SNNC_I_VAL});
 }
 
 // Intervals of targets covered by the same calls, and the calls' entries in
@@ -1074,8 +1112,7 @@ void prepare_all(Ctx& c) {
             call_begin.push_back(cl.gen_begin);
         }
         call_begin.push_back(N);
-        uint64_t* d_hb = static_cast<uint64_t*>(tmp((P + 1) * 8));
-        upload(c, d_hb, host_base.data(), (P + 1) * 8);
+        Fills fills;
 
         // ---------------------------------------------------------- 1-5 image map, keys, sort, first index
         // Default policy: without remote sources the keys hold final sources and
@@ -1090,9 +1127,19 @@ void prepare_all(Ctx& c) {
         const bool mapped = c.numbering != 0 || c.img_sources != 0 || c.force_map_path;
         const uint64_t n_bits = (uint64_t)n_a * G;
         const uint64_t n_words = n_bits / 32 + 1;    // one spare word: rank of the end bit
-        uint32_t* bits = static_cast<uint32_t*>(tmp(n_words * 4));
-        HIPCHK(hipMemsetAsync(bits, 0, n_words * 4, c.stream));
-        uint64_t* word_rank = static_cast<uint64_t*>(tmp((n_words + 1) * 8));
+        const bool need_bits = mapped || amax >= 0;  // the image bit set: numbering before the sort, collective arrays
+        uint32_t* bits = nullptr;
+        uint64_t* word_rank = nullptr;
+        uint64_t* d_hb = nullptr;
+        if (need_bits || remote_net) {
+            d_hb = static_cast<uint64_t*>(tmp((P + 1) * 8));
+            upload(c, d_hb, host_base.data(), (P + 1) * 8);
+        }
+        if (need_bits) {
+            bits = static_cast<uint32_t*>(tmp(n_words * 4));
+            HIPCHK(hipMemsetAsync(bits, 0, n_words * 4, c.stream));
+            word_rank = static_cast<uint64_t*>(tmp((n_words + 1) * 8));
+        }
         uint64_t n_img = 0;
         int32_t* Lmap = nullptr;
         if (mapped) {
@@ -1300,18 +1347,16 @@ void prepare_all(Ctx& c) {
                 const uint64_t tiles = (N + xtile - 1) / xtile;
                 ensure_lookback(c, tiles * 8);
                 next_epoch(c);
-                uint32_t* counter = static_cast<uint32_t*>(tmp(4));
-                HIPCHK(hipMemsetAsync(counter, 0, 4, c.stream));
                 tstart(c, "prep_number");
                 auto number = [&](auto kern32, auto kern64, int nt) {
                     if (wide_prefix)
                         hipLaunchKernelGGL(kern64, dim3((unsigned)tiles), dim3(nt), 0, c.stream,
                                            (const uint64_t*)prefix, N, M_local, (uint64_t*)c.lookback,
-                                           counter, c.sort_epoch, c.d_status, o_src, img_key, row_ptr, d_nimg);
+                                           c.sort_epoch, c.lookback_spins, o_src, img_key, row_ptr, d_nimg);
                     else
                         hipLaunchKernelGGL(kern32, dim3((unsigned)tiles), dim3(nt), 0, c.stream,
                                            reinterpret_cast<const uint32_t*>(prefix), N, M_local, (uint64_t*)c.lookback,
-                                           counter, c.sort_epoch, c.d_status, o_src, img_key, row_ptr, d_nimg);
+                                           c.sort_epoch, c.lookback_spins, o_src, img_key, row_ptr, d_nimg);
                 };
 #define NUMBER(nt, ipt) number(k_number<nt, ipt, uint32_t>, k_number<nt, ipt, uint64_t>, nt)
                 switch (shape.nt * 100 + shape.ipt) {
@@ -1343,11 +1388,13 @@ void prepare_all(Ctx& c) {
                                        img_key, n_img, d_hb, P, G, R);
                     tstop(c);
                     HIPCHK(hipGetLastError());
-                    tstart(c, "prep_bits");
-                    hipLaunchKernelGGL(k_bits_sorted, dim3((unsigned)((n_img + 255) / 256)), dim3(256), 0, c.stream,
-                                       img_key, n_img, bits);
-                    tstop(c);
-                    HIPCHK(hipGetLastError());
+                    if (need_bits) {
+                        tstart(c, "prep_bits");
+                        hipLaunchKernelGGL(k_bits_sorted, dim3((unsigned)((n_img + 255) / 256)), dim3(256), 0, c.stream,
+                                           img_key, n_img, bits);
+                        tstop(c);
+                        HIPCHK(hipGetLastError());
+                    }
                     hipLaunchKernelGGL(k_iota_l, dim3((unsigned)((n_img + 255) / 256)), dim3(256), 0, c.stream, Lmap,
                                        n_img, M_local);
                     HIPCHK(hipGetLastError());
@@ -1366,22 +1413,18 @@ void prepare_all(Ctx& c) {
             result<float>(c, SNNC_WEIGHT, 0);
             const uint64_t n_rows = (uint64_t)M_local + n_img;
             row_ptr = result<uint64_t>(c, SNNC_ROW_PTR, n_rows + 1);
-            hipLaunchKernelGGL(k_fill_u64, dim3((n_rows + 1 + 255) / 256), dim3(256), 0, c.stream, row_ptr, n_rows + 1,
-                               (uint64_t)0);
-            HIPCHK(hipGetLastError());
+            fills.add(row_ptr, n_rows + 1, 0);
         }
         if (!mapped && (!remote_net || !N)) {
             result<int32_t>(c, SNNC_R_VAL, 0);
             result<int32_t>(c, SNNC_L_VAL, 0);
-            uint64_t* r_off = result<uint64_t>(c, SNNC_R_OFF, (uint64_t)n_a * P + 1);
-            int64_t* img_base = result<int64_t>(c, SNNC_IMG_BASE, (uint64_t)n_a * P);
-            HIPCHK(hipMemsetAsync(r_off, 0, ((uint64_t)n_a * P + 1) * 8, c.stream));
-            std::vector<int64_t> ib((size_t)n_a * P, (int64_t)M_local);
-            upload(c, img_base, ib.data(), ib.size() * 8);
+            fills.add(result<uint64_t>(c, SNNC_R_OFF, (uint64_t)n_a * P + 1), (uint64_t)n_a * P + 1, 0);
+            fills.add(reinterpret_cast<uint64_t*>(result<int64_t>(c, SNNC_IMG_BASE, (uint64_t)n_a * P)), (uint64_t)n_a * P,
+                      M_local);
         }
         c.n_img = n_img;
         // word ranks of the image bit set (the collective arrays look images up by bit)
-        if (!mapped) scan_popc_u64(c, bits, word_rank, n_words, false);
+        if (need_bits && !mapped) scan_popc_u64(c, bits, word_rank, n_words, false);
         if (!c.gen_vmm) {   // block store: unmapped after the final wait of Prepare
             dfree(c, c.g_weight);
             c.g_weight = nullptr;
@@ -1392,8 +1435,14 @@ void prepare_all(Ctx& c) {
         // ---------------------------------------------------------- 6 point-to-point lists
         const uint32_t wpr = (M_local + 31) / 32 + 1;     // words per row (+1 spare)
         const uint64_t n_rw = (uint64_t)P * wpr;
-        uint32_t* rows = static_cast<uint32_t*>(tmp(n_rw * 4));
-        HIPCHK(hipMemsetAsync(rows, 0, n_rw * 4, c.stream));
+        uint32_t* rows = nullptr;   // allocated when some call has an entry to make
+        auto row_of = [&](uint32_t tau) {
+            if (!rows) {
+                rows = static_cast<uint32_t*>(tmp(n_rw * 4));
+                HIPCHK(hipMemsetAsync(rows, 0, n_rw * 4, c.stream));
+            }
+            return rows + (uint64_t)tau * wpr;
+        };
         std::vector<WRange> wr;
         uint64_t w_total = 0;
         for (auto& cl : c.calls) {
@@ -1404,7 +1453,7 @@ void prepare_all(Ctx& c) {
             for (uint32_t tau = 0; tau < P; ++tau) {
                 if (tau == PL || count_on(cl.T, tau) == 0) continue;
                 if (flag_sources(c, cl, tau)) {   // regenerate tau's draws, keep the local sources they use
-                    gen_mark(c, cl, tau, rows + (uint64_t)tau * wpr);
+                    gen_mark(c, cl, tau, row_of(tau));
                     continue;
                 }
                 for (auto& g : cl.S.seg)          // not flagged: every local source of the call
@@ -1415,6 +1464,7 @@ void prepare_all(Ctx& c) {
             }
         }
         if (w_total) {
+            row_of(0);
             WRange* d_wr = static_cast<WRange*>(tmp(wr.size() * sizeof(WRange)));
             upload(c, d_wr, wr.data(), wr.size() * sizeof(WRange));
             tstart(c, "prep_s_ranges");
@@ -1423,16 +1473,19 @@ void prepare_all(Ctx& c) {
             tstop(c);
             HIPCHK(hipGetLastError());
         }
-        uint64_t* row_rank = static_cast<uint64_t*>(tmp((n_rw + 1) * 8));
-        const uint64_t n_s = scan_popc_u64(c, rows, row_rank, n_rw, true);
-        std::vector<uint64_t> rank_host(n_rw + 1);
-        download(c, rank_host.data(), row_rank, (n_rw + 1) * 8);
-        std::vector<uint64_t> s_off_h(P + 1);
-        for (uint32_t tau = 0; tau <= P; ++tau) s_off_h[tau] = rank_host[(uint64_t)tau * wpr];
         uint64_t* s_off = result<uint64_t>(c, SNNC_S_OFF, P + 1);
-        upload(c, s_off, s_off_h.data(), (P + 1) * 8);
-        int32_t* S = result<int32_t>(c, SNNC_S_VAL, n_s);
         uint64_t* tp_ptr = result<uint64_t>(c, SNNC_TP_PTR, (uint64_t)M_local + 1);
+        uint64_t* row_rank = nullptr;
+        uint64_t n_s = 0;
+        if (rows) {
+            row_rank = static_cast<uint64_t*>(tmp((n_rw + 1) * 8));
+            n_s = scan_popc_u64(c, rows, row_rank, n_rw, true);
+            hipLaunchKernelGGL(k_row_offsets, dim3((P + 1 + 255) / 256), dim3(256), 0, c.stream, row_rank, P, wpr, s_off);
+            HIPCHK(hipGetLastError());
+        } else {
+            fills.add(s_off, P + 1, 0);
+        }
+        int32_t* S = result<int32_t>(c, SNNC_S_VAL, n_s);
         uint32_t* Tv = result<uint32_t>(c, SNNC_T_VAL, n_s);
         uint32_t* Pv = result<uint32_t>(c, SNNC_P_VAL, n_s);
         if (n_s) {
@@ -1440,8 +1493,6 @@ void prepare_all(Ctx& c) {
             hipLaunchKernelGGL(k_s_vals, dim3(grid_for(n_rw)), dim3(PNT), 0, c.stream, rows, row_rank, n_rw, wpr, S);
             tstop(c);
             HIPCHK(hipGetLastError());
-        }
-        if (M_local) {
             uint32_t* cnt = static_cast<uint32_t*>(tmp((size_t)M_local * 4));
             tstart(c, "prep_tp");
             hipLaunchKernelGGL(k_tp_count, dim3((M_local + PNT - 1) / PNT), dim3(PNT), 0, c.stream, rows, P, wpr,
@@ -1449,15 +1500,13 @@ void prepare_all(Ctx& c) {
             tstop(c);
             HIPCHK(hipGetLastError());
             scan_u32_u64(c, cnt, tp_ptr, M_local, false);
-            if (n_s) {
-                tstart(c, "prep_tp");
-                hipLaunchKernelGGL(k_tp_fill, dim3((M_local + PNT - 1) / PNT), dim3(PNT), 0, c.stream, rows, row_rank,
-                                   s_off, P, wpr, M_local, tp_ptr, Tv, Pv);
-                tstop(c);
-                HIPCHK(hipGetLastError());
-            }
+            tstart(c, "prep_tp");
+            hipLaunchKernelGGL(k_tp_fill, dim3((M_local + PNT - 1) / PNT), dim3(PNT), 0, c.stream, rows, row_rank, s_off,
+                               P, wpr, M_local, tp_ptr, Tv, Pv);
+            tstop(c);
+            HIPCHK(hipGetLastError());
         } else {
-            HIPCHK(hipMemsetAsync(tp_ptr, 0, 8, c.stream));
+            fills.add(tp_ptr, (uint64_t)M_local + 1, 0);
         }
 
         // ---------------------------------------------------------- 7 collective arrays
@@ -1501,7 +1550,8 @@ void prepare_all(Ctx& c) {
         int32_t* d_groups = result<int32_t>(c, SNNC_GROUPS, NG);
         upload(c, d_groups, groups.data(), NG * 4);
         uint64_t* h_off = result<uint64_t>(c, SNNC_H_OFF, (uint64_t)NG * P + 1);
-        upload(c, h_off, h_off_h.data(), h_off_h.size() * 8);
+        if (NG) upload(c, h_off, h_off_h.data(), h_off_h.size() * 8);
+        else fills.add(h_off, 1, 0);
         int32_t* Hv = result<int32_t>(c, SNNC_H_VAL, h_total);
         int32_t* Iv = result<int32_t>(c, SNNC_I_VAL, h_total);
         if (h_total) {
@@ -1537,15 +1587,18 @@ void prepare_all(Ctx& c) {
                 HIPCHK(hipGetLastError());
             }
         } else {
-            tstart(c, "prep_gq");
-            hipLaunchKernelGGL(k_fill_u64, dim3(((uint64_t)M_local + 1 + 255) / 256), dim3(256), 0, c.stream, gq_ptr,
-                               (uint64_t)M_local + 1, (uint64_t)0);
-            tstop(c);
-            HIPCHK(hipGetLastError());
+            fills.add(gq_ptr, (uint64_t)M_local + 1, 0);
             result<int32_t>(c, SNNC_G_VAL, 0);
             result<uint32_t>(c, SNNC_Q_VAL, 0);
         }
-        sync(c);
+        if (fills.count) {
+            uint64_t most = 0;
+            for (int k = 0; k < fills.count; ++k) most = std::max(most, fills.n[k]);
+            tstart(c, "prep_fills");
+            hipLaunchKernelGGL(k_fills, dim3(grid_for(most, 4096)), dim3(PNT), 0, c.stream, fills);
+            tstop(c);
+            HIPCHK(hipGetLastError());
+        }
         place_memory_level(c, M_local);
     } catch (...) {
         cleanup();

@@ -29,6 +29,16 @@ def test_tile_order(spins, bits, n):
     net.close()
 
 
+@pytest.mark.parametrize("spins", [0, 1, 4096])
+@pytest.mark.parametrize("variant", [7, 10])              # 256 x 6 and 1024 x 10 items a tile
+def test_numbering_counts_missing_tiles(spins, variant):
+    from gpu_util import compare_all
+    from paper_2512_09502_amd import workloads as W
+    s = W.balanced_collective(P=7, n_e=400, n_i=100, k_e=180, k_i=45)
+    s["tune"] = {"lookback_spins": spins, "number_variant": variant}
+    compare_all(s, 3)
+
+
 def test_spin_limit_range():
     import paper_2512_09502_amd as snnc
     net = snnc.Network(1, 0, 1, 0.1)
