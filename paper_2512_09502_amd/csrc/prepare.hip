@@ -274,27 +274,32 @@ __global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t 
 }
 
 // The same in target-major order, with the weights moved along: 10 B read
-// (source, delay, weight) and 12 B written per connection.  A wave takes TM_UNIT
-// consecutive positions; it walks the runs of a call in them one after
+// (source, delay, weight) and 12 B written per connection.  A wave takes
+// `unit` consecutive positions; it walks the runs of a call in them one after
 // another (all their parameters the same in every lane, so scalar) and each
 // run by 64 lanes x 4.  The alternative of letting the first radix pass gather
 // its own connections was slower: the pass ranks 16 keys a lane at 16 waves a
 // compute unit, and waits for the gather (multi-area: first pass 10.3 ms
 // instead of 4.1, against 3.3 for this kernel).
-constexpr uint32_t TM_UNIT = 2048;
+constexpr uint32_t TM_UNIT = 2048;   // at most; fewer (whole steps of a wave) where 2048 would leave compute units idle:
+                                     // 1e5 connections 53.6 us with units of 2048, 10.6 with units of 128
+
+uint32_t tm_unit(uint64_t n) {
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n / 8192 / 64 * 64, 128), TM_UNIT);
+}
 
 __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, uint32_t bit_lo, uint32_t n9,
-                                                     uint32_t dbits, uint32_t passes, uint64_t* keys, uint32_t* vals,
-                                                     uint64_t* hist) {
+                                                     uint32_t dbits, uint32_t passes, uint32_t unit_size, uint64_t* keys,
+                                                     uint32_t* vals, uint64_t* hist) {
     __shared__ uint32_t h[8 * HIST_STRIDE];
     for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT) h[i] = 0;
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (uint64_t unit = (uint64_t)blockIdx.x * (PNT / 64) + wave; unit * TM_UNIT < n;
+    for (uint64_t unit = (uint64_t)blockIdx.x * (PNT / 64) + wave; unit * unit_size < n;
          unit += (uint64_t)gridDim.x * (PNT / 64)) {
-        uint64_t q = unit * TM_UNIT;
-        const uint64_t end = q + TM_UNIT < n ? q + TM_UNIT : n;
+        uint64_t q = unit * unit_size;
+        const uint64_t end = q + unit_size < n ? q + unit_size : n;
         uint32_t a = 0, b = g.n_iv;
         while (b - a > 1) {
             const uint32_t m = (a + b) >> 1;
@@ -378,6 +383,15 @@ constexpr int NUMBER_VARIANTS = (int)(sizeof(NUMBER_SHAPES) / sizeof(NUMBER_SHAP
 constexpr uint64_t XFLAG_AGG = 1ull << 62, XFLAG_INC = 2ull << 62, XVALUE = (1ull << 40) - 1;
 constexpr uint32_t XEPOCH_MASK = (1u << 22) - 1;
 
+template <class P>
+__device__ __forceinline__ P last_lane(P v) {   // lane 63's value
+    if constexpr (sizeof(P) == 8)
+        return ((P)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+    else
+        return (P)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 template <int XNT, int XIPT, class P>
 __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, uint64_t n, uint32_t M_local,
                                                 uint64_t* lookback, uint32_t epoch, uint32_t spin_limit, int32_t* o_src,
@@ -393,7 +407,6 @@ __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, ui
     uint32_t incl[XIPT];          // flags up to and including the item, within the wave
     uint32_t fl = 0;              // bit k: item k starts a new image
     const P before_wave = wbase > 0 && wbase - 1 < n ? prefix[wbase - 1] : ~(P)0;
-    P last = before_wave;         // prefix before the wave
     uint32_t carry = 0;
 #pragma unroll
     for (int k = 0; k < XIPT; ++k) {
@@ -401,13 +414,15 @@ __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, ui
         key[k] = i < n ? prefix[i] : ~(P)0;
     }
     const uint64_t upto = ~0ull >> (63 - lane);   // lanes up to and including this one
+    uint32_t bl = 0;              // bit k: item k starts a row
 #pragma unroll
     for (int k = 0; k < XIPT; ++k) {
         const uint64_t i = wbase + (uint64_t)k * 64 + lane;
         P prev = __shfl_up(key[k], 1, 64);
-        if (lane == 0) prev = last;
-        last = __shfl(key[k], 63, 64);
-        const bool f = i < n && key[k] >= M_local && (i == 0 || key[k] != prev);
+        if (lane == 0) prev = k ? last_lane(key[k ? k - 1 : 0]) : before_wave;
+        const bool b = i < n && (i == 0 || key[k] != prev);
+        const bool f = b && key[k] >= M_local;
+        bl |= (b ? 1u : 0u) << k;
         fl |= (f ? 1u : 0u) << k;
         const uint64_t m = __ballot(f);
         incl[k] = carry + (uint32_t)__popcll(m & upto);
@@ -468,33 +483,33 @@ __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, ui
     }
     __syncthreads();
     const uint64_t before = s_excl + wave_excl;   // images started before this wave
-    last = before_wave;
+    // past the local rows every row is an image's, starts at its flag and has connections: one
+    // store per image; among the local rows runs of empty ones are filled as well
+    const bool images_only = wbase > 0 && before_wave >= M_local;   // the same in every lane
 #pragma unroll
     for (int k = 0; k < XIPT; ++k) {
         const uint64_t i = wbase + (uint64_t)k * 64 + lane;
-        P pp = __shfl_up(key[k], 1, 64);     // prefix of the previous connection
-        if (lane == 0) pp = last;
-        last = __shfl(key[k], 63, 64);
         const uint64_t rank = before + incl[k];                 // images started up to and including i
-        int64_t lo = 0, hi = -1, end_lo = 0, end_hi = -1;       // rows closed here and after the last connection
-        if (i < n) {
-            const int64_t src2 = key[k] < M_local ? (int64_t)key[k] : (int64_t)(M_local + rank - 1);
-            o_src[i] = (int32_t)src2;
-            // previous connection's source' (its flag count is rank minus this item's flag)
-            const bool flag_here = (fl >> k) & 1u;
-            int64_t prev2 = -1;
-            if (i > 0) prev2 = pp < M_local ? (int64_t)pp : (int64_t)(M_local + rank - (flag_here ? 1 : 0) - 1);
-            if (flag_here) img_key[rank - 1] = (uint64_t)key[k] - M_local;
-            lo = prev2 + 1;
-            hi = src2;
-            if (i + 1 == n) {
-                end_lo = src2 + 1;
-                end_hi = (int64_t)M_local + (int64_t)rank;
-                *n_img_out = rank;
+        const bool flag_here = (fl >> k) & 1u;
+        const int64_t src2 = key[k] < M_local ? (int64_t)key[k] : (int64_t)(M_local + rank - 1);
+        if (i < n) o_src[i] = (int32_t)src2;
+        if (flag_here) img_key[rank - 1] = (uint64_t)key[k] - M_local;
+        if (images_only) {
+            if (flag_here) row_ptr[src2] = i;
+        } else if (__ballot((bl >> k) & 1u)) {
+            P pp = __shfl_up(key[k], 1, 64);     // prefix of the previous connection
+            if (lane == 0) pp = k ? last_lane(key[k ? k - 1 : 0]) : before_wave;
+            int64_t lo = 0, hi = -1;
+            if ((bl >> k) & 1u) {   // the previous row: a local one, or the image before this one
+                lo = i == 0 ? 0 : pp < M_local ? (int64_t)pp + 1 : src2;
+                hi = src2;
             }
+            fill_rows(row_ptr, lo, hi, i);
         }
-        fill_rows(row_ptr, lo, hi, i);
-        if (__ballot(end_hi >= end_lo)) fill_rows(row_ptr, end_lo, end_hi, n);
+        if (i + 1 == n) *n_img_out = rank;
+        const bool ends = i + 1 == n;
+        if (__ballot(ends))   // rows after the last connection
+            fill_rows(row_ptr, ends ? src2 + 1 : 0, ends ? (int64_t)M_local + (int64_t)rank : -1, n);
     }
 }
 
@@ -805,24 +820,53 @@ struct HRange {
     uint32_t a, sigma;  // map index alpha + 1 and host
 };
 
+// H and I: a workgroup takes PNT * HI_RUN consecutive entries at a time and finds
+// the range of its first one once (the ranges are long: a host's population);
+// only entries past that range search for their own.  canonical: images are
+// numbered in the order of their bits, so L is the rank and is not read.
+// Bound by the two written arrays and the random reads of the bit set; 1,024
+// hosts with 2.3e8 entries: 0.70 ms, one entry a thread with a search each 2.5 ms.
+constexpr int HI_RUN = 8;
+
 __global__ __launch_bounds__(PNT) void k_hi(const HRange* rg, uint32_t n_rg, uint64_t n_h, const uint32_t* bits,
-                                            const uint64_t* word_rank, const int32_t* Lmap, const uint64_t* host_base,
-                                            uint64_t G, uint32_t PL, int32_t* H, int32_t* I) {
-    for (uint64_t j = (uint64_t)blockIdx.x * PNT + threadIdx.x; j < n_h; j += (uint64_t)gridDim.x * PNT) {
-        uint32_t a = 0, b = n_rg;
-        while (b - a > 1) {
-            const uint32_t m = (a + b) >> 1;
-            if (rg[m].h_begin <= j) a = m; else b = m;
+                                            const uint64_t* word_rank, const int32_t* Lmap, int canonical,
+                                            uint32_t M_local, const uint64_t* host_base, uint64_t G, uint32_t PL,
+                                            int32_t* H, int32_t* I) {
+    for (uint64_t j0 = (uint64_t)blockIdx.x * PNT * HI_RUN; j0 < n_h; j0 += (uint64_t)gridDim.x * PNT * HI_RUN) {
+        auto range_of = [&](uint64_t j) {
+            uint32_t a = 0, b = n_rg;
+            while (b - a > 1) {
+                const uint32_t m = (a + b) >> 1;
+                if (rg[m].h_begin <= j) a = m; else b = m;
+            }
+            return a;
+        };
+        const HRange first = rg[range_of(j0)];
+        const uint64_t first_end = first.h_begin + first.len;
+        const uint64_t first_bit = (uint64_t)first.a * G + host_base[first.sigma];
+#pragma unroll
+        for (int k = 0; k < HI_RUN; ++k) {
+            const uint64_t j = j0 + (uint64_t)k * PNT + threadIdx.x;
+            if (j >= n_h) break;
+            HRange r = first;
+            uint64_t bit0 = first_bit;
+            if (j >= first_end) {
+                r = rg[range_of(j)];
+                bit0 = (uint64_t)r.a * G + host_base[r.sigma];
+            }
+            const uint32_t s = r.lo + (uint32_t)(j - r.h_begin);
+            H[j] = (int32_t)s;
+            int32_t img = -1;
+            if (r.sigma != PL) {
+                const uint64_t bit = bit0 + s;
+                const uint32_t word = bits[bit >> 5];
+                if ((word >> (bit & 31)) & 1u) {
+                    const uint64_t rank = word_rank[bit >> 5] + (uint64_t)__popc(word & ((1u << (bit & 31)) - 1u));
+                    img = canonical ? (int32_t)(M_local + rank) : Lmap[rank];
+                }
+            }
+            I[j] = img;
         }
-        const HRange r = rg[a];
-        const uint32_t s = r.lo + (uint32_t)(j - r.h_begin);
-        H[j] = (int32_t)s;
-        int32_t img = -1;
-        if (r.sigma != PL) {
-            const uint64_t bit = (uint64_t)r.a * G + host_base[r.sigma] + s;
-            if ((bits[bit >> 5] >> (bit & 31)) & 1u) img = Lmap[rank_of(bits, word_rank, bit)];
-        }
-        I[j] = img;
     }
 }
 
@@ -1289,9 +1333,11 @@ void prepare_all(Ctx& c) {
             uint64_t* hist = static_cast<uint64_t*>(tmp(8 * HIST_STRIDE * 8));
             HIPCHK(hipMemsetAsync(hist, 0, 8 * HIST_STRIDE * 8, c.stream));
             tstart(c, "prep_keys");
+            const uint32_t unit = tm_unit(N);
             if (by_source)
-                hipLaunchKernelGGL(k_keys_tmajor, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, gs, N, bit_lo, pl.n9,
-                                   pl.dbits, pl.passes, keys0, moved, hist);
+                hipLaunchKernelGGL(k_keys_tmajor,
+                                   dim3((unsigned)std::min<uint64_t>((N + unit * 4 - 1) / (unit * 4), 8192)), dim3(PNT), 0,
+                                   c.stream, gs, N, bit_lo, pl.n9, pl.dbits, pl.passes, unit, keys0, moved, hist);
             else
                 hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, gs, N, bit_lo, pl.n9, pl.dbits,
                                    pl.passes, keys0, hist);
@@ -1558,8 +1604,9 @@ void prepare_all(Ctx& c) {
             HRange* d_rg = static_cast<HRange*>(tmp(ranges.size() * sizeof(HRange)));
             upload(c, d_rg, ranges.data(), ranges.size() * sizeof(HRange));
             tstart(c, "prep_hi");
-            hipLaunchKernelGGL(k_hi, dim3(grid_for(h_total)), dim3(PNT), 0, c.stream, d_rg, (uint32_t)ranges.size(),
-                               h_total, bits, word_rank, Lmap, d_hb, G, PL, Hv, Iv);
+            hipLaunchKernelGGL(k_hi, dim3(grid_for((h_total + HI_RUN - 1) / HI_RUN)), dim3(PNT), 0, c.stream, d_rg,
+                               (uint32_t)ranges.size(), h_total, bits, word_rank, Lmap, c.numbering == 0 ? 1 : 0, M_local,
+                               d_hb, G, PL, Hv, Iv);
             tstop(c);
             HIPCHK(hipGetLastError());
         }

@@ -60,3 +60,9 @@ def test_sort_settings(variant, mode):
     s = W.balanced_collective(P=5, n_e=160, n_i=40, k_e=90, k_i=22)
     s["tune"] = {"sort_variant": variant, "sort_mode": mode}
     compare_all(s, 2)
+
+
+@pytest.mark.parametrize("n_e", [1, 2007, 2008, 2009, 4057])
+def test_group_ranges(n_e):
+    """H/I ranges below, at and above the 2,048 entries a workgroup takes at a time (40 more by the inhibitory one)."""
+    compare_all(W.balanced_collective(P=5, n_e=n_e, n_i=40, k_e=3, k_i=2), 3)
