@@ -400,7 +400,7 @@ void scan_batch_run(Ctx& c);
 void first_small_batch_run(Ctx& c);
 // the same over popcounts of 32-bit words
 uint64_t scan_popc_u64(Ctx& c, const uint32_t* words, uint64_t* out, uint64_t n_words, bool want_total);
-uint64_t scan_u64_u64(Ctx& c, const uint64_t* in, uint64_t* out, uint64_t n, bool want_total);
+void scan_u64_u64_to(Ctx& c, const uint64_t* in, uint64_t* out, uint64_t n, uint64_t* total_dev);   // n > 0
 
 // stable LSD radix sort on bits [bit_lo, bit_hi) of 64-bit keys with a
 // 32-bit payload (sort.hip).  Ping-pong buffers are supplied by the caller;

@@ -133,3 +133,44 @@ def test_spike_exchange_errors():
         fresh.spike_packets(0, _dev([0]))
     assert e.value.code == -4
     fresh.close()
+
+
+def _in(K, **kw):
+    return {"rule": "fixed_indegree", "n": K, "autapses": True, "multapses": True, **kw}
+
+
+SYN = {"weight": W.W_E, "delay": {"kind": "const", "mean": 0.3}}
+
+
+@pytest.mark.parametrize("P,n_src,K", [(3, 3000, 40), (700, 300, 30), (4101, 60, 5)])
+def test_packet_tiles(P, n_src, K):
+    """Spike counts around one workgroup's share, single spikes a tile, more destinations than a wave counts at a time."""
+    ops = [("create", 0, n_src)] + [("create", h, 2) for h in range(1, P)]
+    ops += [("connect", [(0, 0, n_src)], [(h, 0, 2)], _in(K), SYN, -1) for h in range(1, P)]
+    gnet, onet = _nets({"name": f"tiles P={P}", "P": P, "seed": 3, "dt": 0.1, "ops": ops}, 0)
+    rng = np.random.default_rng(P)
+    for n_spk in (1, 23, 63, 64, 65, 1023, 1024, 1025, 8193):
+        spikes = rng.integers(0, n_src, size=n_spk)
+        _check_packets(gnet, onet, 0, spikes, rng.integers(1, 5, size=n_spk) if n_spk % 2 else None)
+    gnet.close()
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 3000])
+def test_delivery_blocks(n):
+    """Entry counts around a block, rows of 0 to thousands of events, long runs of entries without events."""
+    calls = [([(1, 0, 2)], [(0, 0, 300)], _in(60), SYN, -1), ([(1, 2, 200)], [(0, 0, 300)], _in(1), SYN, -1)]
+    script = {"name": "blocks", "P": 2, "seed": 3, "dt": 0.1, "map_policy": (0, 2, 1.0),
+              "ops": [("create", 0, 300), ("create", 1, 400)] + [("connect",) + cl for cl in calls]}
+    gnet, onet = _nets(script, 0)
+    used = int(onet.array("r_off")[2] - onet.array("r_off")[1])
+    ptr, img = onet.array("row_ptr"), onet.array("l_val")
+    rows = np.array([int(ptr[i + 1] - ptr[i]) for i in np.asarray(img).astype(np.int64)])
+    empty = np.flatnonzero(rows == 0)
+    rng = np.random.default_rng(n)
+    for pos in (np.zeros(n, np.int64), rng.integers(0, used, size=n), rng.integers(2, used, size=n)):
+        _check_deliver(gnet, onet, 0, np.ones(n), pos, None)
+        if empty.size:
+            pos = pos.copy()
+            pos[1:-1] = empty[0]     # a first and a last row with events, none between
+            _check_deliver(gnet, onet, 0, np.ones(n), pos, rng.integers(1, 9, size=n))
+    gnet.close()
