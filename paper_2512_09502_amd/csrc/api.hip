@@ -484,7 +484,11 @@ static std::shared_ptr<const DelayTable> delay_table_for(Ctx& c, const snnc_dist
             t->guide[j] = (uint32_t)i;
         }
     }
-    if (c.delay_tables.size() >= 4096) c.delay_tables.clear();   // bound the cache
+    if (c.delay_tables.size() >= 4096) {   // bound the cache; a table still in use goes with the context
+        for (auto& kv : c.delay_tables)
+            if (kv.second.use_count() == 1) dfree(c, kv.second->dev);
+        c.delay_tables.clear();
+    }
     c.delay_tables.emplace(key, t);
     return t;
 }
@@ -596,11 +600,16 @@ static void fill_meta(const Call& cl, char* host) {
     }
 }
 
+SetRef set_ref(const HostSet& s, const SegD* d) {
+    return SetRef{d, (uint32_t)s.seg.size(), s.seg.empty() ? SegD{} : SegD{s.ord_begin[0], s.seg[0].host, s.seg[0].first}};
+}
+
 static void bind_meta(Call& cl, void* dev) {
     const size_t nS = std::max<size_t>(cl.S.seg.size(), 1), nT = std::max<size_t>(cl.T.seg.size(), 1);
     const bool tab = cl.dtab && !cl.dtab->tab.empty();
     const size_t nD = tab ? cl.dtab->tab.size() : 1;
     cl.meta = dev;
+    cl.has_meta = true;
     cl.meta_bytes = meta_size(cl);
     cl.dS = static_cast<SegD*>(dev);
     cl.dT = cl.dS + nS;
@@ -608,13 +617,49 @@ static void bind_meta(Call& cl, void* dev) {
     cl.dguide_dev = tab ? cl.dtab_dev + nD : nullptr;
 }
 
+// On the caller's stream calls of one distribution share its table (uploaded
+// by the first) and sets of one segment are inline, so an ordinary call
+// uploads nothing: an allocation and a copy were half of a small call's time.
+// The counting lane, whose work is not ordered with the caller's stream, has
+// copies of its own.
 void upload_meta(Ctx& c, Call& cl) {
-    const size_t bytes = meta_size(cl);
-    std::vector<char> host(bytes);
-    fill_meta(cl, host.data());
-    void* dev = dalloc(c, bytes);
-    upload(c, dev, host.data(), bytes);
-    bind_meta(cl, dev);
+    if (c.lane == 0) {
+        const DelayTable* t = cl.dtab && !cl.dtab->tab.empty() ? cl.dtab.get() : nullptr;
+        if (t && !t->dev) {
+            std::vector<uint32_t> both(t->tab);
+            both.insert(both.end(), t->guide.begin(), t->guide.end());
+            uint32_t* dev = dalloc_n<uint32_t>(c, both.size());
+            try {
+                upload(c, dev, both.data(), both.size() * sizeof(uint32_t));
+            } catch (...) {
+                dfree(c, dev);
+                throw;
+            }
+            t->dev = dev;
+        }
+        const size_t nS = cl.S.seg.size(), nT = cl.T.seg.size();
+        if (nS > 1 || nT > 1) {
+            std::vector<char> host(meta_size(cl));
+            fill_meta(cl, host.data());
+            const size_t bytes = (std::max<size_t>(nS, 1) + std::max<size_t>(nT, 1)) * sizeof(SegD);
+            void* dev = dalloc(c, bytes);
+            cl.meta = dev;
+            upload(c, dev, host.data(), bytes);
+            cl.dS = static_cast<SegD*>(dev);
+            cl.dT = cl.dS + std::max<size_t>(nS, 1);
+        }
+        cl.dtab_dev = t ? t->dev : nullptr;
+        cl.dguide_dev = t ? t->dev + t->tab.size() : nullptr;
+        cl.meta_bytes = meta_size(cl);   // the resident bytes count them with every call
+        cl.has_meta = true;
+    } else {
+        const size_t bytes = meta_size(cl);
+        std::vector<char> host(bytes);
+        fill_meta(cl, host.data());
+        void* dev = dalloc(c, bytes);
+        upload(c, dev, host.data(), bytes);
+        bind_meta(cl, dev);
+    }
     if (cl.rule == SNNC_ASSIGNED_NODES && cl.n) {
         cl.pairs = dalloc_n<uint32_t>(c, 2 * cl.n);
         upload(c, cl.pairs, cl.in_src_pos, cl.n * 4);
@@ -648,6 +693,7 @@ static void upload_meta_batch(Ctx& c, std::vector<Call*>& calls) {
 static void free_meta(Ctx& c, Call& cl) {
     if (!cl.meta_shared) dfree(c, cl.meta);
     cl.meta = nullptr;
+    cl.has_meta = false;
 }
 
 // ------------------------------------------------------------------ generation store in blocks
@@ -982,7 +1028,7 @@ static void connect_impl(Ctx& c, const snnc_nodeset* src, const snnc_nodeset* tg
             c.conn_started = true;
         }
         cl.gen_begin = c.n_gen;
-        cl.gen_count = cl.meta ? gen_local(c, cl) : 0;   // no tables: no local target
+        cl.gen_count = cl.has_meta ? gen_local(c, cl) : 0;   // no tables: no local target
         HIPCHK(hipGetLastError());
     } catch (...) {
         free_meta(c, cl);
@@ -1055,7 +1101,6 @@ static void submit_many_impl(Ctx& c, uint32_t n, const snnc_nodeset* src, const 
         free_meta(c, cl);
         dfree(c, cl.pairs);
         release_pre(c, cl);
-        cl.meta = nullptr;
         cl.pairs = nullptr;
     };
     auto fatal = [](const Error& e) {

@@ -74,14 +74,21 @@ __device__ __forceinline__ void normal_weights(const uint32_t (&w0)[N], const ui
 // Delay step from the threshold table: k_lo + #{k : w >= t_k}.  The guide
 // bounds the search to the thresholds inside w's 2^24-wide slice (usually
 // none or one).
-__device__ __forceinline__ uint16_t delay_step(const uint32_t* tab, const uint32_t* guide, uint32_t klo,
-                                               uint32_t w) {
-    uint32_t a = guide[w >> 24], b = guide[(w >> 24) + 1];
-    while (a < b) {
-        const uint32_t m = (a + b) >> 1;
-        if (tab[m] <= w) a = m + 1; else b = m;
+template <int N>
+__device__ __forceinline__ void delay_steps(const uint32_t* tab, const uint32_t* guide, uint32_t klo,
+                                            const uint32_t (&w)[N], uint16_t (&d)[N]) {
+    uint32_t a[N], b[N];
+    SNNC_UNROLL for (int i = 0; i < N; ++i) {
+        a[i] = guide[w[i] >> 24];
+        b[i] = guide[(w[i] >> 24) + 1];
     }
-    return (uint16_t)(klo + a);
+    SNNC_UNROLL for (int i = 0; i < N; ++i) {
+        while (a[i] < b[i]) {
+            const uint32_t m = (a[i] + b[i]) >> 1;
+            if (tab[m] <= w[i]) a[i] = m + 1; else b[i] = m;
+        }
+        d[i] = (uint16_t)(klo + a[i]);
+    }
 }
 
 // Weights and delays of N elements (in lockstep, see bm_math.h).
@@ -100,9 +107,8 @@ __device__ __forceinline__ void syn_values(const SynD& s, uint32_t seed, uint32_
             b1[i] = b.y;
             b2[i] = b.z;
         }
+        if (s.d_normal) delay_steps<N>(s.dtab, s.dguide, s.d_klo, b2, d);
         if (s.w_normal) normal_weights<N>(b0, b1, s.w_mean, s.w_sd, w);
-        if (s.d_normal)
-            SNNC_UNROLL for (int i = 0; i < N; ++i) d[i] = delay_step(s.dtab, s.dguide, s.d_klo, b2[i]);
     }
 }
 
@@ -117,14 +123,18 @@ __device__ __forceinline__ void syn_values(const SynD& s, uint32_t seed, uint32_
 }
 
 // Ordinal -> (host, local id) in a node set (segments sorted by ordinal).
-__device__ __forceinline__ void set_lookup(const SegD* seg, uint32_t nseg, uint64_t ord, uint32_t& host,
-                                           uint32_t& local) {
-    uint32_t a = 0, b = nseg;   // last segment with ord_begin <= ord
+__device__ __forceinline__ void set_lookup(const SetRef& set, uint64_t ord, uint32_t& host, uint32_t& local) {
+    if (set.n <= 1) {
+        host = set.one.host;
+        local = set.one.first + (uint32_t)ord;
+        return;
+    }
+    uint32_t a = 0, b = set.n;   // last segment with ord_begin <= ord
     while (b - a > 1) {
         const uint32_t m = (a + b) >> 1;
-        if (seg[m].ord_begin <= ord) a = m; else b = m;
+        if (set.d[m].ord_begin <= ord) a = m; else b = m;
     }
-    const SegD s = seg[a];
+    const SegD s = set.d[a];
     host = s.host;
     local = s.first + (uint32_t)(ord - s.ord_begin);
 }

@@ -88,14 +88,13 @@ struct IdSink {
 // Point-to-point regeneration: set the bit of every source that lives on
 // `host` (one bit row over that host's neurons).
 struct MarkSink {
-    const SegD* S;
-    uint32_t nS;
+    SetRef S;
     uint32_t host;
     uint32_t* bits;
     uint32_t words;   // words of the row: (neurons on `host` + 31) / 32
     __device__ __forceinline__ void mark(const Res& r) const {
         uint32_t h, l;
-        set_lookup(S, nS, r.src, h, l);
+        set_lookup(S, r.src, h, l);
         if (h != host) return;
         // most draws hit sources already marked: a plain read skips their atomics
         // (a stale read only costs a redundant atomic)
@@ -192,8 +191,7 @@ struct OutDegree {
     uint32_t K;
     FastDiv fk;
     uint32_t n_t;
-    const SegD* T;
-    uint32_t nT;
+    SetRef T;
     uint32_t host;
     uint32_t seed, call;
     __device__ __forceinline__ Run run(uint64_t g) const { return run_at(ch, g, K); }
@@ -207,7 +205,7 @@ struct OutDegree {
         uint32_t t = uniform_index(b.x, b.y, n_t - (skip ? 1u : 0u));
         if (skip && t >= (uint64_t)c.self_base + s_rel) ++t;
         uint32_t h, l;
-        set_lookup(T, nT, t, h, l);
+        set_lookup(T, t, h, l);
         if (h != host) return 0;
         r[0] = Res{(uint32_t)s_ord, l, e};
         return 1;
@@ -220,10 +218,8 @@ struct OutDegree {
 // repeats of an earlier valid pair when multapses are excluded (first[c] = 0).
 struct Total {
     static constexpr int R = 1;
-    const SegD* S;
-    uint32_t nS;
-    const SegD* T;
-    uint32_t nT;
+    SetRef S;
+    SetRef T;
     uint32_t n_s, n_t;
     uint32_t autapses;
     const uint8_t* first;   // null when multapses are allowed
@@ -235,11 +231,11 @@ struct Total {
         const uint32_t s = uniform_index(b.x, b.y, n_s);
         const uint32_t t = uniform_index(b.z, b.w, n_t);
         uint32_t th, tl;
-        set_lookup(T, nT, t, th, tl);
+        set_lookup(T, t, th, tl);
         if (th_out) *th_out = th;
         if (!autapses) {
             uint32_t sh, sl;
-            set_lookup(S, nS, s, sh, sl);
+            set_lookup(S, s, sh, sl);
             if (sh == th && sl == tl) return 0;
         }
         if (first && !first[cand]) return 0;
@@ -254,14 +250,13 @@ struct Assigned {
     static constexpr int R = 1;
     const uint32_t* src_pos;
     const uint32_t* tgt_pos;
-    const SegD* T;
-    uint32_t nT;
+    SetRef T;
     uint32_t host;
     __device__ __forceinline__ Run run(uint64_t) const { return Run{TChunk{}, ~0ull}; }
     __device__ __forceinline__ int eval_in(const TChunk&, uint64_t i, Res* r) const { return eval(i, r); }
     __device__ __forceinline__ int eval(uint64_t i, Res* r) const {
         uint32_t h, l;
-        set_lookup(T, nT, tgt_pos[i], h, l);
+        set_lookup(T, tgt_pos[i], h, l);
         if (h != host) return 0;
         r[0] = Res{src_pos[i], l, i};
         return 1;
@@ -603,7 +598,7 @@ __global__ __launch_bounds__(NT) void k_gen_mark_lds(Rule rule, MarkSink sink, u
         const int n = rule.eval(item, r);
         for (int k = 0; k < n; ++k) {
             uint32_t h, l;
-            set_lookup(sink.S, sink.nS, r[k].src, h, l);
+            set_lookup(sink.S, r[k].src, h, l);
             if (h == sink.host) atomicOr(&row[l >> 5], 1u << (l & 31));
         }
     }
@@ -816,8 +811,7 @@ struct FloydArgs {
     uint64_t n_units;
     uint32_t K, n_set;     // draws per unit, candidate set size
     uint32_t in_degree;
-    const SegD* T;         // out-degree: target set
-    uint32_t nT;
+    SetRef T;              // out-degree: target set
     uint32_t host;
     uint32_t kpad;         // power of two >= K
     uint32_t kshift;       // log2(kpad): step bits of a 32-bit sort key
@@ -1054,7 +1048,7 @@ __global__ __launch_bounds__(NT) void k_floyd(FloydArgs a, Sink sink, uint32_t* 
                     ok = true;
                 } else {
                     uint32_t h, l;
-                    set_lookup(a.T, a.nT, v, h, l);
+                    set_lookup(a.T, v, h, l);
                     r = Res{(uint32_t)ord, l, e0 + j};
                     ok = (h == a.host);
                 }
@@ -1129,7 +1123,7 @@ __device__ __forceinline__ void floyd_small_unit(const FloydArgs& a, uint64_t u,
             ok = true;
         } else {
             uint32_t h, l;
-            set_lookup(a.T, a.nT, v, h, l);
+            set_lookup(a.T, v, h, l);
             r = Res{(uint32_t)ord, l, e0 + j};
             ok = (h == a.host);
         }
@@ -1560,11 +1554,11 @@ enum class Out { APPEND, AT_BASE, COUNT, MARK };
 //            depends on the draws);
 //   MARK:    mark the sources on P_local (point-to-point regeneration).
 uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits) {
-    if (!cl.meta) upload_meta(c, cl);
+    if (!cl.has_meta) upload_meta(c, cl);
     const bool mark = mode == Out::MARK;
     WriteSink ws{};
     MarkSink ms{};
-    if (mark) ms = MarkSink{cl.dS, (uint32_t)cl.S.seg.size(), c.P_local, mark_bits, (c.M[c.P_local] + 31) / 32};
+    if (mark) ms = MarkSink{set_ref(cl.S, cl.dS), c.P_local, mark_bits, (c.M[c.P_local] + 31) / 32};
     // room for the n connections; returns the sink writing them
     auto reserve = [&](uint64_t n) -> WriteSink* {
         uint64_t base = c.n_gen;
@@ -1579,7 +1573,7 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
         return &ws;
     };
 
-    const uint32_t nS = (uint32_t)cl.S.seg.size(), nT = (uint32_t)cl.T.seg.size();
+    const SetRef rS = set_ref(cl.S, cl.dS), rT = set_ref(cl.T, cl.dT);
     const uint64_t ns = cl.S.total, nt = cl.T.total;
     uint64_t result = 0;
     std::vector<void*> temps;
@@ -1602,7 +1596,7 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
                 if (mark) launch_gen<InDegree, MarkSink, MARK>(c, "gen_indegree", r, ms, items, nullptr, nullptr, 0);
                 else launch_gen<InDegree, WriteSink, DIRECT>(c, "gen_indegree", r, *reserve(items), items, nullptr, nullptr, 0);
             } else {
-                FloydArgs a{dc.tab, items / K, (uint32_t)K, (uint32_t)ns, 1, cl.dT, nT, host,
+                FloydArgs a{dc.tab, items / K, (uint32_t)K, (uint32_t)ns, 1, rT, host,
                             next_pow2((uint32_t)K), log2_pow2(next_pow2((uint32_t)K)), c.seed, cl.id};
                 if (mark) launch_floyd<MarkSink, MARK>(c, a, ms, nullptr, nullptr);
                 else launch_floyd_direct(c, a, *reserve(items), items);
@@ -1627,7 +1621,7 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
             DeviceChunks dc = upload_chunks(c, runs, items);
             temps.push_back(dc.d);
             if (cl.multapses) {
-                OutDegree r{dc.tab, (uint32_t)K, make_fastdiv((uint32_t)K), (uint32_t)nt, cl.dT, nT, host,
+                OutDegree r{dc.tab, (uint32_t)K, make_fastdiv((uint32_t)K), (uint32_t)nt, rT, host,
                             c.seed, cl.id};
                 if (mark) {
                     launch_gen<OutDegree, MarkSink, MARK>(c, "gen_outdegree", r, ms, items, nullptr, nullptr, 0);
@@ -1639,7 +1633,7 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
                 }
             } else {
                 const uint64_t units = items / K;
-                FloydArgs a{dc.tab, units, (uint32_t)K, (uint32_t)nt, 0, cl.dT, nT, host,
+                FloydArgs a{dc.tab, units, (uint32_t)K, (uint32_t)nt, 0, rT, host,
                             next_pow2((uint32_t)K), log2_pow2(next_pow2((uint32_t)K)), c.seed, cl.id};
                 if (mark) {
                     launch_floyd<MarkSink, MARK>(c, a, ms, nullptr, nullptr);
@@ -1669,7 +1663,7 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
             if (!cl.n || !on_host) break;
             const bool all_local = on_host == nt;
             const uint64_t N = cl.n;
-            Total r{cl.dS, nS, cl.dT, nT, (uint32_t)ns, (uint32_t)nt, cl.autapses ? 1u : 0u, nullptr, c.seed, cl.id};
+            Total r{rS, rT, (uint32_t)ns, (uint32_t)nt, cl.autapses ? 1u : 0u, nullptr, c.seed, cl.id};
             if (cl.autapses && cl.multapses && all_local) {
                 result = N;
                 if (mark) launch_gen<Total, MarkSink, MARK>(c, "gen_total", r, ms, N, nullptr, nullptr, 0);
@@ -1978,7 +1972,7 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
             uint64_t on_host = 0;
             for (auto& g : cl.T.seg) if (g.host == host) on_host += g.n;
             if (!on_host && !mark) break;
-            Assigned r{cl.pairs, cl.pairs + n, cl.dT, nT, host};
+            Assigned r{cl.pairs, cl.pairs + n, rT, host};
             if (mark) {
                 launch_gen<Assigned, MarkSink, MARK>(c, "gen_assigned", r, ms, n, nullptr, nullptr, 0);
             } else if (on_host == nt) {      // every target here: every pair is kept
@@ -2165,7 +2159,7 @@ ChunkTab batch_tab(const std::vector<TChunk>& runs, std::vector<TChunk>& chunks,
 
 bool fused_desc(Ctx& c, Call& cl, FusedReq& q, std::vector<TChunk>& chunks, size_t* chunk_at) {
     const uint32_t host = c.P_local;
-    const uint32_t nS = (uint32_t)cl.S.seg.size(), nT = (uint32_t)cl.T.seg.size();
+    const SetRef rS = set_ref(cl.S, cl.dS), rT = set_ref(cl.T, cl.dT);
     const uint64_t ns = cl.S.total, nt = cl.T.total;
     memset(&q, 0, sizeof q);
     q.out_base = cl.gen_begin;
@@ -2191,7 +2185,7 @@ bool fused_desc(Ctx& c, Call& cl, FusedReq& q, std::vector<TChunk>& chunks, size
         auto runs = unit_runs(cl.S, cl.autapses ? nullptr : &cl.T, -1, K, MAX_RUN_ELEMS);
         q.kind = F_OUTDEGREE;
         q.outd = OutDegree{batch_tab(runs, chunks, chunk_at), (uint32_t)K, make_fastdiv((uint32_t)K), (uint32_t)nt,
-                           cl.dT, nT, host, c.seed, cl.id};
+                           rT, host, c.seed, cl.id};
         return true;
     }
     case SNNC_FIXED_TOTAL_NUMBER: {
@@ -2200,7 +2194,7 @@ bool fused_desc(Ctx& c, Call& cl, FusedReq& q, std::vector<TChunk>& chunks, size
         for (auto& g : cl.T.seg) if (g.host == host) on_host += g.n;
         if (on_host != nt) return false;   // targets on several hosts: candidates are filtered
         q.kind = F_TOTAL;
-        q.tot = Total{cl.dS, nS, cl.dT, nT, (uint32_t)ns, (uint32_t)nt, 1u, nullptr, c.seed, cl.id};
+        q.tot = Total{rS, rT, (uint32_t)ns, (uint32_t)nt, 1u, nullptr, c.seed, cl.id};
         return true;
     }
     case SNNC_ONE_TO_ONE: {

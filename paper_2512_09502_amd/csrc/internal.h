@@ -35,6 +35,14 @@ struct SegD {
     uint32_t host, first;
 };
 
+// A node set for kernels.  A set of one segment travels with the kernel's
+// arguments and has no device table.
+struct SetRef {
+    const SegD* d;   // device table of n > 1 segments
+    uint32_t n;
+    SegD one;        // the segment of n == 1
+};
+
 // A run of consecutive target ordinals that live on the generating host, for
 // the rules whose unit is a target.  Within a run the "self position" (the
 // ordinal of the same neuron in the source set, for autapse exclusion) is
@@ -74,6 +82,7 @@ struct HostSet {
 struct DelayTable {
     uint32_t klo = 0;
     std::vector<uint32_t> tab, guide;
+    mutable uint32_t* dev = nullptr;   // thresholds and guide in device memory, for calls on the caller's stream
 };
 
 struct Call {
@@ -90,7 +99,8 @@ struct Call {
     uint32_t d_klo = 0;
     std::shared_ptr<const DelayTable> dtab;   // normal delays only
     // device copies
-    void* meta = nullptr;       // one allocation: S segs, T segs, delay table
+    bool has_meta = false;      // what a run on this host needs is in place
+    void* meta = nullptr;       // one allocation: S segs, T segs, delay table (those not inline or shared)
     bool meta_shared = false;   // meta lies in a block shared by a batch of calls (released with the context)
     size_t meta_bytes = 0;
     SegD* dS = nullptr;
@@ -362,7 +372,8 @@ void release_pre(Ctx& c, Call& cl);
 // number of tile shapes of the image-numbering pass
 int number_variant_count();
 bool count_on_device(const Ctx& c, const Call& cl);
-// device copies of a call's sets and tables (cl.meta), once
+// device copies of a call's sets and tables, once
+SetRef set_ref(const HostSet& s, const SegD* d);
 void upload_meta(Ctx& c, Call& cl);
 // exact number of connections the call has on P_local's share (may launch a
 // counting pass)

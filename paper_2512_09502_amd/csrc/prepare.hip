@@ -32,8 +32,7 @@ constexpr int PNT = 256;
 
 struct CallD {
     uint64_t gen_begin;
-    const SegD* S;
-    uint32_t nS;
+    SetRef S;
     uint32_t a;      // alpha + 1
     uint32_t order;  // position of the call in call order
     uint32_t flag;   // 1: only the sources its local connections use get images
@@ -43,7 +42,7 @@ struct CallD {
 
 // segment lookup by division when every source segment of the call has the same length
 CallD make_calld(const Call& cl, uint32_t order, uint32_t flag) {
-    CallD d{cl.gen_begin, cl.dS, (uint32_t)cl.S.seg.size(), (uint32_t)(cl.alpha + 1), order, flag, 0, FastDiv{}};
+    CallD d{cl.gen_begin, set_ref(cl.S, cl.dS), (uint32_t)(cl.alpha + 1), order, flag, 0, FastDiv{}};
     const auto& seg = cl.S.seg;
     bool uniform = seg.size() > 1 && seg[0].n > 0 && cl.S.total < (1ull << 31);
     for (const auto& g : seg) uniform = uniform && g.n == seg[0].n;
@@ -98,18 +97,18 @@ struct SourceCursor {
                                        uint64_t& bit) {
         call_at(L, i);
         if (ord < seg_lo || ord >= seg_hi) {
-            uint32_t a = 0, b = call.nS;
+            uint32_t a = 0, b = call.S.n;
             if (call.uniform) {
                 a = fastdiv(ord, call.seg_div);
             } else {
                 while (b - a > 1) {
                     const uint32_t m = (a + b) >> 1;
-                    if (call.S[m].ord_begin <= ord) a = m; else b = m;
+                    if (call.S.d[m].ord_begin <= ord) a = m; else b = m;
                 }
             }
-            const SegD s = call.S[a];
+            const SegD s = call.S.n <= 1 ? call.S.one : call.S.d[a];
             seg_lo = s.ord_begin;
-            seg_hi = a + 1 < call.nS ? call.S[a + 1].ord_begin : ~0ull;
+            seg_hi = a + 1 < call.S.n ? call.S.d[a + 1].ord_begin : ~0ull;
             seg_host = s.host;
             seg_first = s.first;
             bit_base = (uint64_t)call.a * L.G + L.host_base[s.host] + s.first - s.ord_begin;
@@ -1151,7 +1150,7 @@ void prepare_all(Ctx& c) {
                 const uint64_t remote = M_local + a * G + host_base[g.host] + g.first;
                 seg_add.push_back((int64_t)(g.host == PL ? g.first : remote) - (int64_t)cl.S.ord_begin[j]);
             }
-            maps.push_back(SrcMap{seg_add[seg_at.back()], nullptr, cl.dS, d.uniform ? d.seg_div.m : 0, d.seg_div.shift, d.nS});
+            maps.push_back(SrcMap{seg_add[seg_at.back()], nullptr, cl.dS, d.uniform ? d.seg_div.m : 0, d.seg_div.shift, d.S.n});
             with_conns.push_back(k);
             call_begin.push_back(cl.gen_begin);
         }
@@ -1191,7 +1190,7 @@ void prepare_all(Ctx& c) {
             try {
                 HIPCHK(hipMemsetAsync(fc, 0xff, n_bits * 4, c.stream));
                 bool any_flagged = false;
-                for (auto& cd : calls) any_flagged |= (cd.flag && cd.nS > 0);
+                for (auto& cd : calls) any_flagged |= (cd.flag && cd.S.n > 0);
                 if (N && remote_net && any_flagged) {
                     CallD* d_calls = static_cast<CallD*>(tmp(calls.size() * sizeof(CallD)));
                     upload(c, d_calls, calls.data(), calls.size() * sizeof(CallD));

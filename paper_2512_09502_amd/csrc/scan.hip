@@ -70,38 +70,34 @@ __global__ __launch_bounds__(SNT) void k_scan(L load, uint64_t n, const uint64_t
     }
 }
 
-// One workgroup, chunks of ONE_TILE in order with the running total carried:
-// one launch and no scratch where the three of the general form (two of them
-// over a few blocks) cost more than the chunks' serial chain: 5,216 counts 7.4
-// us against 3 x 6 us and two gaps; 2 chunks, as a third would cost as much again.
-constexpr int ONE_NT = 1024;
-constexpr uint64_t ONE_TILE = ONE_NT * SIPT, ONE_MAX = 2 * ONE_TILE;
+// One workgroup: one launch and no scratch where the three of the general form
+// (two of them over a few blocks) cost more.  5,216 counts take 7.4 us, three
+// launches 6 us each with their gaps; beyond ONE_MAX the single compute unit's
+// loads and stores do (32,768 counts: 32 us).
+constexpr int ONE_NT = 1024, ONE_IPT = 8;
+constexpr uint64_t ONE_MAX = ONE_NT * ONE_IPT;
 
 template <class L>
 __global__ __launch_bounds__(ONE_NT) void k_scan_one(L load, uint64_t n, uint64_t* out, uint64_t* total_out) {
     __shared__ uint64_t scratch[ONE_NT / 64];
-    uint64_t carry = 0;
-    for (uint64_t base = 0; base < n; base += ONE_TILE) {
-        const uint64_t first = base + (uint64_t)threadIdx.x * SIPT;
-        uint64_t v[SIPT];
-        uint64_t sum = 0;
+    const uint64_t first = (uint64_t)threadIdx.x * ONE_IPT;
+    uint64_t v[ONE_IPT];
+    uint64_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < SIPT; ++k) {
-            v[k] = first + k < n ? load(first + k) : 0;
-            sum += v[k];
-        }
-        uint64_t tot;
-        uint64_t run = carry + block_excl_scan<ONE_NT, uint64_t>(sum, scratch, &tot);
+    for (int k = 0; k < ONE_IPT; ++k) {
+        v[k] = first + k < n ? load(first + k) : 0;
+        sum += v[k];
+    }
+    uint64_t total;
+    uint64_t run = block_excl_scan<ONE_NT, uint64_t>(sum, scratch, &total);
 #pragma unroll
-        for (int k = 0; k < SIPT; ++k) {
-            if (first + k < n) out[first + k] = run;
-            run += v[k];
-        }
-        carry += tot;
+    for (int k = 0; k < ONE_IPT; ++k) {
+        if (first + k < n) out[first + k] = run;
+        run += v[k];
     }
     if (threadIdx.x == 0) {
-        out[n] = carry;
-        if (total_out) *total_out = carry;
+        out[n] = total;
+        if (total_out) *total_out = total;
     }
 }
 
