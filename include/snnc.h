@@ -136,7 +136,8 @@ snnc_status snnc_init(snnc_ctx** out, uint32_t P, uint32_t P_local, uint32_t see
  * Buffers the caller's allocator gave go back to it.  The library's own
  * stream-ordered blocks are kept, up to 8 GiB per device, in a per-device
  * cache that later contexts on that device draw exact-size blocks from
- * (and pinned host staging buffers likewise); the rest return to the
+ * (pinned host staging buffers likewise, and up to 256 MiB of the pinned
+ * blocks that held result arrays); the rest return to the
  * library's memory pool, which keeps its memory until the process ends. */
 snnc_status snnc_destroy(snnc_ctx* ctx);
 

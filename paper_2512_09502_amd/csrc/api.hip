@@ -336,6 +336,67 @@ void pinned_give(void* p, size_t bytes, unsigned flags) {
     (void)hipHostFree(p);
 }
 
+// Pinned blocks of host-resident results (GPU memory levels 0 and 1) are kept
+// for the next context on the device, the oldest given back beyond
+// RESULT_PINNED_MAX: pinning and unpinning the nine arrays of a small share
+// took 0.5 ms a construction.
+namespace {
+constexpr size_t RESULT_PINNED_MAX = 256u << 20;
+
+struct ResultBlock {
+    void* p;
+    size_t bytes;
+    int device;
+};
+
+std::vector<ResultBlock>& result_blocks() {   // oldest first, under pinned_mutex
+    static std::vector<ResultBlock> v;
+    return v;
+}
+}  // namespace
+
+void* result_pinned_take(int device, size_t bytes, size_t* got) {
+    {
+        std::lock_guard<std::mutex> lock(pinned_mutex());
+        auto& v = result_blocks();
+        size_t best = v.size();
+        for (size_t k = 0; k < v.size(); ++k)   // the smallest that fits, no more than twice as large
+            if (v[k].device == device && v[k].bytes >= bytes && v[k].bytes / 2 <= bytes + (64u << 10) &&
+                (best == v.size() || v[k].bytes < v[best].bytes))
+                best = k;
+        if (best < v.size()) {
+            void* p = v[best].p;
+            *got = v[best].bytes;
+            v.erase(v.begin() + (long)best);
+            return p;
+        }
+    }
+    const size_t size = (bytes + (64u << 10) - 1) & ~(size_t)((64u << 10) - 1);
+    void* p = nullptr;
+    HIPCHK(hipHostMalloc(&p, size, hipHostMallocMapped));
+    *got = size;
+    return p;
+}
+
+// the caller's stream has drained
+void result_pinned_give(int device, void* p, size_t bytes) {
+    if (!p) return;
+    std::vector<void*> out;
+    {
+        std::lock_guard<std::mutex> lock(pinned_mutex());
+        auto& v = result_blocks();
+        v.push_back(ResultBlock{p, bytes, device});
+        size_t total = 0;
+        for (auto& b : v) total += b.bytes;
+        while (total > RESULT_PINNED_MAX) {
+            total -= v.front().bytes;
+            out.push_back(v.front().p);
+            v.erase(v.begin());
+        }
+    }
+    for (void* q : out) (void)hipHostFree(q);
+}
+
 void init_ring(StageRing& r, size_t bytes) {
     for (auto& e : r.ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     r.buf = static_cast<char*>(pinned_take(bytes, hipHostMallocDefault));
@@ -601,7 +662,9 @@ static void fill_meta(const Call& cl, char* host) {
 }
 
 SetRef set_ref(const HostSet& s, const SegD* d) {
-    return SetRef{d, (uint32_t)s.seg.size(), s.seg.empty() ? SegD{} : SegD{s.ord_begin[0], s.seg[0].host, s.seg[0].first}};
+    SetRef r{d, (uint32_t)s.seg.size(), {}};
+    for (size_t k = 0; k < s.seg.size() && k < SEG_INLINE; ++k) r.in[k] = SegD{s.ord_begin[k], s.seg[k].host, s.seg[k].first};
+    return r;
 }
 
 static void bind_meta(Call& cl, void* dev) {
@@ -618,7 +681,7 @@ static void bind_meta(Call& cl, void* dev) {
 }
 
 // On the caller's stream calls of one distribution share its table (uploaded
-// by the first) and sets of one segment are inline, so an ordinary call
+// by the first) and sets of few segments are inline, so an ordinary call
 // uploads nothing: an allocation and a copy were half of a small call's time.
 // The counting lane, whose work is not ordered with the caller's stream, has
 // copies of its own.
@@ -638,7 +701,7 @@ void upload_meta(Ctx& c, Call& cl) {
             t->dev = dev;
         }
         const size_t nS = cl.S.seg.size(), nT = cl.T.seg.size();
-        if (nS > 1 || nT > 1) {
+        if (nS > SEG_INLINE || nT > SEG_INLINE) {
             std::vector<char> host(meta_size(cl));
             fill_meta(cl, host.data());
             const size_t bytes = (std::max<size_t>(nS, 1) + std::max<size_t>(nT, 1)) * sizeof(SegD);
@@ -1309,6 +1372,11 @@ void flush_pending(Ctx& c) {
 static void free_results(Ctx& c) {
     for (auto& kv : c.arrays) free_array(c, kv.second);
     c.arrays.clear();
+    if (c.host_block) {
+        (void)hipStreamSynchronize(c.stream);   // no copy into it is left
+        result_pinned_give(c.device, c.host_block, c.host_block_bytes);
+        c.host_block = nullptr;
+    }
     c.counts.clear();
 }
 
@@ -1510,9 +1578,8 @@ snnc_status snnc_destroy(snnc_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->main_stream);
     if (c->count_stream) (void)hipStreamSynchronize(c->count_stream);
-    for (auto& kv : c->arrays)
-        if (kv.second.host) (void)hipHostFree(kv.second.p);
     c->arrays.clear();
+    result_pinned_give(c->device, c->host_block, c->host_block_bytes);
     gen_release(*c);
     std::vector<void*> ptrs;
     for (auto& kv : c->live) ptrs.push_back(kv.first);

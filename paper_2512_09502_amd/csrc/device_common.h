@@ -123,18 +123,25 @@ __device__ __forceinline__ void syn_values(const SynD& s, uint32_t seed, uint32_
 }
 
 // Ordinal -> (host, local id) in a node set (segments sorted by ordinal).
-__device__ __forceinline__ void set_lookup(const SetRef& set, uint64_t ord, uint32_t& host, uint32_t& local) {
-    if (set.n <= 1) {
-        host = set.one.host;
-        local = set.one.first + (uint32_t)ord;
-        return;
+__device__ __forceinline__ SegD segment_of(const SetRef& set, uint64_t ord) {
+    if (set.n <= SEG_INLINE) {
+        SegD s = set.in[0];
+        const bool second = set.n > 1 && set.in[1].ord_begin <= ord;   // field by field: selects
+        s.ord_begin = second ? set.in[1].ord_begin : s.ord_begin;
+        s.host = second ? set.in[1].host : s.host;
+        s.first = second ? set.in[1].first : s.first;
+        return s;
     }
     uint32_t a = 0, b = set.n;   // last segment with ord_begin <= ord
     while (b - a > 1) {
         const uint32_t m = (a + b) >> 1;
         if (set.d[m].ord_begin <= ord) a = m; else b = m;
     }
-    const SegD s = set.d[a];
+    return set.d[a];
+}
+
+__device__ __forceinline__ void set_lookup(const SetRef& set, uint64_t ord, uint32_t& host, uint32_t& local) {
+    const SegD s = segment_of(set, ord);
     host = s.host;
     local = s.first + (uint32_t)(ord - s.ord_begin);
 }

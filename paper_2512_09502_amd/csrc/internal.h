@@ -35,12 +35,15 @@ struct SegD {
     uint32_t host, first;
 };
 
-// A node set for kernels.  A set of one segment travels with the kernel's
-// arguments and has no device table.
+// A node set for kernels.  Up to SEG_INLINE segments (a population, or the
+// excitatory and the inhibitory one of an area) travel with the kernel's
+// arguments; such a set has no device table.
+constexpr uint32_t SEG_INLINE = 2;
+
 struct SetRef {
-    const SegD* d;   // device table of n > 1 segments
+    const SegD* d;   // device table of n > SEG_INLINE segments
     uint32_t n;
-    SegD one;        // the segment of n == 1
+    SegD in[SEG_INLINE];
 };
 
 // A run of consecutive target ordinals that live on the generating host, for
@@ -219,6 +222,8 @@ struct Ctx {
 
     // results of prepare
     std::map<int32_t, DevArray> arrays;    // by snnc_array_id
+    void* host_block = nullptr;            // the pinned block of the host-resident ones
+    size_t host_block_bytes = 0;
     std::map<int32_t, uint64_t> counts;
     uint64_t n_img = 0;
     uint32_t sort_passes = 0, key_bits = 0;
@@ -350,6 +355,10 @@ T* dalloc_n(Ctx& c, uint64_t n) {
 void tstart(Ctx& c, const char* name);
 void tstop(Ctx& c);
 void resolve_times(Ctx& c);
+
+// pinned host blocks of result arrays (mapped), kept for later contexts
+void* result_pinned_take(int device, size_t bytes, size_t* got);
+void result_pinned_give(int device, void* p, size_t bytes);
 
 // upload helpers: the host buffer may be reused as soon as upload returns
 // (small copies go through the pinned staging area without a stream sync)

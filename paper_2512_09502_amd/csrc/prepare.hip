@@ -97,8 +97,11 @@ struct SourceCursor {
                                        uint64_t& bit) {
         call_at(L, i);
         if (ord < seg_lo || ord >= seg_hi) {
+            const bool inl = call.S.n <= SEG_INLINE;
             uint32_t a = 0, b = call.S.n;
-            if (call.uniform) {
+            if (inl) {
+                a = b > 1 && call.S.in[1].ord_begin <= ord ? 1 : 0;
+            } else if (call.uniform) {
                 a = fastdiv(ord, call.seg_div);
             } else {
                 while (b - a > 1) {
@@ -106,9 +109,9 @@ struct SourceCursor {
                     if (call.S.d[m].ord_begin <= ord) a = m; else b = m;
                 }
             }
-            const SegD s = call.S.n <= 1 ? call.S.one : call.S.d[a];
+            const SegD s = !inl ? call.S.d[a] : a ? call.S.in[1] : call.S.in[0];
             seg_lo = s.ord_begin;
-            seg_hi = a + 1 < call.S.n ? call.S.d[a + 1].ord_begin : ~0ull;
+            seg_hi = a + 1 >= call.S.n ? ~0ull : inl ? call.S.in[1].ord_begin : call.S.d[a + 1].ord_begin;
             seg_host = s.host;
             seg_first = s.first;
             bit_base = (uint64_t)call.a * L.G + L.host_base[s.host] + s.first - s.ord_begin;
@@ -131,7 +134,7 @@ __device__ __forceinline__ void block_range(uint64_t n, uint64_t& lo, uint64_t& 
 struct SrcMap {
     int64_t add;             // the only segment's addend (nS == 1)
     const int64_t* seg_add;  // per segment
-    const SegD* S;
+    const uint64_t* seg_ord; // first ordinal per segment
     uint64_t div_m;          // equal segment lengths: segment = ordinal * div_m >> div_shift; else 0
     uint32_t div_shift;
     uint32_t nS;
@@ -199,7 +202,7 @@ __device__ __forceinline__ int64_t segment_add(const SrcMap& m, uint32_t ord) {
         uint32_t a = 0, b = m.nS;
         while (b - a > 1) {
             const uint32_t x = (a + b) >> 1;
-            if (m.S[x].ord_begin <= ord) a = x; else b = x;
+            if (m.seg_ord[x] <= ord) a = x; else b = x;
         }
         j = a;
     }
@@ -968,28 +971,38 @@ __global__ void k_img_rows(const uint64_t* row_ptr, uint32_t M_local, uint64_t n
     }
 }
 
-// Moves result arrays into pinned host memory that kernels can read: all the
+// Moves result arrays into pinned host memory that kernels can read: one
+// block for all (pinning costs 30 us a call and more with its pages), all the
 // copies, then one wait.
 void to_host(Ctx& c, std::initializer_list<int32_t> ids) {
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    size_t total = 0;
+    for (int32_t id : ids) {
+        auto it = c.arrays.find(id);
+        if (it != c.arrays.end()) total += up(std::max<size_t>(it->second.bytes, 1));
+    }
+    if (!total) return;
+    c.host_block = result_pinned_take(c.device, total, &c.host_block_bytes);
+    char* h = static_cast<char*>(c.host_block);
+    void* dev = nullptr;
+    if (hipHostGetDevicePointer(&dev, h, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        raise(SNNC_EDEVICE, "pinned host memory without a device address");
+    }
+    char* d = static_cast<char*>(dev);
     std::vector<void*> old;
     for (int32_t id : ids) {
         auto it = c.arrays.find(id);
-        if (it == c.arrays.end() || it->second.host) continue;
+        if (it == c.arrays.end()) continue;
         DevArray& a = it->second;
-        void* h = nullptr;
-        HIPCHK(hipHostMalloc(&h, std::max<size_t>(a.bytes, 1), hipHostMallocMapped));
-        void* d = nullptr;
-        if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipHostFree(h);
-            raise(SNNC_EDEVICE, "pinned host memory without a device address");
-        }
         old.push_back(a.p);
         const void* from = a.p;
         a.p = h;
         a.dev = d;
         a.host = true;
-        if (a.bytes) HIPCHK(hipMemcpyAsync(h, from, a.bytes, hipMemcpyDeviceToHost, c.stream));
+        h += up(std::max<size_t>(a.bytes, 1));
+        d += up(std::max<size_t>(a.bytes, 1));
+        if (a.bytes) HIPCHK(hipMemcpyAsync(a.p, from, a.bytes, hipMemcpyDeviceToHost, c.stream));
     }
     sync(c);
     for (void* p : old) dfree(c, p);
@@ -1137,6 +1150,7 @@ void prepare_all(Ctx& c) {
         std::vector<SrcMap> maps;
         std::vector<uint64_t> call_begin;
         std::vector<int64_t> seg_add;       // all calls' segment tables, concatenated
+        std::vector<uint64_t> seg_ord;
         std::vector<size_t> seg_at;
         for (uint32_t k = 0; k < n_calls; ++k) {
             const Call& cl = c.calls[k];
@@ -1149,8 +1163,9 @@ void prepare_all(Ctx& c) {
                 const snnc_segment& g = cl.S.seg[j];
                 const uint64_t remote = M_local + a * G + host_base[g.host] + g.first;
                 seg_add.push_back((int64_t)(g.host == PL ? g.first : remote) - (int64_t)cl.S.ord_begin[j]);
+                seg_ord.push_back(cl.S.ord_begin[j]);
             }
-            maps.push_back(SrcMap{seg_add[seg_at.back()], nullptr, cl.dS, d.uniform ? d.seg_div.m : 0, d.seg_div.shift, d.S.n});
+            maps.push_back(SrcMap{seg_add[seg_at.back()], nullptr, nullptr, d.uniform ? d.seg_div.m : 0, d.seg_div.shift, d.S.n});
             with_conns.push_back(k);
             call_begin.push_back(cl.gen_begin);
         }
@@ -1294,16 +1309,21 @@ void prepare_all(Ctx& c) {
             const size_t b_maps = up16(maps.size() * sizeof(SrcMap)), b_call = up16(call_begin.size() * 8);
             const size_t b_seg = up16(seg_add.size() * 8), b_iv = up16(iv.size() * sizeof(TInterval));
             const size_t b_ent = up16(ent.size() * sizeof(TEntry));
-            std::vector<char> tab(b_maps + b_call + b_seg + b_iv + b_ent);
+            std::vector<char> tab(b_maps + b_call + 2 * b_seg + b_iv + b_ent);
             char* d_tab = static_cast<char*>(tmp(tab.size()));
             const int64_t* d_seg = reinterpret_cast<const int64_t*>(d_tab + b_maps + b_call);
-            for (size_t k = 0; k < maps.size(); ++k) maps[k].seg_add = d_seg + seg_at[k];
+            const uint64_t* d_ord = reinterpret_cast<const uint64_t*>(d_tab + b_maps + b_call + b_seg);
+            for (size_t k = 0; k < maps.size(); ++k) {
+                maps[k].seg_add = d_seg + seg_at[k];
+                maps[k].seg_ord = d_ord + seg_at[k];
+            }
             memcpy(tab.data(), maps.data(), maps.size() * sizeof(SrcMap));
             memcpy(tab.data() + b_maps, call_begin.data(), call_begin.size() * 8);
             memcpy(tab.data() + b_maps + b_call, seg_add.data(), seg_add.size() * 8);
+            memcpy(tab.data() + b_maps + b_call + b_seg, seg_ord.data(), seg_ord.size() * 8);
             if (!iv.empty()) {
-                memcpy(tab.data() + b_maps + b_call + b_seg, iv.data(), iv.size() * sizeof(TInterval));
-                memcpy(tab.data() + b_maps + b_call + b_seg + b_iv, ent.data(), ent.size() * sizeof(TEntry));
+                memcpy(tab.data() + b_maps + b_call + 2 * b_seg, iv.data(), iv.size() * sizeof(TInterval));
+                memcpy(tab.data() + b_maps + b_call + 2 * b_seg + b_iv, ent.data(), ent.size() * sizeof(TEntry));
             }
             upload(c, d_tab, tab.data(), tab.size());
             GenSource gs{};
@@ -1316,8 +1336,8 @@ void prepare_all(Ctx& c) {
             gs.ncalls = (uint32_t)maps.size();
             if (by_source) {
                 gs.n_iv = (uint32_t)iv.size();
-                gs.iv = reinterpret_cast<const TInterval*>(d_tab + b_maps + b_call + b_seg);
-                gs.ent = reinterpret_cast<const TEntry*>(d_tab + b_maps + b_call + b_seg + b_iv);
+                gs.iv = reinterpret_cast<const TInterval*>(d_tab + b_maps + b_call + 2 * b_seg);
+                gs.ent = reinterpret_cast<const TEntry*>(d_tab + b_maps + b_call + 2 * b_seg + b_iv);
             }
             gs.bits = mapped ? bits : nullptr;
             gs.word_rank = mapped ? word_rank : nullptr;
@@ -1654,8 +1674,7 @@ void prepare_all(Ctx& c) {
 }
 
 void free_array(Ctx& c, DevArray& a) {
-    if (a.host) (void)hipHostFree(a.p);
-    else dfree(c, a.p);
+    if (!a.host) dfree(c, a.p);   // host arrays lie in the context's pinned block
     a = DevArray{};
 }
 

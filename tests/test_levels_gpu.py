@@ -81,3 +81,22 @@ def test_device_bytes_by_level():
         net.close()
     log(f"device bytes after prepare: level 1 {live[1]}, level 2 {live[2]}")
     assert live[1] < live[2]
+
+
+def test_host_blocks_of_several_networks():
+    """Networks alive together, then closed and built again in another order and size: each keeps its own arrays."""
+    import paper_2512_09502_amd as snnc
+    from gpu_util import LEVEL_ARRAYS, PREP_ARRAYS, compare
+    scripts = [_p2p(1), dict(W.balanced_collective(P=12, n_e=400, n_i=100, k_e=90, k_i=22), memory_level=0),
+               dict(W.multiarea_p2p(P=3, n_e=20, n_i=5, k_e=4, k_i=1, k_remote_max=4, seed=5), memory_level=1)]
+    refs = [oracle.run_script(s, 2) for s in scripts]
+    alive = {}
+    for step in (0, 1, 2, 0, 2, 1, 1, 0):
+        if step in alive:
+            alive.pop(step).close()
+        alive[step] = snnc.run_script(scripts[step], 2)
+        for k, net in alive.items():
+            for name in PREP_ARRAYS + ([n for n in LEVEL_ARRAYS if scripts[k]["memory_level"] <= 1]):
+                compare(name, net.array(name), refs[k].array(name), f"network {k}")
+    for net in alive.values():
+        net.close()
