@@ -102,6 +102,12 @@ __global__ __launch_bounds__(HSTRIDE) void k_hist_scan(const uint64_t* hist, uin
 // tiles to a die; over 2^22 pairs 34 us as here, 42 with tickets.
 constexpr uint32_t DIES = 8, CHUNK = 8;
 
+// Earlier tiles whose counts a look-back reads at once: a word costs a trip past
+// the L2 (the dies share no cache), and the walk is the longest part of a tile's
+// time.  2^28 pairs, eight and nine bits: one 1647 and 1872 us, four 1598 and
+// 1848, eight (more words than the walk needs) 1900 and 1934.
+constexpr int AHEAD = 4;
+
 __device__ __forceinline__ uint32_t pass_tile(uint32_t b, uint32_t grid) {
     const uint32_t first = b / (DIES * CHUNK) * (DIES * CHUNK), r = b - first;
     return first + DIES * CHUNK <= grid ? first + r % DIES * CHUNK + r / DIES : b;
@@ -121,7 +127,8 @@ __device__ __forceinline__ uint32_t pass_tile(uint32_t b, uint32_t grid) {
 // half the time the vector units rank (4 operations per digit bit and key),
 // the rest waits on memory at 24 B per pair.  2^28 pairs, 8-bit digit: 1787 us
 // (3.6 TB/s) before the ranking's three-operand bit operations, the dealing of
-// tiles and the keys loaded ahead of the payloads, 1668 us (3.9 TB/s) with them.
+// tiles, the keys loaded ahead of the payloads and the look-back four tiles at a
+// time, 1598 us (4.0 TB/s) with them.
 template <int NT, int IPT, bool FINAL, bool LB, int RB, bool SPLIT>
 __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                  uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, uint64_t n,
@@ -209,17 +216,26 @@ __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ ki
                 __hip_atomic_store(my, pack_status(FLAG_AGG, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 int64_t pred = (int64_t)tile - 1;
                 uint32_t spins = 0;
-                while (pred >= 0) {
-                    const uint64_t st = __hip_atomic_load(lookback + (uint64_t)pred * RB + d, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT);
-                    const uint64_t flag = st & (3ull << 62);
-                    const uint32_t ep = (uint32_t)((st >> 40) & EPOCH_MAX);
-                    if (flag != 0 && ep == epoch) {
-                        excl += st & VALUE_MASK;
-                        if (flag == FLAG_INC) break;
-                        --pred;
-                        continue;
+                bool found = false;
+                while (pred >= 0 && !found) {
+                    uint64_t st[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u)
+                        st[u] = __hip_atomic_load(lookback + (uint64_t)max(pred - u, (int64_t)0) * RB + d,
+                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int64_t from = pred;
+                    bool ready = true;
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        const uint64_t flag = st[u] & (3ull << 62);
+                        ready = ready && !found && pred >= 0 && flag != 0 && (uint32_t)((st[u] >> 40) & EPOCH_MAX) == epoch;
+                        if (ready) {
+                            excl += st[u] & VALUE_MASK;
+                            found = flag == FLAG_INC;
+                            --pred;
+                        }
                     }
+                    if (pred != from) continue;
                     if (spins++ >= spin_limit) {   // its keys are all there: every tile before the last is full
                         const uint64_t* pk = kin + (uint64_t)pred * TILE;
                         uint32_t c = 0;
