@@ -524,7 +524,9 @@ snnc_status snnc_set_map_policy(snnc_ctx* ctx, int32_t numbering, int32_t image_
 /* Tuning knobs of the context, by name.  "sort_variant": tile shape of the
  * radix-sort passes, 0 .. 13, as threads x keys per thread: 0 = 512x16 with
  * keys and payloads staged through LDS one after the other (70 KB, two
- * workgroups per compute unit; default), 1 = 256x8, 2 = 512x8, 3 = 512x16,
+ * workgroups per compute unit; the default, which below 1.5 x 2^20 pairs
+ * stands for 8 and from 2^27 pairs, or 2^25 with 9-bit digits, for 12 while
+ * neither this nor "sort_mode" was set), 1 = 256x8, 2 = 512x8, 3 = 512x16,
  * 4 = 256x16, 5 = 256x12, 6 = 1024x8, and staged in two phases like 0:
  * 7 = 1024x8, 8 = 512x8, 9 = 512x12, 10 = 256x16, 11 = 512x11, 12 = 1024x16,
  * 13 = 768x12.  SNNC_EINVAL for an unknown key or value. */

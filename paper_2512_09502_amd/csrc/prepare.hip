@@ -219,19 +219,17 @@ __device__ __forceinline__ uint64_t conn_key(const GenSource& g, int64_t add, ui
 }
 
 // the digits of one key per lane (valid lanes) into the workgroup's histograms; bits above the key's top are zero
-__device__ __forceinline__ void key_digits(uint32_t* h, uint64_t key, bool valid, uint32_t bit_lo, uint32_t n9,
-                                           uint32_t dbits, uint32_t passes) {
-    for (uint32_t p = 0; p < passes; ++p)
-        wave_hist_add(&h[p * HIST_STRIDE],
-                      (uint32_t)(key >> pass_shift(bit_lo, n9, dbits, p)) & (p < n9 ? 0x1ffu : (1u << dbits) - 1), valid);
+__device__ __forceinline__ void key_digits(uint32_t* h, uint64_t key, bool valid, uint32_t bit_lo, const Digits& dg) {
+    for (uint32_t p = 0; p < dg.passes; ++p)
+        wave_hist_add(&h[p * dg.stride], (uint32_t)(key >> dg.shift(bit_lo, p)) & ((1u << dg.width(p)) - 1), valid);
 }
 
 // Sort keys in generation order, with the digit histograms of all radix
 // passes: 10 B read and 8 B written per connection.
-__global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t bit_lo, uint32_t n9, uint32_t dbits,
-                                              uint32_t passes, uint64_t* keys, uint64_t* hist) {
-    __shared__ uint32_t h[8 * HIST_STRIDE];
-    for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT) h[i] = 0;
+__global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t bit_lo, Digits dg,
+                                              uint64_t* keys, uint64_t* hist) {
+    extern __shared__ uint32_t h[];   // a histogram a pass
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT) h[i] = 0;
     __syncthreads();
     uint64_t lo, hi;
     block_range(n, lo, hi);
@@ -268,10 +266,10 @@ __global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t 
         }
 #pragma unroll
         for (int u = 0; u < KU; ++u)
-            key_digits(h, key[u], base + (uint64_t)u * PNT + threadIdx.x < hi, bit_lo, n9, dbits, passes);
+            key_digits(h, key[u], base + (uint64_t)u * PNT + threadIdx.x < hi, bit_lo, dg);
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT)
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT)
         if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
 }
 
@@ -290,11 +288,11 @@ uint32_t tm_unit(uint64_t n) {
     return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n / 8192 / 64 * 64, 128), TM_UNIT);
 }
 
-__global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, uint32_t bit_lo, uint32_t n9,
-                                                     uint32_t dbits, uint32_t passes, uint32_t unit_size, uint64_t* keys,
-                                                     uint32_t* vals, uint64_t* hist) {
-    __shared__ uint32_t h[8 * HIST_STRIDE];
-    for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT) h[i] = 0;
+__global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, uint32_t bit_lo, Digits dg,
+                                                     uint32_t unit_size, uint64_t* keys, uint32_t* vals,
+                                                     uint64_t* hist) {
+    extern __shared__ uint32_t h[];   // a histogram a pass
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT) h[i] = 0;
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -344,7 +342,7 @@ __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, ui
                         keys[q + x] = key;
                         vals[q + x] = w[u];
                     }
-                    key_digits(h, key, x < len, bit_lo, n9, dbits, passes);
+                    key_digits(h, key, x < len, bit_lo, dg);
                 }
             }
             q += len;
@@ -362,7 +360,7 @@ __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, ui
         }
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < passes * HIST_STRIDE; i += PNT)
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT)
         if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
 }
 
@@ -1345,21 +1343,22 @@ void prepare_all(Ctx& c) {
             gs.M_local = M_local;
             gs.tgt_shift = 16 + tbits;
             const uint32_t bit_lo = by_source ? 16 + tbits : 16, bit_hi = 16 + sbits + tbits;
-            const SortPlan pl = plan_sort(c, N, bit_hi - bit_lo);   // the sort below takes the same plan
+            const Digits dg = plan_sort(c, N, bit_hi - bit_lo).d;   // the sort below takes the same plan
             uint64_t* keys0 = static_cast<uint64_t*>(tmp(N * 8));
             uint32_t* weights = reinterpret_cast<uint32_t*>(c.g_weight);
             uint32_t* moved = by_source ? static_cast<uint32_t*>(tmp(N * 4)) : nullptr;
-            uint64_t* hist = static_cast<uint64_t*>(tmp(8 * HIST_STRIDE * 8));
-            HIPCHK(hipMemsetAsync(hist, 0, 8 * HIST_STRIDE * 8, c.stream));
+            const size_t n_hist = (size_t)dg.passes * dg.stride;
+            uint64_t* hist = static_cast<uint64_t*>(tmp(std::max<size_t>(n_hist, 1) * 8));
+            HIPCHK(hipMemsetAsync(hist, 0, std::max<size_t>(n_hist, 1) * 8, c.stream));
             tstart(c, "prep_keys");
             const uint32_t unit = tm_unit(N);
             if (by_source)
                 hipLaunchKernelGGL(k_keys_tmajor,
-                                   dim3((unsigned)std::min<uint64_t>((N + unit * 4 - 1) / (unit * 4), 8192)), dim3(PNT), 0,
-                                   c.stream, gs, N, bit_lo, pl.n9, pl.dbits, pl.passes, unit, keys0, moved, hist);
+                                   dim3((unsigned)std::min<uint64_t>((N + unit * 4 - 1) / (unit * 4), 8192)), dim3(PNT),
+                                   n_hist * 4, c.stream, gs, N, bit_lo, dg, unit, keys0, moved, hist);
             else
-                hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), 0, c.stream, gs, N, bit_lo, pl.n9, pl.dbits,
-                                   pl.passes, keys0, hist);
+                hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), n_hist * 4, c.stream, gs, N, bit_lo, dg, keys0,
+                                   hist);
             tstop(c);
             HIPCHK(hipGetLastError());
             // the source ordinals, targets and delays now live in the keys (released in stream order)

@@ -20,7 +20,7 @@ namespace snnc {
 namespace {
 
 constexpr int RADIX = 256;          // buckets of an 8-bit digit
-constexpr int HSTRIDE = HIST_STRIDE; // histogram entries per pass (up to 9-bit digits)
+constexpr int MAX_STRIDE = 512;     // buckets of the widest digit
 
 // look-back status word: [63:62] flag, [61:40] epoch, [39:0] count
 constexpr uint64_t FLAG_AGG = 1ull << 62;
@@ -56,9 +56,9 @@ namespace {
 constexpr int HNT = 256;
 
 __global__ __launch_bounds__(HNT) void k_hist(const uint64_t* keys, uint64_t n, uint32_t bit_lo, uint32_t bit_hi,
-                                              uint32_t n9, uint32_t dbits, uint32_t passes, uint64_t* hist) {
-    __shared__ uint32_t h[8 * HSTRIDE];
-    for (uint32_t i = threadIdx.x; i < passes * HSTRIDE; i += HNT) h[i] = 0;
+                                              Digits dg, uint64_t* hist) {
+    extern __shared__ uint32_t h[];   // a histogram a pass
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += HNT) h[i] = 0;
     __syncthreads();
     constexpr int HU = 4;   // independent keys per thread per step: their loads overlap
     for (uint64_t base = (uint64_t)blockIdx.x * HNT * HU; base < n; base += (uint64_t)gridDim.x * HNT * HU) {
@@ -71,41 +71,40 @@ __global__ __launch_bounds__(HNT) void k_hist(const uint64_t* keys, uint64_t n, 
 #pragma unroll
         for (int u = 0; u < HU; ++u) {
             const bool valid = base + (uint64_t)u * HNT + threadIdx.x < n;
-            for (uint32_t p = 0; p < passes; ++p) {
-                const uint32_t mask = (1u << pass_bits(bit_lo, bit_hi, n9, dbits, p)) - 1;
-                wave_hist_add(&h[p * HSTRIDE], (uint32_t)((k[u] >> pass_shift(bit_lo, n9, dbits, p)) & mask), valid);
+            for (uint32_t p = 0; p < dg.passes; ++p) {
+                const uint32_t s = dg.shift(bit_lo, p);
+                const uint32_t mask = (1u << min(bit_hi - s, dg.width(p))) - 1;
+                wave_hist_add(&h[p * dg.stride], (uint32_t)((k[u] >> s) & mask), valid);
             }
         }
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < passes * HSTRIDE; i += HNT)
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += HNT)
         if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
 }
 
 // exclusive scan over the buckets of each pass (one workgroup per pass)
-__global__ __launch_bounds__(HSTRIDE) void k_hist_scan(const uint64_t* hist, uint64_t* off) {
-    __shared__ uint64_t scratch[HSTRIDE / 64];
-    const uint64_t v = hist[blockIdx.x * HSTRIDE + threadIdx.x];
+template <int STRIDE>
+__global__ __launch_bounds__(STRIDE) void k_hist_scan(const uint64_t* hist, uint64_t* off) {
+    __shared__ uint64_t scratch[STRIDE / 64];
+    const uint64_t v = hist[blockIdx.x * STRIDE + threadIdx.x];
     uint64_t tot;
-    const uint64_t ex = block_excl_scan<HSTRIDE, uint64_t>(v, scratch, &tot);
-    off[blockIdx.x * HSTRIDE + threadIdx.x] = ex;
+    const uint64_t ex = block_excl_scan<STRIDE, uint64_t>(v, scratch, &tot);
+    off[blockIdx.x * STRIDE + threadIdx.x] = ex;
 }
 
 // The tile of onesweep workgroup b of `grid`.  Workgroups go to the eight dies
-// (each with its own L2) in turn by index; the tiles of every 64 are dealt so
-// that a die gets CHUNK = 8 consecutive ones: their runs of equal digits meet
+// (each with its own L2) in turn by index; the tiles of every 128 are dealt so
+// that a die gets CHUNK = 16 consecutive ones: their runs of equal digits meet
 // inside cache lines, and the die's L2 merges both sides of such a line before
 // it is written.  The tile is known without a ticket from an atomic counter,
 // whose round trip would come before every tile's loads.  Passes over 2^28
-// pairs, eight and nine bits: 2030 and 2221 us with tile = index, 1691 and 1909
-// with tickets and the dealing, 1684 and 1915 as here, 1707 and 1940 with 16
-// tiles to a die; over 2^22 pairs 34 us as here, 42 with tickets.
-constexpr uint32_t DIES = 8, CHUNK = 8;
+// pairs, eight and nine bits: 1346 and 1493 us with 8 tiles to a die, 1334 and
+// 1470 with 16, 1493 and 1622 with 32 (tile = index cost a fifth more than 8).
+constexpr uint32_t DIES = 8, CHUNK = 16;
 
 // Earlier tiles whose counts a look-back reads at once: a word costs a trip past
-// the L2 (the dies share no cache), and the walk is the longest part of a tile's
-// time.  2^28 pairs, eight and nine bits: one 1647 and 1872 us, four 1598 and
-// 1848, eight (more words than the walk needs) 1900 and 1934.
+// the L2 (the dies share no cache).  2^28 pairs: two 1358 us, four 1346, six 1349.
 constexpr int AHEAD = 4;
 
 __device__ __forceinline__ uint32_t pass_tile(uint32_t b, uint32_t grid) {
@@ -122,13 +121,13 @@ __device__ __forceinline__ uint32_t pass_tile(uint32_t b, uint32_t grid) {
 // RB: buckets of the digit (256, or 512 for 9-bit digits).  SPLIT: stage the
 // keys, then the payloads, through one LDS buffer of 8 B per pair that also
 // holds the per-wave digit counts while the tile is ranked: about 67 KB for an
-// 8192-pair tile, so two workgroups share a compute unit and one's ranking and
-// look-back overlap the other's memory traffic.  Bound by that overlap: about
-// half the time the vector units rank (4 operations per digit bit and key),
-// the rest waits on memory at 24 B per pair.  2^28 pairs, 8-bit digit: 1787 us
-// (3.6 TB/s) before the ranking's three-operand bit operations, the dealing of
-// tiles, the keys loaded ahead of the payloads and the look-back four tiles at a
-// time, 1598 us (4.0 TB/s) with them.
+// 8192-pair tile (two workgroups a compute unit), 133 KB for 16384 pairs.
+// A tile's count is published as soon as it is known and looked back for only
+// when the tile stands staged in LDS: by then the earlier tiles have mostly
+// published theirs.  Waiting for them before the staging took 40% of a tile's
+// time; 2^28 pairs, 8-bit digit, 8192-pair tiles: 1594 us so, 1401 as here
+// (16384-pair tiles 1501 and 1334 us: 4.8 TB/s at 24 B per pair, the rate of a
+// large copy).
 template <int NT, int IPT, bool FINAL, bool LB, int RB, bool SPLIT>
 __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                  uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, uint64_t n,
@@ -195,25 +194,48 @@ __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ ki
         }
         __syncthreads();
 
-        // per digit: tile count, per-wave offsets, look-back over earlier tiles
+        // per digit: the tile's count, published before anything else, and the slots of its first key and
+        // of each wave's first one
         const uint32_t d = threadIdx.x;
         const bool digit_thread = d < RB;
+        uint64_t* const my = lookback + tile * RB + d;
         uint32_t cnt = 0;
-        uint32_t woff[WAVES];
-        uint64_t excl = 0;
         if (digit_thread) {
+            uint32_t woff[WAVES];
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) woff[w] = wave_hist[w][d];
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) {
-                woff[w] = cnt;
-                cnt += wave_hist[w][d];
+                wave_hist[w][d] = cnt;
+                cnt += woff[w];
             }
-            uint64_t* my = lookback + tile * RB + d;
-            if (!LB) {
-                // offsets known from the reduce-then-scan counts
-            } else if (tile == 0) {
-                __hip_atomic_store(my, pack_status(FLAG_INC, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                __hip_atomic_store(my, pack_status(FLAG_AGG, epoch, cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (LB)
+                __hip_atomic_store(my, pack_status(tile ? FLAG_AGG : FLAG_INC, epoch, cnt), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        uint32_t tot;
+        const uint32_t start = block_excl_scan<NT, uint32_t>(cnt, reinterpret_cast<uint32_t*>(scan_scratch), &tot);
+        if (digit_thread) out_base[d] = start;
+        __syncthreads();
+        const uint32_t tile_n = (uint32_t)min((uint64_t)TILE, n - base);
+        // slots (with SPLIT the counts share the staging buffer: all slots first)
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            const uint32_t dk = (uint32_t)(key[k] >> shift) & mask;
+            rank[k] += wave_hist[wave][dk] + (uint32_t)out_base[dk];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < IPT; ++k)
+            if (full || wbase + (uint64_t)k * 64 < n) {
+                stage_k[rank[k]] = key[k];
+                if constexpr (!SPLIT) stage_v[rank[k]] = val[k];
+            }
+
+        // per digit: look-back over earlier tiles, which had the time of the staging to publish theirs
+        if (digit_thread) {
+            uint64_t excl = 0;
+            if (LB && tile) {
                 int64_t pred = (int64_t)tile - 1;
                 uint32_t spins = 0;
                 bool found = false;
@@ -250,28 +272,9 @@ __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ ki
                 __hip_atomic_store(my, pack_status(FLAG_INC, epoch, excl + cnt), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
-        }
-        // digit start within the tile (exclusive scan over digits)
-        uint32_t tot;
-        const uint32_t start = block_excl_scan<NT, uint32_t>(cnt, reinterpret_cast<uint32_t*>(scan_scratch), &tot);
-        if (digit_thread) {
+            // (LB false: offsets known from the reduce-then-scan counts)
             out_base[d] = (LB ? digit_off[d] + excl : digit_off[(uint64_t)d * ((n + TILE - 1) / TILE) + tile]) - start;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) wave_hist[w][d] = start + woff[w];
         }
-        __syncthreads();
-
-        const uint32_t tile_n = (uint32_t)min((uint64_t)TILE, n - base);
-        // slots (with SPLIT the counts share the staging buffer: all slots first)
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) rank[k] += wave_hist[wave][(uint32_t)(key[k] >> shift) & mask];
-        if constexpr (SPLIT) __syncthreads();
-#pragma unroll
-        for (int k = 0; k < IPT; ++k)
-            if (full || wbase + (uint64_t)k * 64 < n) {
-                stage_k[rank[k]] = key[k];
-                if constexpr (!SPLIT) stage_v[rank[k]] = val[k];
-            }
         __syncthreads();
         // every thread writes slots tid, tid + NT, ...: equal digits go to consecutive positions
         uint32_t dd[IPT];   // digits of the thread's slots, kept for the payloads
@@ -407,10 +410,8 @@ struct Variant {
     int nt, ipt;
     bool split;   // keys and payloads staged through LDS one after the other
 };
-// tile shapes available to the tuner; index 0 is the default, the fastest
-// measured for sorts of 4e8 .. 2e9 pairs: 8192-pair tiles (digit runs long
-// enough for whole-line writes) staged in two phases, so that two workgroups
-// share each compute unit
+// tile shapes available to the tuner; unless one is set, plan_sort takes 8, 0 or
+// 12 by the number of pairs: 4096-, 8192- and 16384-pair tiles staged in two phases
 constexpr Variant VARIANTS[] = {{512, 16, true},  {256, 8, false},  {512, 8, false}, {512, 16, false},
                                 {256, 16, false}, {256, 12, false}, {1024, 8, false}, {1024, 8, true},
                                 {512, 8, true},   {512, 12, true},  {256, 16, true},  {512, 11, true},
@@ -495,16 +496,23 @@ void next_epoch(Ctx& c) {
 int sort_variant_count() { return N_VARIANTS; }
 
 // Pass algorithm, tile shape and digit plan of a sort of n keys over `bits`
-// bits.  9-bit digits (512 buckets) are taken when the tile has at least 512
-// threads and they save a pass over 8-bit digits (or when forced).
-SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits) {
+// bits: as few passes as the tile shape's digits allow, of equal or nearly equal
+// width (a pass costs more the wider its digit).  9-bit digits (512 buckets)
+// need a tile of at least 512 threads; 10-bit ones were not worth it (passes over
+// 2^28 pairs with the largest tile: 8 bits 1501, 9 bits 1642, 10 bits 2070 us).
+// The scratch of fixed size (`fixed`) keeps to the tiles its limits are stated for.
+SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits, bool fixed) {
     SortPlan p;
     p.variant = (c.sort_variant >= 0 && c.sort_variant < N_VARIANTS) ? c.sort_variant : 0;
     p.mode = c.sort_mode;
     if (!c.sort_pinned) {
         // few tiles: half-size ones, whose ranking is half as long a chain (passes over 1e5, 3e5, 1e6
-        // pairs: 12.7, 15.6, 23.6 us against 15.1, 17.7, 23.5 with the full size)
-        if (p.variant == 0 && n < (1u << 19)) p.variant = 8;
+        // pairs: 12.5, 14.5, 20.7 us against 14.6, 16.8, 21.9 with the full size; 3e6 pairs 29.3 against 27.4)
+        if (p.variant == 0 && n < (1u << 20) + (1u << 19)) p.variant = 8;
+        // many: double-size ones, whose runs fill whole lines (8 bits, 2^26, 2^27, 2^28 pairs: 339, 674,
+        // 1334 us against 335, 678, 1363; 9 bits, 2^23, 2^25, 2^28: 60, 197, 1470 against 55, 213, 1716)
+        const bool nine = (bits + 8) / 9 < (bits + 7) / 8;
+        if (p.variant == 0 && n >= (nine ? 1ull << 25 : 1ull << 27) && !fixed) p.variant = 12;
         auto it = tune_cache().find(TuneKey{log2_floor(std::max<uint64_t>(n, 1)), bits});
         if (it != tune_cache().end()) {
             p.mode = it->second.first;
@@ -513,19 +521,16 @@ SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits) {
     }
     const uint32_t p8 = (bits + 7) / 8, p9 = (bits + 8) / 9;
     const bool can9 = VARIANTS[p.variant].nt >= 512;
-    const bool use9 = can9 && (c.digit_bits == 9 || (c.digit_bits == 0 && p9 < p8));
-    p.passes = use9 ? p9 : p8;
-    if (use9 && c.digit_bits == 9) {          // forced: every pass 9 bits
-        p.n9 = p.passes;
-        p.dbits = 9;
-    } else if (use9) {                         // as few 9-bit passes as the pass count allows
-        p.n9 = bits - 8 * p.passes;           // (a 9-bit pass costs more than an 8-bit one)
-        p.dbits = 8;
+    Digits& d = p.d;
+    if (can9 && c.digit_bits == 9) {          // forced: every pass 9 bits
+        d.passes = p9;
+        d.dbits = 9;
     } else {
-        p.n9 = 0;
-        p.dbits = p.passes ? (bits + p.passes - 1) / p.passes : 0;
+        d.passes = c.digit_bits != 8 && can9 ? p9 : p8;
+        d.dbits = d.passes ? bits / d.passes : 0;
+        d.n_long = d.passes ? bits % d.passes : 0;
     }
-    p.wide = p.n9 > 0;
+    d.stride = std::max<uint32_t>(256, 1u << (d.dbits + (d.n_long ? 1 : 0)));
     return p;
 }
 
@@ -545,13 +550,12 @@ uint32_t hist_grid(uint64_t n) {
     return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((n + per - 1) / per, 8192));
 }
 
-void launch_hist(Ctx& c, const uint64_t* keys, uint64_t n, uint32_t bit_lo, uint32_t bit_hi, uint32_t n9,
-                 uint32_t dbits, uint32_t passes, uint64_t* hist) {
-    HIPCHK(hipMemsetAsync(hist, 0, (size_t)passes * HSTRIDE * 8, c.stream));
-    if (!n || !passes) return;
+void launch_hist(Ctx& c, const uint64_t* keys, uint64_t n, uint32_t bit_lo, uint32_t bit_hi,
+                 const Digits& dg, uint64_t* hist) {
+    HIPCHK(hipMemsetAsync(hist, 0, (size_t)dg.passes * dg.stride * 8, c.stream));
     const uint32_t grid = hist_grid(n);
     tstart(c, sort_timer(c, "hist").c_str());
-    hipLaunchKernelGGL(k_hist, dim3(grid), dim3(HNT), 0, c.stream, keys, n, bit_lo, bit_hi, n9, dbits, passes, hist);
+    hipLaunchKernelGGL(k_hist, dim3(grid), dim3(HNT), dg.passes * dg.stride * 4, c.stream, keys, n, bit_lo, bit_hi, dg, hist);
     tstop(c);
     HIPCHK(hipGetLastError());
 }
@@ -573,12 +577,12 @@ void fill_words(Ctx& c, uint64_t* p, uint64_t n) {
 
 // passes whose digit differs between keys (the others leave the order unchanged);
 // hh: their digit histograms, or null when they were not read back
-uint32_t live_passes(const uint64_t* hh, uint32_t passes, uint64_t n, uint32_t* live) {
+uint32_t live_passes(const uint64_t* hh, const Digits& dg, uint64_t n, uint32_t* live) {
     uint32_t n_live = 0;
-    for (uint32_t p = 0; p < passes; ++p) {
+    for (uint32_t p = 0; p < dg.passes; ++p) {
         bool trivial = false;
-        for (int b = 0; hh && b < HSTRIDE; ++b)
-            if (hh[(size_t)p * HSTRIDE + b] == n) trivial = true;
+        for (uint32_t b = 0; hh && b < dg.stride; ++b)
+            if (hh[(size_t)p * dg.stride + b] == n) trivial = true;
         if (!trivial) live[n_live++] = p;
     }
     return n_live;
@@ -598,11 +602,12 @@ struct FixedScratch {
 int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, uint32_t* vals1, uint64_t n,
                     uint32_t bit_lo, uint32_t bit_hi, const uint64_t* digit_hist, const FinalOutFn& final_out,
                     bool wait_for_plan, const FixedScratch* fs) {
-    const SortPlan plan = plan_sort(c, n, bit_hi > bit_lo ? bit_hi - bit_lo : 0);
-    const uint32_t passes = plan.passes, dbits = plan.dbits;
+    const SortPlan plan = plan_sort(c, n, bit_hi > bit_lo ? bit_hi - bit_lo : 0, fs != nullptr);
+    const Digits& dg = plan.d;
+    const uint32_t passes = dg.passes;
     // the reduce-then-scan passes allocate per-tile counts: fixed scratch takes onesweep passes
     const int variant = plan.variant, mode = fs ? 0 : plan.mode;
-    const uint32_t rb = plan.wide ? 512 : RADIX;
+    const uint32_t rb = dg.stride;
     if (passes > 8) raise(SNNC_EUNSUPPORTED, "radix sort over more than 64 bits");
     const uint64_t tile = (uint64_t)VARIANTS[variant].nt * VARIANTS[variant].ipt;
     const uint64_t tiles = (n + tile - 1) / tile;
@@ -619,40 +624,43 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
     const size_t lookback_bytes = fs ? fs->lookback_bytes : 0;
     int cur = 0;
     try {
-        uint64_t hh[8 * HSTRIDE];
+        uint64_t hh[8 * MAX_STRIDE];
         uint64_t* off = nullptr;
         if (passes && n) {
             uint64_t* hist = const_cast<uint64_t*>(digit_hist);
             if (!hist && fs) {
                 hist = fs->hist;
-                fill_words(c, hist, (uint64_t)passes * HSTRIDE);
+                fill_words(c, hist, (uint64_t)passes * dg.stride);
                 const uint32_t grid = hist_grid(n);
-                hipLaunchKernelGGL(k_hist, dim3(grid), dim3(HNT), 0, c.stream, keys0, n, bit_lo, bit_hi, plan.n9, dbits,
-                                   passes, hist);
+                hipLaunchKernelGGL(k_hist, dim3(grid), dim3(HNT), passes * dg.stride * 4, c.stream, keys0, n, bit_lo,
+                                   bit_hi, dg, hist);
                 HIPCHK(hipGetLastError());
             } else if (!hist) {
-                hist = dalloc_n<uint64_t>(c, (uint64_t)passes * HSTRIDE);
+                hist = dalloc_n<uint64_t>(c, (uint64_t)passes * dg.stride);
                 temps[0] = hist;
-                launch_hist(c, keys0, n, bit_lo, bit_hi, plan.n9, dbits, passes, hist);
+                launch_hist(c, keys0, n, bit_lo, bit_hi, dg, hist);
             }
             if (fs) {
                 off = fs->off;
             } else {
-                off = dalloc_n<uint64_t>(c, (uint64_t)passes * HSTRIDE);
+                off = dalloc_n<uint64_t>(c, (uint64_t)passes * dg.stride);
                 temps[1] = off;
             }
             tstart(c, sort_timer(c, "hist_scan").c_str());
-            hipLaunchKernelGGL(k_hist_scan, dim3(passes), dim3(HSTRIDE), 0, c.stream, hist, off);
+            if (dg.stride == 512)
+                hipLaunchKernelGGL(k_hist_scan<512>, dim3(passes), dim3(512), 0, c.stream, hist, off);
+            else
+                hipLaunchKernelGGL(k_hist_scan<256>, dim3(passes), dim3(256), 0, c.stream, hist, off);
             tstop(c);
             HIPCHK(hipGetLastError());
-            if (wait_for_plan) download(c, hh, hist, (size_t)passes * HSTRIDE * 8);
+            if (wait_for_plan) download(c, hh, hist, (size_t)passes * dg.stride * 8);
             if (!fs) {
                 ensure_lookback(c, (size_t)tiles * rb * 8);
                 lookback = c.lookback;
             }
         }
         uint32_t live[8];
-        const uint32_t n_live = live_passes(wait_for_plan && passes && n ? hh : nullptr, passes, n, live);
+        const uint32_t n_live = live_passes(wait_for_plan && passes && n ? hh : nullptr, dg, n, live);
         c.sort_passes = n_live;
         uint64_t* kb[2] = {keys0, keys1};
         uint32_t* vb[2] = {vals0, vals1};
@@ -665,9 +673,9 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
                 epoch = 1;
             }
             const bool last = (li + 1 == n_live) && final_out;
-            const uint32_t width = pass_bits(bit_lo, bit_hi, plan.n9, dbits, p);
-            PassArgs a{kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], n, pass_shift(bit_lo, plan.n9, dbits, p), width,
-                       off + (size_t)p * HSTRIDE, (uint64_t*)lookback, epoch, c.lookback_spins,
+            const uint32_t shift = dg.shift(bit_lo, p), width = std::min(bit_hi - shift, dg.width(p));
+            PassArgs a{kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], n, shift, width,
+                       off + (size_t)p * dg.stride, (uint64_t*)lookback, epoch, c.lookback_spins,
                        last ? final_out(cur) : FinalOut{}, mode};
             tstart(c, sort_timer(c, last ? "pass_final" : "pass").c_str());
             launch_variant(c, variant, a, last, width > 8);
@@ -839,8 +847,8 @@ namespace {
 
 constexpr size_t NA_BYTES = 16u << 20;
 constexpr size_t NA_HIST = 0;
-constexpr size_t NA_OFF = NA_HIST + 8 * HSTRIDE * 8;
-constexpr size_t NA_LB = NA_OFF + 8 * HSTRIDE * 8 + 256;   // (256 B spare)
+constexpr size_t NA_OFF = NA_HIST + 8 * MAX_STRIDE * 8;
+constexpr size_t NA_LB = NA_OFF + 8 * MAX_STRIDE * 8 + 256;   // (256 B spare)
 constexpr size_t NA_LB_BYTES = NA_BYTES - NA_LB;
 constexpr int NA_MAX_DEVICES = 64;
 

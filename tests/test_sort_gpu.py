@@ -71,3 +71,22 @@ def test_digit_width(net, digit_bits, variant, n, lo, hi):
     np.testing.assert_array_equal(v.cpu().numpy(), order.astype(np.int32))
     np.testing.assert_array_equal(k.cpu().numpy().view(np.uint64), keys[order])
     net.tune("digit_bits", 0)
+
+
+@pytest.mark.parametrize("n,lo,hi", [(3 * 2**19 - 1, 16, 45), (3 * 2**19, 16, 45), (2**25 - 1, 16, 52), (2**25, 16, 52),
+                                     (2**25 + 16385, 16, 50), (2**27, 16, 40)])
+def test_tile_rule_edges(n, lo, hi):
+    """Untuned sorts on both sides of the sizes where the tile changes; digits of unequal width."""
+    import torch
+    import paper_2512_09502_amd as snnc
+    print(f"tile rule n={n} bits {lo}..{hi}", flush=True)
+    fresh = snnc.Network(1, 0, 1, 0.1)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    keys = torch.randint(0, 1 << 56, (n,), generator=g, device="cuda", dtype=torch.int64)
+    vals = torch.arange(n, device="cuda", dtype=torch.int32)
+    k, v = fresh.sort_pairs(keys.clone(), vals, lo, hi)
+    d = (k >> lo) & ((1 << (hi - lo)) - 1)
+    v = v.long()
+    assert bool((d[1:] >= d[:-1]).all()) and bool((keys[v] == k).all())
+    assert bool(((d[1:] > d[:-1]) | (v[1:] > v[:-1])).all())        # stable: equal digits keep their order
+    fresh.close()
