@@ -157,8 +157,9 @@ struct TInterval {
 struct TEntry {              // a call's share of an interval: offsets [o, end) of each target's D
     uint32_t o, end, K, call;
     int64_t base;            // generation index = base + (target - first) K + offset
-    int64_t add;             // of a call with one source segment
-    uint32_t nS, pad;
+    int64_t add, add2;       // one or two source segments: the addends of ordinals below `split` and from it on
+    uint32_t split;          // 0: more segments; `add` is their div_m if they are of equal length, else 0
+    uint32_t seg;            // place of the call's segments among all calls' << 6 | div_shift
 };
 
 struct GenSource {
@@ -168,6 +169,8 @@ struct GenSource {
     const uint32_t* weight;
     const SrcMap* maps;            // per call with connections
     const uint64_t* call_begin;    // [ncalls + 1], the last one N
+    const int64_t* seg_add;        // of all calls
+    uint32_t n_seg;
     uint32_t ncalls;
     uint32_t n_iv;
     const TInterval* iv;
@@ -277,12 +280,20 @@ __global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t 
 // (source, delay, weight) and 12 B written per connection.  A wave takes
 // `unit` consecutive positions; it walks the runs of a call in them one after
 // another (all their parameters the same in every lane, so scalar) and each
-// run by 64 lanes x 4.  The alternative of letting the first radix pass gather
-// its own connections was slower: the pass ranks 16 keys a lane at 16 waves a
-// compute unit, and waits for the gather (multi-area: first pass 10.3 ms
-// instead of 4.1, against 3.3 for this kernel).
+// run by 64 lanes x 4, loading one step ahead.  Everything a step needs of its
+// call comes with the run's table entry: looked up per key through the call's
+// own table, the scalar loads stood in every key's way.  2.25e9 connections from
+// 1,024 hosts 14.9 -> 9.6 ms (5.2 TB/s), 6.3e8 from 32 areas 4.1 -> 3.7.
+// The alternative of letting the first radix pass gather its own connections
+// was slower: the pass ranks 16 keys a lane at 16 waves a compute unit, and
+// waits for the gather (6.3e8 connections: first pass 10.3 ms instead of 4.1).
 constexpr uint32_t TM_UNIT = 2048;   // at most; fewer (whole steps of a wave) where 2048 would leave compute units idle:
                                      // 1e5 connections 53.6 us with units of 2048, 10.6 with units of 128
+
+// Segment addends read from LDS, at most so many: a gather from memory takes a
+// cycle a lane in the address unit (2.25e9 connections, 2 x 1,024 segments: 11.3
+// ms through memory, 10.0 through LDS).
+constexpr uint32_t SEG_LDS = 2048;
 
 uint32_t tm_unit(uint64_t n) {
     return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n / 8192 / 64 * 64, 128), TM_UNIT);
@@ -291,11 +302,17 @@ uint32_t tm_unit(uint64_t n) {
 __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, uint32_t bit_lo, Digits dg,
                                                      uint32_t unit_size, uint64_t* keys, uint32_t* vals,
                                                      uint64_t* hist) {
-    extern __shared__ uint32_t h[];   // a histogram a pass
+    extern __shared__ __align__(8) uint32_t h[];   // a histogram a pass, then the segments' addends if they are few
     for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT) h[i] = 0;
+    int64_t* adds = nullptr;
+    if (g.n_seg <= SEG_LDS) {
+        adds = reinterpret_cast<int64_t*>(h + dg.passes * dg.stride);
+        for (uint32_t i = threadIdx.x; i < g.n_seg; i += PNT) adds[i] = g.seg_add[i];
+    }
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    constexpr int KU = 4;
     for (uint64_t unit = (uint64_t)blockIdx.x * (PNT / 64) + wave; unit * unit_size < n;
          unit += (uint64_t)gridDim.x * (PNT / 64)) {
         uint64_t q = unit * unit_size;
@@ -313,49 +330,91 @@ __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, ui
             const uint32_t m = (e + f) >> 1;
             if (g.ent[m].o <= r) e = m; else f = m;
         }
-        while (q < end) {   // one call's run of one target, or what of it lies in the unit
-            const TEntry en = g.ent[e];
-            const uint32_t len = (uint32_t)min((uint64_t)(en.end - r), end - q);
-            const uint64_t i0 = (uint64_t)(en.base + (int64_t)((uint64_t)t * en.K) + r);
-            const uint32_t tgt = v.first + t;
-            constexpr int KU = 4;
-            for (uint32_t x0 = 0; x0 < len; x0 += 64 * KU) {
-                uint32_t ord[KU], dl[KU], w[KU];
-#pragma unroll
-                for (int u = 0; u < KU; ++u) {
-                    const uint32_t x = x0 + u * 64 + lane;
-                    ord[u] = dl[u] = w[u] = 0;
-                    if (x < len) {
-                        ord[u] = g.src[i0 + x];
-                        dl[u] = g.delay[i0 + x];
-                        w[u] = g.weight[i0 + x];
+        // Steps of at most 64 KU connections of one call's run of one target; a step's connections are
+        // loaded, and the step after it worked out, while the one before it is written.
+        struct Step {
+            uint64_t i, q;           // generation index and position of its first connection
+            uint32_t cnt, tgt, split, seg, call;
+            int64_t add, add2;
+        };
+        TEntry en{};
+        uint64_t i0 = 0;
+        uint32_t len = 0, x0 = 0;    // the run (or what of it lies in the unit) and how far it is stepped through
+        auto next = [&]() {
+            Step st{};
+            if (q >= end) return st;
+            if (!x0) {
+                en = g.ent[e];
+                len = (uint32_t)min((uint64_t)(en.end - r), end - q);
+                i0 = (uint64_t)(en.base + (int64_t)((uint64_t)t * en.K) + r);
+            }
+            st = Step{i0 + x0, q + x0, len - x0 < 64u * KU ? len - x0 : 64u * KU, v.first + t, en.split, en.seg, en.call,
+                      en.add, en.add2};
+            x0 += 64 * KU;
+            if (x0 >= len) {
+                x0 = 0;
+                q += len;
+                r += len;
+                ++e;
+                if (r == v.D) {   // next target, or the next interval's first
+                    r = 0;
+                    ++t;
+                    if (q == v.q1 && q < end) {
+                        v = g.iv[++a];
+                        t = 0;
                     }
-                }
-#pragma unroll
-                for (int u = 0; u < KU; ++u) {
-                    if (x0 + u * 64 >= len) break;   // the same in every lane
-                    const uint32_t x = x0 + u * 64 + lane;
-                    uint64_t key = 0;
-                    if (x < len) {
-                        const int64_t add = en.nS == 1 ? en.add : segment_add(g.maps[en.call], ord[u]);
-                        key = conn_key(g, add, ord[u], tgt, dl[u]);
-                        keys[q + x] = key;
-                        vals[q + x] = w[u];
-                    }
-                    key_digits(h, key, x < len, bit_lo, dg);
+                    e = v.e0;
                 }
             }
-            q += len;
-            r += len;
-            ++e;
-            if (r == v.D) {   // next target, or the next interval's first
-                r = 0;
-                ++t;
-                if (q == v.q1 && q < end) {
-                    v = g.iv[++a];
-                    t = 0;
+            return st;
+        };
+        auto load = [&](const Step& st, uint32_t (&ord)[KU], uint32_t (&dl)[KU], uint32_t (&w)[KU]) {
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                const uint32_t x = u * 64 + lane;
+                ord[u] = dl[u] = w[u] = 0;
+                if (x < st.cnt) {
+                    ord[u] = g.src[st.i + x];
+                    dl[u] = g.delay[st.i + x];
+                    w[u] = g.weight[st.i + x];
                 }
-                e = v.e0;
+            }
+        };
+        Step cur = next();
+        uint32_t ord[KU], dl[KU], w[KU];
+        load(cur, ord, dl, w);
+        while (cur.cnt) {
+            const Step nxt = next();
+            uint32_t ord1[KU], dl1[KU], w1[KU];
+            load(nxt, ord1, dl1, w1);
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                if (u * 64u >= cur.cnt) break;   // the same in every lane
+                const uint32_t x = u * 64 + lane;
+                uint64_t key = 0;
+                if (x < cur.cnt) {
+                    int64_t add;
+                    if (cur.split) {
+                        add = ord[u] < cur.split ? cur.add : cur.add2;
+                    } else if (cur.add) {
+                        const uint32_t j =
+                            (cur.seg >> 6) + (uint32_t)(((uint64_t)ord[u] * (uint64_t)cur.add) >> (cur.seg & 63));
+                        add = adds ? adds[j] : g.seg_add[j];
+                    } else {
+                        add = segment_add(g.maps[cur.call], ord[u]);
+                    }
+                    key = conn_key(g, add, ord[u], cur.tgt, dl[u]);
+                    keys[cur.q + x] = key;
+                    vals[cur.q + x] = w[u];
+                }
+                key_digits(h, key, x < cur.cnt, bit_lo, dg);
+            }
+            cur = nxt;
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                ord[u] = ord1[u];
+                dl[u] = dl1[u];
+                w[u] = w1[u];
             }
         }
     }
@@ -1044,7 +1103,8 @@ void place_memory_level(Ctx& c, uint32_t M_local) {
 // call has no such runs, or they are short (fewer than 16 connections a run on
 // average: a run takes at least one step of a wave), or the tables would be long.
 bool target_major(const Ctx& c, const std::vector<uint32_t>& with_conns, const std::vector<SrcMap>& maps,
-                  std::vector<TInterval>& iv, std::vector<TEntry>& ent) {
+                  const std::vector<size_t>& seg_at, const std::vector<int64_t>& seg_add,
+                  const std::vector<uint64_t>& seg_ord, std::vector<TInterval>& iv, std::vector<TEntry>& ent) {
     constexpr size_t MAX_ENTRIES = 1u << 16;
     struct Run {
         TargetRun r;
@@ -1100,8 +1160,19 @@ bool target_major(const Ctx& c, const std::vector<uint32_t>& with_conns, const s
                 e.K = r.K;
                 e.call = kv.first;
                 e.base = (int64_t)(r.begin + (t - r.first) * r.K) - (int64_t)o;
-                e.add = maps[kv.first].add;
-                e.nS = maps[kv.first].nS;
+                const SrcMap& m = maps[kv.first];
+                const size_t at = seg_at[kv.first];
+                if (m.nS == 1) {
+                    e.split = 1;
+                    e.add = e.add2 = m.add;
+                } else if (m.nS == 2 && seg_ord[at + 1]) {
+                    e.split = (uint32_t)seg_ord[at + 1];
+                    e.add = seg_add[at];
+                    e.add2 = seg_add[at + 1];
+                } else if (at < (1u << 26)) {
+                    e.add = (int64_t)m.div_m;
+                    e.seg = (uint32_t)at << 6 | m.div_shift;
+                }
                 ent.push_back(e);
                 o += r.K;
             }
@@ -1298,7 +1369,7 @@ void prepare_all(Ctx& c) {
             // the source maps and, where it exists, the target-major order: one block, one copy
             std::vector<TInterval> iv;
             std::vector<TEntry> ent;
-            const bool by_source = target_major(c, with_conns, maps, iv, ent);
+            const bool by_source = target_major(c, with_conns, maps, seg_at, seg_add, seg_ord, iv, ent);
             if (!by_source) {
                 iv.clear();
                 ent.clear();
@@ -1332,6 +1403,8 @@ void prepare_all(Ctx& c) {
             gs.maps = reinterpret_cast<const SrcMap*>(d_tab);
             gs.call_begin = reinterpret_cast<const uint64_t*>(d_tab + b_maps);
             gs.ncalls = (uint32_t)maps.size();
+            gs.seg_add = d_seg;
+            gs.n_seg = (uint32_t)seg_add.size();
             if (by_source) {
                 gs.n_iv = (uint32_t)iv.size();
                 gs.iv = reinterpret_cast<const TInterval*>(d_tab + b_maps + b_call + 2 * b_seg);
@@ -1355,7 +1428,8 @@ void prepare_all(Ctx& c) {
             if (by_source)
                 hipLaunchKernelGGL(k_keys_tmajor,
                                    dim3((unsigned)std::min<uint64_t>((N + unit * 4 - 1) / (unit * 4), 8192)), dim3(PNT),
-                                   n_hist * 4, c.stream, gs, N, bit_lo, dg, unit, keys0, moved, hist);
+                                   n_hist * 4 + (gs.n_seg <= SEG_LDS ? gs.n_seg * 8 : 0), c.stream, gs, N, bit_lo, dg, unit,
+                                   keys0, moved, hist);
             else
                 hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), n_hist * 4, c.stream, gs, N, bit_lo, dg, keys0,
                                    hist);

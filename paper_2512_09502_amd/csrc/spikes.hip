@@ -197,7 +197,7 @@ __global__ __launch_bounds__(ONE_NT) void k_packets_one(Spikes sp, uint32_t d_bi
     __syncthreads();
     uint32_t* mine = lds + wave * nd;
     const uint64_t tile = (sp.n + ONE_WAVES - 1) / ONE_WAVES;
-    const uint64_t k0 = min(wave * tile, sp.n), k1 = min(k0 + tile, sp.n);
+    const uint64_t k0 = min((uint64_t)wave * tile, sp.n), k1 = min(k0 + tile, sp.n);
     walk_records(sp, k0, k1, row_of[wave], err, [&](uint64_t, uint32_t d, uint64_t, bool live) {
         if (live) atomicAdd(&mine[d], 1u);
     });

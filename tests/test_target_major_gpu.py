@@ -66,3 +66,15 @@ def test_sort_settings(variant, mode):
 def test_group_ranges(n_e):
     """H/I ranges below, at and above the 2,048 entries a workgroup takes at a time (40 more by the inhibitory one)."""
     compare_all(W.balanced_collective(P=5, n_e=n_e, n_i=40, k_e=3, k_i=2), 3)
+
+
+@pytest.mark.parametrize("sizes", [[50], [50, 30], [30, 30], [40, 40, 40], [40, 41, 39], [3] * 2049, [2] * 900 + [3] * 900])
+@pytest.mark.parametrize("K", [63, 300])
+def test_source_segments(sizes, K):
+    """One, two, several source segments of equal and unequal length, more of them than fit beside the histograms."""
+    n = sum(sizes)
+    first = [sum(sizes[k + 1:]) for k in range(len(sizes))]         # the segments in descending order of neurons
+    src = [(0, f, m) for f, m in zip(first, sizes)]
+    half = src[: max(1, len(src) // 2)]
+    calls = [(src, [(0, 5, 40)], _in(K), SYN, -1), (half, [(0, 0, 30)], _in(17), SYN_C, -1)]
+    compare_all(_script(f"{len(sizes)} segments", 1, [(0, max(n, 50))], calls), 0)
