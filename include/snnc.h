@@ -540,7 +540,7 @@ snnc_status snnc_tune(snnc_ctx* ctx, const char* key, int64_t value);
  * (0: 9-bit digits, 512 buckets, when they save a pass and the tile has at
  * least 512 threads; 8 or 9: forced where the tile allows), "number_variant"
  * (tile shape of the image-numbering pass after the sort, 0 .. 11; default 10 =
- * 1024 threads x 10 items with the payload loaded before the look-back) and
+ * 1024 threads x 10 items) and
  * "mark_in_lds" (1, default: regeneration for the point-to-point lists marks
  * its bit row in LDS when the row has at most 2^19 neurons; 0: a global
  * atomic per draw) and "floyd_wave_max" (0 .. 8192, default 1024: Floyd's

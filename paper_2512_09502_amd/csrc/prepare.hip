@@ -1334,6 +1334,11 @@ void prepare_all(Ctx& c) {
                     // stable sort of the canonical indices by first call: the paper's order
                     uint64_t* ik1 = static_cast<uint64_t*>(tmp(n_img * 8));
                     uint32_t* iv1 = static_cast<uint32_t*>(tmp(n_img * 4));
+                    struct Tag {   // its passes are not the connections'
+                        Ctx& c;
+                        explicit Tag(Ctx& ctx) : c(ctx) { c.sort_tag = "prep_first_sort"; }
+                        ~Tag() { c.sort_tag = nullptr; }
+                    } tag(c);
                     const int w = radix_sort(c, ik0, iv0, ik1, iv1, n_img, 16, 16 + call_bits, nullptr, nullptr);
                     tstart(c, "prep_number_calls");
                     hipLaunchKernelGGL(k_scatter_l, dim3((unsigned)((n_img + 255) / 256)), dim3(256), 0, c.stream,
