@@ -229,21 +229,23 @@ __device__ __forceinline__ void key_digits(uint32_t* h, uint64_t key, bool valid
 
 // Sort keys in generation order, with the digit histograms of all radix
 // passes: 10 B read and 8 B written per connection.
-__global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t bit_lo, Digits dg,
+constexpr int KNT = 512;   // few, large workgroups: see hist_grid
+
+__global__ __launch_bounds__(KNT) void k_keys(GenSource g, uint64_t n, uint32_t bit_lo, Digits dg,
                                               uint64_t* keys, uint64_t* hist) {
     extern __shared__ uint32_t h[];   // a histogram a pass
-    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT) h[i] = 0;
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += KNT) h[i] = 0;
     __syncthreads();
     uint64_t lo, hi;
     block_range(n, lo, hi);
     constexpr int KU = 4;   // independent elements per thread per step: their table loads overlap
     uint64_t call_end = 0;  // end of the call that holds the step's first element
     SrcMap m{};
-    for (uint64_t base = lo; base < hi; base += (uint64_t)PNT * KU) {
+    for (uint64_t base = lo; base < hi; base += (uint64_t)KNT * KU) {
         uint32_t ord[KU], tg[KU], dl[KU];
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            const uint64_t i = base + (uint64_t)u * PNT + threadIdx.x;
+            const uint64_t i = base + (uint64_t)u * KNT + threadIdx.x;
             ord[u] = tg[u] = dl[u] = 0;
             if (i < hi) {
                 ord[u] = g.src[i];
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t 
         uint64_t key[KU];
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            const uint64_t i = base + (uint64_t)u * PNT + threadIdx.x;
+            const uint64_t i = base + (uint64_t)u * KNT + threadIdx.x;
             key[u] = 0;
             if (i >= hi) continue;
             const int64_t add = i < call_end ? segment_add(m, ord[u])
@@ -269,10 +271,10 @@ __global__ __launch_bounds__(PNT) void k_keys(GenSource g, uint64_t n, uint32_t 
         }
 #pragma unroll
         for (int u = 0; u < KU; ++u)
-            key_digits(h, key[u], base + (uint64_t)u * PNT + threadIdx.x < hi, bit_lo, dg);
+            key_digits(h, key[u], base + (uint64_t)u * KNT + threadIdx.x < hi, bit_lo, dg);
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT)
+    for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += KNT)
         if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
 }
 
@@ -1436,7 +1438,7 @@ void prepare_all(Ctx& c) {
                                    n_hist * 4 + (gs.n_seg <= SEG_LDS ? gs.n_seg * 8 : 0), c.stream, gs, N, bit_lo, dg, unit,
                                    keys0, moved, hist);
             else
-                hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(PNT), n_hist * 4, c.stream, gs, N, bit_lo, dg, keys0,
+                hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(KNT), n_hist * 4, c.stream, gs, N, bit_lo, dg, keys0,
                                    hist);
             tstop(c);
             HIPCHK(hipGetLastError());

@@ -53,7 +53,7 @@ __device__ __forceinline__ uint64_t pack_status(uint64_t flag, uint32_t epoch, u
 
 namespace {
 
-constexpr int HNT = 256;
+constexpr int HNT = 1024;
 
 __global__ __launch_bounds__(HNT) void k_hist(const uint64_t* keys, uint64_t n, uint32_t bit_lo, uint32_t bit_hi,
                                               Digits dg, uint64_t* hist) {
@@ -542,11 +542,12 @@ std::string sort_timer(const Ctx& c, const char* step) {
 
 // Workgroups of a pass that builds digit histograms of n keys: every workgroup
 // ends with one global atomic per non-empty bucket and pass (about 5e10/s over
-// the device), so it takes at least 8192 keys, fewer only where that would
-// leave most compute units idle.  4096 workgroups whatever n spent 80 of the
-// 100 us of the histogram of 3e6 keys in 5 digits on those atomics.
+// the device), so it takes 8192 keys, fewer only below 512 workgroups, and is
+// large (512 or 1024 threads) so that these fill the compute units.
+// 3e6 keys in 5 digits: 100 us with 4096 workgroups of 256 threads, 40 with 1024, 23
+// with 512 of 1024 threads.
 uint32_t hist_grid(uint64_t n) {
-    const uint64_t per = std::min<uint64_t>(std::max<uint64_t>(n / 1024, 1024), 8192);
+    const uint64_t per = std::min<uint64_t>(std::max<uint64_t>(n / 512, 1024), 8192);
     return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((n + per - 1) / per, 8192));
 }
 
