@@ -602,7 +602,7 @@ snnc_status snnc_autotune_fused(snnc_ctx* ctx, uint64_t n, int32_t* wgs_out, flo
  * of entries; when it exceeds cap nothing is written and SNNC_EINVAL is
  * returned.  Runs on the context stream and waits for completion.
  * Errors: SNNC_ESTATE before snnc_prepare; SNNC_EINVAL for an unknown kind,
- * a spike id >= M_local or a small cap. */
+ * a spike id >= M_local (nothing written) or a small cap. */
 snnc_status snnc_spike_packets(snnc_ctx* ctx, int32_t kind, const uint32_t* spikes, const uint32_t* mult,
                                uint64_t n, uint64_t* off, uint32_t* pos_out, uint32_t* mult_out, uint64_t cap,
                                uint64_t* n_out);

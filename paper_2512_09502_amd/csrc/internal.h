@@ -239,6 +239,8 @@ struct Ctx {
     std::vector<size_t> open_timers;      // indices into pending of brackets not yet closed
     std::vector<hipEvent_t> event_pool;
     std::map<std::string, KernelTime> ktimes;
+    uint64_t* exchange_bad = nullptr;    // device word: number of the last exchange call with an entry out of range
+    uint64_t exchange_calls = 0;
     double ms_connect = 0.0, ms_prepare = 0.0;
     hipEvent_t phase_a = nullptr, phase_b = nullptr;
 

@@ -24,12 +24,30 @@ namespace {
 
 constexpr int SNT = 256;
 
-// The exchange's error word: a mapped pinned word that the kernels set with a
-// plain store (any lane, same value) and the host reads after the stream's
-// wait; cleared by the host before the launches (the previous call waited).
-static uint32_t* err_word(Ctx& c) {
+// Where a call's kernels note an entry outside its range, with plain stores
+// (any lane, same value): a mapped pinned word that the host reads after the
+// stream's wait (cleared by the host before the launches: the previous call
+// waited), and a word in device memory for the call's later kernels, which then
+// leave the caller's arrays alone.  The latter holds the number of the last
+// call with such an entry, so nothing has to clear it.
+struct Bad {
+    uint32_t* host;
+    uint64_t* dev;
+    uint64_t call;
+    __device__ __forceinline__ void set() const {
+        *host = 1u;
+        *dev = call;
+    }
+    __device__ __forceinline__ bool is_set() const { return *dev == call; }
+};
+
+Bad new_bad(Ctx& c) {
+    if (!c.exchange_bad) {
+        c.exchange_bad = dalloc_n<uint64_t>(c, 1);
+        HIPCHK(hipMemsetAsync(c.exchange_bad, 0, 8, c.stream));
+    }
     *reinterpret_cast<volatile uint32_t*>(c.tot_pin + 2) = 0u;
-    return reinterpret_cast<uint32_t*>(c.tot_pin_dev + 2);
+    return Bad{reinterpret_cast<uint32_t*>(c.tot_pin_dev + 2), c.exchange_bad, ++c.exchange_calls};
 }
 
 // destination rank of a list entry: the host itself (point-to-point) or the
@@ -68,10 +86,11 @@ __device__ __forceinline__ void lds_in_order() {
 
 // One wave walks the records of spikes [k0, k1) in order, 64 at a time:
 // lane's f(spike, dest, entry, live).  The rows of 64 spikes are laid end to
-// end, so short rows leave no lanes idle; row_of (65 words of the wave's LDS)
-// holds where each begins.
+// end, so short rows leave no lanes idle; row_of (64 words of the wave's LDS)
+// holds where each begins.  A spike without a row (its id is not a local
+// neuron's) sets *bad, which may be null.
 template <class F>
-__device__ __forceinline__ void walk_records(const Spikes& sp, uint64_t k0, uint64_t k1, uint32_t* row_of, uint32_t* err,
+__device__ __forceinline__ void walk_records(const Spikes& sp, uint64_t k0, uint64_t k1, uint32_t* row_of, uint32_t* bad,
                                              F f) {
     const int lane = threadIdx.x & 63;
     for (uint64_t kb = k0; kb < k1; kb += 64) {
@@ -81,7 +100,7 @@ __device__ __forceinline__ void walk_records(const Spikes& sp, uint64_t k0, uint
         if (k < k1) {
             const uint32_t s = sp.id[k];
             if (s >= sp.M) {
-                if (err) *err = 1u;   // any lane may set it
+                if (bad) *bad = 1u;   // any lane may set it
             } else {
                 row = sp.ptr[s];
                 len = (uint32_t)(sp.ptr[s + 1] - row);
@@ -118,18 +137,20 @@ __device__ __forceinline__ void walk_records(const Spikes& sp, uint64_t k0, uint
 // cnt[d * n_tiles + tile]: records of the tile for destination d.  One wave a
 // tile and range of DEST_RANGE destinations (blockIdx.y).
 __global__ __launch_bounds__(64) void k_packet_count(Spikes sp, uint64_t tile, uint32_t n_tiles, uint32_t* cnt,
-                                                     uint32_t* err) {
+                                                     Bad bad) {
     extern __shared__ __align__(8) uint32_t lds[];
-    __shared__ uint32_t row_of[64];
+    __shared__ uint32_t row_of[64], s_bad;
+    if (threadIdx.x == 0) s_bad = 0;
     const uint32_t d0 = blockIdx.y * DEST_RANGE;
     const uint32_t nd = min(sp.n_dest - d0, DEST_RANGE);
     for (uint32_t i = threadIdx.x; i < nd; i += 64) lds[i] = 0;
     __syncthreads();
     const uint64_t k0 = blockIdx.x * tile;
-    walk_records(sp, k0, min(k0 + tile, sp.n), row_of, err, [&](uint64_t, uint32_t d, uint64_t, bool live) {
+    walk_records(sp, k0, min(k0 + tile, sp.n), row_of, &s_bad, [&](uint64_t, uint32_t d, uint64_t, bool live) {
         if (live && d - d0 < nd) atomicAdd(&lds[d - d0], 1u);
     });
     __syncthreads();
+    if (threadIdx.x == 0 && s_bad) bad.set();
     for (uint32_t i = threadIdx.x; i < nd; i += 64) cnt[(uint64_t)(d0 + i) * n_tiles + blockIdx.x] = lds[i];
 }
 
@@ -157,14 +178,14 @@ __device__ __forceinline__ void place_records(const Spikes& sp, uint32_t d, bool
     lds_in_order();
 }
 
-// nothing is written where the records (off[n_dest * n_tiles]) exceed the caller's capacity
+// nothing is written where the records (first[n_dest * n_tiles]) exceed the caller's capacity or a spike has no row
 __global__ __launch_bounds__(64) void k_packet_place(Spikes sp, uint64_t tile, uint32_t n_tiles, uint32_t d_bits,
                                                      const uint64_t* first, uint64_t cap, uint64_t* off,
-                                                     uint32_t* pos_out, uint32_t* mult_out) {
+                                                     uint32_t* pos_out, uint32_t* mult_out, Bad bad) {
     extern __shared__ __align__(8) uint64_t next[];
     __shared__ uint32_t row_of[64];
     const uint64_t total = first[(uint64_t)sp.n_dest * n_tiles];
-    if (total > cap) return;
+    if ((total > cap) | bad.is_set()) return;   // both words loaded at once
     const uint32_t d0 = blockIdx.y * DEST_RANGE;
     const uint32_t nd = min(sp.n_dest - d0, DEST_RANGE);
     for (uint32_t i = threadIdx.x; i < nd; i += 64) {
@@ -188,9 +209,10 @@ constexpr uint64_t ONE_SPIKES_MAX = 1024, ONE_RECORDS_MAX = 16384;   // spikes, 
 
 __global__ __launch_bounds__(ONE_NT) void k_packets_one(Spikes sp, uint32_t d_bits, uint64_t cap, uint64_t* off,
                                                         uint32_t* pos_out, uint32_t* mult_out, uint64_t* total_out,
-                                                        uint32_t* err) {
+                                                        Bad bad) {
     extern __shared__ __align__(8) uint32_t lds[];   // [wave][destination]
-    __shared__ uint32_t row_of[ONE_WAVES][64];
+    __shared__ uint32_t row_of[ONE_WAVES][64], s_bad;
+    if (threadIdx.x == 0) s_bad = 0;
     __shared__ uint64_t scratch[ONE_WAVES];
     const uint32_t wave = threadIdx.x >> 6, nd = sp.n_dest;
     for (uint32_t i = threadIdx.x; i < nd * ONE_WAVES; i += ONE_NT) lds[i] = 0;
@@ -198,10 +220,14 @@ __global__ __launch_bounds__(ONE_NT) void k_packets_one(Spikes sp, uint32_t d_bi
     uint32_t* mine = lds + wave * nd;
     const uint64_t tile = (sp.n + ONE_WAVES - 1) / ONE_WAVES;
     const uint64_t k0 = min((uint64_t)wave * tile, sp.n), k1 = min(k0 + tile, sp.n);
-    walk_records(sp, k0, k1, row_of[wave], err, [&](uint64_t, uint32_t d, uint64_t, bool live) {
+    walk_records(sp, k0, k1, row_of[wave], &s_bad, [&](uint64_t, uint32_t d, uint64_t, bool live) {
         if (live) atomicAdd(&mine[d], 1u);
     });
     __syncthreads();
+    if (s_bad) {   // the same in every thread
+        if (threadIdx.x == 0) bad.set();
+        return;
+    }
     uint64_t sum = 0;
     if (threadIdx.x < nd)
         for (uint32_t w = 0; w < ONE_WAVES; ++w) sum += lds[w * nd + threadIdx.x];
@@ -234,7 +260,7 @@ __global__ __launch_bounds__(LOOK_NT) void k_deliver_lookup(
     const uint32_t* grp, const uint32_t* host, const uint32_t* pos, uint64_t n, uint32_t P, uint32_t PL,
     uint32_t n_maps_grp, int kind, const uint64_t* map_off, const int32_t* map_img, const uint64_t* row_ptr,
     const uint64_t* img_first, const uint32_t* img_count, uint32_t M_local, int32_t* image, uint64_t* rb, uint64_t* re,
-    uint64_t* in_block, uint64_t* block_sum, uint64_t* total_out, uint32_t* err) {
+    uint64_t* in_block, uint64_t* block_sum, uint64_t* total_out, Bad bad) {
     __shared__ uint64_t scratch[LOOK_NT / 64];
     for (uint64_t e0 = (uint64_t)blockIdx.x * LOOK_NT; e0 < n; e0 += (uint64_t)gridDim.x * LOOK_NT) {
         const uint64_t e = e0 + threadIdx.x;
@@ -254,7 +280,7 @@ __global__ __launch_bounds__(LOOK_NT) void k_deliver_lookup(
                 if ((uint64_t)pos[e] < b - a) img = map_img[a + pos[e]];
                 else ok = false;
             }
-            if (!ok) *err = 1u;   // any lane may set it
+            if (!ok) bad.set();
             if (img >= 0 && img_first) {     // image rows kept apart (GPU memory levels 0 and 1)
                 lo = img_first[(uint32_t)img - M_local];
                 hi = lo + img_count[(uint32_t)img - M_local];
@@ -283,18 +309,19 @@ __global__ __launch_bounds__(LOOK_NT) void k_deliver_lookup(
 // its first and last one (64 probes a step); the entries between are brought
 // into LDS, where each event finds its own.  Bound by latency at one step's
 // sizes (a search of all entries by each event 30 us, this 12), by the 10 B
-// read and 10 B written an event beyond.  Nothing is written where the events exceed the caller's capacity.
+// read and 10 B written an event beyond.  Nothing is written where the events
+// exceed the caller's capacity or an entry lies outside its map.
 constexpr uint32_t EV_CHUNK = 1024, EV_ENTRIES = 512;
 
 __global__ __launch_bounds__(SNT) void k_deliver_events(const uint64_t* block_off, const uint64_t* in_block, uint64_t n,
                                                         uint64_t n_blocks, uint64_t cap, const uint64_t* rb,
                                                         const uint32_t* mult, const int32_t* tgt, const uint16_t* delay,
                                                         const float* weight, int32_t* ev_tgt, uint16_t* ev_delay,
-                                                        float* ev_weight) {
+                                                        float* ev_weight, Bad bad) {
     __shared__ uint64_t ends[2], begin[EV_ENTRIES], from[EV_ENTRIES];
     __shared__ float times[EV_ENTRIES];
     const uint64_t total = block_off[n_blocks];
-    if (total > cap) return;
+    if ((total > cap) | bad.is_set()) return;   // both words loaded at once
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto first_event = [&](uint64_t e) { return block_off[e / LOOK_NT] + in_block[e]; };
     for (uint64_t o0 = (uint64_t)blockIdx.x * EV_CHUNK; o0 < total; o0 += (uint64_t)gridDim.x * EV_CHUNK) {
@@ -395,11 +422,11 @@ uint64_t spike_packets(Ctx& c, int kind, const uint32_t* spikes, const uint32_t*
     const Spikes sp{spikes, n, M, ptr, dest, where, groups, n_groups, n_dest, mult};
     const uint32_t nd = std::min(n_dest, DEST_RANGE);
     const uint32_t d_bits = bits_for_values(nd);
-    uint32_t* err = err_word(c);   // mapped pinned memory, as the total: both read after the wait
+    const Bad bad = new_bad(c);   // its host word and the total are mapped pinned memory: both read after the wait
     if (n_dest == 0 || (n <= ONE_SPIKES_MAX && n_dest <= ONE_DEST_MAX && n * n_dest <= ONE_RECORDS_MAX)) {
         tstart(c, "spike_packets");
         hipLaunchKernelGGL(k_packets_one, dim3(1), dim3(ONE_NT), ONE_WAVES * nd * 4, c.stream, sp, d_bits, cap, off,
-                           pos_out, mult_out, c.tot_pin_dev, err);
+                           pos_out, mult_out, c.tot_pin_dev, bad);
         tstop(c);
         HIPCHK(hipGetLastError());
         sync(c);
@@ -417,13 +444,13 @@ uint64_t spike_packets(Ctx& c, int kind, const uint32_t* spikes, const uint32_t*
         try {
             first = dalloc_n<uint64_t>(c, cells + 1);
             tstart(c, "spike_records");
-            hipLaunchKernelGGL(k_packet_count, grid, dim3(64), nd * 4, c.stream, sp, tile, n_tiles, cnt, err);
+            hipLaunchKernelGGL(k_packet_count, grid, dim3(64), nd * 4, c.stream, sp, tile, n_tiles, cnt, bad);
             tstop(c);
             HIPCHK(hipGetLastError());
             scan_u32_u64_to(c, cnt, first, cells, c.tot_pin_dev);
             tstart(c, "spike_packets");
             hipLaunchKernelGGL(k_packet_place, grid, dim3(64), nd * 8, c.stream, sp, tile, n_tiles, d_bits,
-                               (const uint64_t*)first, cap, off, pos_out, mult_out);
+                               (const uint64_t*)first, cap, off, pos_out, mult_out, bad);
             tstop(c);
             HIPCHK(hipGetLastError());
             sync(c);
@@ -455,7 +482,7 @@ uint64_t deliver(Ctx& c, int kind, const uint32_t* grp, const uint32_t* host, co
     }
     const uint64_t n_blocks = (n + LOOK_NT - 1) / LOOK_NT;
     const bool one = n_blocks == 1;
-    uint32_t* err = err_word(c);   // mapped pinned memory, as the total: both read after the wait
+    const Bad bad = new_bad(c);   // its host word and the total are mapped pinned memory: both read after the wait
     uint64_t* in_block = dalloc_n<uint64_t>(c, n);
     uint64_t *sums = nullptr, *block_off = nullptr;
     try {
@@ -466,7 +493,7 @@ uint64_t deliver(Ctx& c, int kind, const uint32_t* grp, const uint32_t* host, co
                            c.stream, grp, host, pos, n, c.P, c.P_local, (uint32_t)c.counts[SNNC_GROUPS], kind, map_off,
                            map_img, row_ptr, arr_or_null<uint64_t>(c, SNNC_IMG_FIRST),
                            arr_or_null<uint32_t>(c, SNNC_IMG_COUNT), c.M[c.P_local], image, rb, re, in_block, sums,
-                           one ? c.tot_pin_dev : (uint64_t*)nullptr, err);
+                           one ? c.tot_pin_dev : (uint64_t*)nullptr, bad);
         tstop(c);
         HIPCHK(hipGetLastError());
         if (!one) scan_u64_u64_to(c, sums, block_off, n_blocks, c.tot_pin_dev);
@@ -477,7 +504,7 @@ uint64_t deliver(Ctx& c, int kind, const uint32_t* grp, const uint32_t* host, co
             hipLaunchKernelGGL(k_deliver_events, dim3((unsigned)std::min<uint64_t>(chunks, (uint64_t)c.n_cu * 8)),
                                dim3(SNT), 0, c.stream, (const uint64_t*)block_off, (const uint64_t*)in_block, n, n_blocks,
                                ev_cap, (const uint64_t*)rb, mult, arr<int32_t>(c, SNNC_TGT),
-                               arr<uint16_t>(c, SNNC_DELAY), arr<float>(c, SNNC_WEIGHT), ev_tgt, ev_delay, ev_weight);
+                               arr<uint16_t>(c, SNNC_DELAY), arr<float>(c, SNNC_WEIGHT), ev_tgt, ev_delay, ev_weight, bad);
             tstop(c);
             HIPCHK(hipGetLastError());
         }
