@@ -288,7 +288,7 @@ __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ ki
                 const uint64_t g = out_base[dd[k]] + s;
                 if constexpr (FINAL) {
                     if (fo.prefix64) fo.prefix64[g] = x >> fo.tgt_shift;
-                else fo.src[g] = (int32_t)(x >> fo.tgt_shift);
+                    else fo.src[g] = (int32_t)(x >> fo.tgt_shift);
                     fo.tgt[g] = (int32_t)((x >> 16) & fo.tgt_mask);
                     fo.delay[g] = (uint16_t)(x & 0xffffu);
                 } else {
@@ -610,6 +610,10 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
     const int variant = plan.variant, mode = fs ? 0 : plan.mode;
     const uint32_t rb = dg.stride;
     if (passes > 8) raise(SNNC_EUNSUPPORTED, "radix sort over more than 64 bits");
+    if (!n) {   // no tile to launch
+        c.sort_passes = 0;
+        return 0;
+    }
     const uint64_t tile = (uint64_t)VARIANTS[variant].nt * VARIANTS[variant].ipt;
     const uint64_t tiles = (n + tile - 1) / tile;
     if (fs && passes && n && (size_t)tiles * rb * 8 > fs->lookback_bytes)
@@ -627,7 +631,7 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
     try {
         uint64_t hh[8 * MAX_STRIDE];
         uint64_t* off = nullptr;
-        if (passes && n) {
+        if (passes) {
             uint64_t* hist = const_cast<uint64_t*>(digit_hist);
             if (!hist && fs) {
                 hist = fs->hist;
@@ -661,7 +665,7 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
             }
         }
         uint32_t live[8];
-        const uint32_t n_live = live_passes(wait_for_plan && passes && n ? hh : nullptr, dg, n, live);
+        const uint32_t n_live = live_passes(wait_for_plan && passes ? hh : nullptr, dg, n, live);
         c.sort_passes = n_live;
         uint64_t* kb[2] = {keys0, keys1};
         uint32_t* vb[2] = {vals0, vals1};
@@ -684,7 +688,7 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
             HIPCHK(hipGetLastError());
             cur ^= 1;
         }
-        if (final_out && !n_live && n) {
+        if (final_out && !n_live) {
             tstart(c, sort_timer(c, "unpack").c_str());
             hipLaunchKernelGGL(k_unpack, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c.stream, kb[cur], vb[cur], n,
                                final_out(cur));
