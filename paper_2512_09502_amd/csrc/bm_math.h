@@ -2,12 +2,13 @@
 // written for the arguments that occur there (usable on host and device):
 // ln(v / 2^32) for integer v in [1, 2^32] and cos(2 pi w / 2^32) for a word w.
 // Both reduce their argument exactly with integer operations, so only short
-// polynomials remain (Taylor series of atanh and sin, truncated below 2^-56 on
-// the reduced ranges).
+// polynomials remain (Taylor series of atanh, sin and cos, truncated below
+// 2^-56 on the reduced ranges).
 #pragma once
 
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 
 #ifndef __HIPCC__
 #define SNNC_HD inline
@@ -24,8 +25,16 @@ namespace snnc {
 SNNC_HD double approx_rcp(double x) { return __builtin_amdgcn_rcp(x); }
 SNNC_HD double approx_rsq(double x) { return __builtin_amdgcn_rsq(x); }
 #else
-SNNC_HD double approx_rcp(double x) { return 1.0 / x; }
-SNNC_HD double approx_rsq(double x) { return 1.0 / std::sqrt(x); }
+// 23 significant bits, fewer than the hardware's: a host check then sees the refinement work
+SNNC_HD double leading_bits(double x) {
+    uint64_t u;
+    std::memcpy(&u, &x, 8);
+    u &= ~0ull << 30;
+    std::memcpy(&x, &u, 8);
+    return x;
+}
+SNNC_HD double approx_rcp(double x) { return leading_bits(1.0 / x); }
+SNNC_HD double approx_rsq(double x) { return leading_bits(1.0 / std::sqrt(x)); }
 #endif
 
 // The functions take N arguments in lockstep: a coefficient is then brought
@@ -33,7 +42,9 @@ SNNC_HD double approx_rsq(double x) { return 1.0 / std::sqrt(x); }
 // as many moves as multiply-adds were issued for the coefficients.
 
 // n / d for 1 <= d <= 4: the reciprocal refined by two Newton steps, the
-// quotient by its remainder (no scaling: neither end of the exponent range occurs)
+// quotient by its remainder (Markstein, IBM J. Res. Dev. 34, 1990; no scaling:
+// neither end of the exponent range occurs).  On the device equal to n / d for
+// each of the 2^32 arguments of the logarithm below.
 template <int N>
 SNNC_HD void quotients(const double (&n)[N], const double (&d)[N], double (&q)[N]) {
     double r[N];
@@ -44,8 +55,10 @@ SNNC_HD void quotients(const double (&n)[N], const double (&d)[N], double (&q)[N
     SNNC_UNROLL for (int i = 0; i < N; ++i) q[i] = fma(fma(-d[i], q[i], n[i]), r[i], q[i]);
 }
 
-// square roots of x in [0, 64]: y = x rsq(x) refined by Newton steps on y and
-// on 1 / (2 y), then by y's remainder
+// square roots of x in [0, 64]: y = x rsq(x) refined by a Newton step on y and
+// on 1 / (2 y) together (Goldschmidt's iteration; Markstein, RNC 6, 2004), then
+// twice by y's remainder.  On the device equal to sqrt(x) for each of the 2^32
+// values of -2 ln(v / 2^32).
 template <int N>
 SNNC_HD void square_roots(const double (&x)[N], double (&y)[N]) {
     double g[N], h[N];
@@ -102,44 +115,48 @@ SNNC_HD void log_u32_fracs(const uint64_t (&v)[N], double (&out)[N]) {
 
 // cos(x) for x = fl(2pi_d * w / 2^32), the argument as a double product
 // (2pi_d = 2 pi rounded to double), as Box-Muller in double precision forms
-// it.  theta = 2 pi w / 2^32 is reduced exactly: with q = w >> 30 and the
-// offset r in the quadrant, cos theta = +- sin b for b = 2 pi g / 2^32, g = r in
-// the odd quadrants and 2^30 - r in the even ones; sin b on [0, pi/2] by its
-// Taylor series to b^21 (the next term is below 2^-59).  Then x = theta + corr
-// with corr = (2pi_d - 2 pi) u + (the product's rounding error, exact by a
-// fused multiply-add), so cos x = cos theta - corr sin theta (corr <= 1e-15:
-// the next term is below 1e-30, and sin theta in single precision is enough).
+// it.  theta = 2 pi w / 2^32 is reduced exactly: quadrant q = w >> 30, the
+// offset r inside it folded to [0, pi/4] (cos a = sin(pi/2 - a)), sine and
+// cosine there by their Taylor series; then x = theta + corr with
+// corr = (2pi_d - 2 pi) u + (the product's rounding error, exact by a fused
+// multiply-add), so cos x = cos theta - corr sin theta (corr <= 1e-15: the
+// next term is below 1e-30).  One sine series on [0, pi/2] saves nine
+// multiply-adds, but its largest error is 2.5e-16 instead of 2.2e-16.
 template <int N>
 SNNC_HD void cos_2pi_u32s(const uint32_t (&w)[N], double (&out)[N]) {
     const double two_pi_over_2_32 = 1.4629180792671596e-09;   // 2 pi / 2^32
     const double two_pi_d = 6.283185307179586;                 // 2 pi rounded to double
     const double two_pi_err = -2.4492935982947064e-16;         // two_pi_d - 2 pi
-    // sin b = b - b^3/3! + b^5/5! - ... (to b^21)
-    const double c[10] = {1.0 / 51090942171709440000.0, -1.0 / 121645100408832000.0, 1.0 / 355687428096000.0,
-                          -1.0 / 1307674368000.0,       1.0 / 6227020800.0,          -1.0 / 39916800.0,
-                          1.0 / 362880.0,               -1.0 / 5040.0,               1.0 / 120.0,
-                          -1.0 / 6.0};
-    double b[N], z[N], p[N];
+    // sin b = b - b^3/3! + b^5/5! - ... (to b^19), cos b = 1 - b^2/2! + b^4/4! - ... (to b^18), b^2 <= 0.617
+    const double cs[9] = {-1.0 / 121645100408832000.0, 1.0 / 355687428096000.0, -1.0 / 1307674368000.0,
+                          1.0 / 6227020800.0,          -1.0 / 39916800.0,       1.0 / 362880.0,
+                          -1.0 / 5040.0,               1.0 / 120.0,             -1.0 / 6.0};
+    const double cc[9] = {1.0 / 6402373705728000.0, -1.0 / 20922789888000.0, 1.0 / 87178291200.0,
+                          -1.0 / 479001600.0,       1.0 / 3628800.0,         -1.0 / 40320.0,
+                          1.0 / 720.0,              -1.0 / 24.0,             1.0 / 2.0};
+    double b[N], z[N], q[N], p[N];
     SNNC_UNROLL for (int i = 0; i < N; ++i) {
         const uint32_t r = w[i] & 0x3fffffffu;
-        b[i] = (double)(((w[i] >> 30) & 1u) ? r : (1u << 30) - r) * two_pi_over_2_32;
+        b[i] = (double)(r < (1u << 29) ? r : (1u << 30) - r) * two_pi_over_2_32;
         z[i] = b[i] * b[i];
-        p[i] = c[0];
+        q[i] = cs[0];
+        p[i] = cc[0];
     }
-    SNNC_UNROLL for (int k = 1; k < 10; ++k)
-        SNNC_UNROLL for (int i = 0; i < N; ++i) p[i] = p[i] * z[i] + c[k];
+    SNNC_UNROLL for (int k = 1; k < 9; ++k)
+        SNNC_UNROLL for (int i = 0; i < N; ++i) {
+            q[i] = q[i] * z[i] + cs[k];
+            p[i] = p[i] * z[i] + cc[k];
+        }
     SNNC_UNROLL for (int i = 0; i < N; ++i) {
-        const double sb = fma(b[i], z[i] * p[i], b[i]);
-        const double ct = ((w[i] + (1u << 30)) >> 31) ? -sb : sb;       // quadrants 1 and 2
+        const double sb = b[i] + b[i] * (z[i] * q[i]), cb = 1.0 - z[i] * p[i];
+        const bool cosine = (((w[i] >> 29) ^ (w[i] >> 30)) & 1u) == 0;   // the lower half of an even quadrant, the upper of an odd one
+        const double c1 = cosine ? cb : sb, s1 = cosine ? sb : cb;
+        const double ct = ((w[i] + (1u << 30)) >> 31) ? -c1 : c1;       // cos theta: negative in quadrants 1 and 2
+        const double st = (w[i] >> 31) ? -s1 : s1;                      // sin theta: negative in quadrants 2 and 3
         const double u = (double)w[i] * (1.0 / 4294967296.0);
         const double x = two_pi_d * u;
         const double corr = two_pi_err * u - fma(two_pi_d, u, -x);      // x - 2 pi u
-#ifdef __HIP_DEVICE_COMPILE__
-        const float st = __builtin_amdgcn_sinf((float)w[i] * (1.0f / 4294967296.0f));   // sin theta
-#else
-        const float st = std::sin((float)x);
-#endif
-        out[i] = ct - (double)st * corr;
+        out[i] = ct - st * corr;
     }
 }
 
