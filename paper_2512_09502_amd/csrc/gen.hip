@@ -492,7 +492,7 @@ struct OneToOne {
 // lie in [g, end) and in the run that holds g; returns where that run or the
 // range ends.  pos: the item's index within the call (whose items start at
 // `origin`).  The run is the same in every lane, so that its parameters stay in
-// scalar registers; a tile nearly always meets one.
+// scalar registers; nearly every tile lies in one.
 template <class Rule>
 __device__ __forceinline__ uint64_t eval_tile(const Rule& rule, uint64_t first, uint64_t g, uint64_t end, uint64_t origin,
                                               uint64_t (&pos)[IPT], Res (&r)[IPT], bool (&ok)[IPT]) {
@@ -510,16 +510,22 @@ __device__ __forceinline__ uint64_t eval_tile(const Rule& rule, uint64_t first, 
 
 // Items [first, end) of a tile, each written at its index.  A thread takes its
 // IPT items together: their draws are independent, and the coefficients of the
-// Box-Muller polynomials are loaded once for all of them.
+// Box-Muller polynomials are loaded once for all of them.  In a tile of several
+// runs every item looks its own up: with the runs taken one after another, each
+// paid the draws and synapse values of a whole tile (20,000 targets in segments
+// of one, one connection each: 33 us a call so, 2,860 by runs; one-to-one over 300
+// such segments 12 and 710).
 template <class Rule, class Sink>
 __device__ __forceinline__ void direct_tile(const Rule& rule, const Sink& sink, uint64_t first, uint64_t end) {
-    for (uint64_t g = first; g < end;) {
-        uint64_t pos[IPT];
-        Res r[IPT];
-        bool ok[IPT];
-        g = eval_tile(rule, first, g, end, 0, pos, r, ok);
-        sink.put_all(pos, r, ok);
+    uint64_t pos[IPT];
+    Res r[IPT];
+    bool ok[IPT];
+    if (eval_tile(rule, first, first, end, 0, pos, r, ok) < end) {
+#pragma unroll
+        for (int k = 0; k < IPT; ++k)
+            ok[k] = first + (uint64_t)k * NT + threadIdx.x < end && rule.eval(pos[k], &r[k]) != 0;
     }
+    sink.put_all(pos, r, ok);
 }
 
 // Elements written unit by unit (K elements per unit, in the order of the unit
@@ -534,6 +540,7 @@ struct UnitElems {
         r[0] = Res{0, 0, c.t_ord * (uint64_t)K + (g - c.out_begin)};
         return 1;
     }
+    __device__ __forceinline__ int eval(uint64_t g, Res* r) const { return eval_in(ch.at(g), g, r); }
 };
 
 // ------------------------------------------------------------------ generic kernel
@@ -2003,9 +2010,12 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
 // ------------------------------------------------------------------ fused batches
 // Many small calls whose connections are written one per element (no count
 // depends on the draws) run as one persistent launch: a descriptor per call
-// gives its item range in the batch and its rule parameters; every item finds
-// its call by binary search and is generated exactly as in the per-call
-// kernel, at the position the call was admitted to.
+// gives its item range in the batch and its rule parameters; every item is
+// generated exactly as in the per-call kernel, at the position the call was
+// admitted to.  k_fused takes the calls of a tile one after another, and the runs
+// of a call, all threads on one: calls of a few hundred items or more.  Calls
+// below that, or with runs below that, and small batches go to k_fused_items, where
+// every item finds its call, and its run, by binary search.
 // F_SYN_FILL: the synapse values of a Floyd call (its sources and targets
 // written by its own launch), element index from the run table as in
 // k_syn_fill; `ind` holds the run table and K.
@@ -2135,6 +2145,36 @@ __global__ __launch_bounds__(NT) void k_fused(const FusedReq* __restrict__ reqs,
             fused_items(reqs + k, h, first, g, k + 1 < r_hi ? reqs[k + 1].item_begin : end, my_fx);
         }
     }
+}
+
+// One item of the call with descriptor q; fx is the thread's first slot of the
+// small Floyd sampler's LDS values.
+__device__ __forceinline__ void fused_item(const FusedReq* __restrict__ q, const FusedHdr& h, uint64_t item,
+                                           uint32_t* fx) {
+    const uint64_t pos[1] = {item - q->item_begin};
+    if (q->kind == F_FLOYD_SMALL) {
+        const IdSink ids{h.src, h.tgt, q->out_base};
+        floyd_small_unit<IdSink, DIRECT>(q->fl, pos[0], fx, NT, ids, nullptr, nullptr);
+        return;
+    }
+    Res r[1] = {};
+    bool ok[1];
+    switch (q->kind) {
+    case F_INDEGREE: ok[0] = q->ind.eval(pos[0], r) != 0; break;
+    case F_TOTAL: ok[0] = q->tot.eval(pos[0], r) != 0; break;
+    case F_OUTDEGREE: ok[0] = q->outd.eval(pos[0], r) != 0; break;
+    case F_SYN_FILL: ok[0] = UnitElems{q->ind.ch, q->ind.K}.eval(pos[0], r) != 0; break;
+    default: ok[0] = q->o2o.eval(pos[0], r) != 0; break;
+    }
+    const bool fill = q->kind == F_SYN_FILL;
+    const WriteSink ws{fill ? nullptr : h.src, h.tgt, h.delay, h.weight, q->out_base, q->syn, h.seed, q->call};
+    ws.put_all(pos, r, ok);
+}
+
+__global__ __launch_bounds__(NT) void k_fused_items(const FusedReq* __restrict__ reqs, FusedHdr h) {
+    __shared__ uint32_t fx[FLOYD_SMALL * NT];
+    for (uint64_t item = (uint64_t)blockIdx.x * NT + threadIdx.x; item < h.total; item += (uint64_t)gridDim.x * NT)
+        fused_item(reqs + find_req(reqs, 0, (uint32_t)h.n_req, item), h, item, fx + threadIdx.x);
 }
 
 // Descriptor of a call for the fused launch, or false if the call needs its
@@ -2269,12 +2309,37 @@ void gen_mark(Ctx& c, Call& cl, uint32_t host, uint32_t* bits) { run_call(c, cl,
 // One batch of admitted calls: the fusable ones in one persistent launch
 // (replayed from a captured graph), the others with their own launches, all
 // writing at their admitted positions.  Records the batch's completion event.
+// Whether a call goes to k_fused_items.  A turn of k_fused costs the draws and
+// synapse values of a whole tile however few of the call's items are in it; one
+// item a thread costs more where tiles are full.  1,024 requests of n connections,
+// k_fused and k_fused_items: n = 1 4,390 and 16 us, 100 69 and 14, 300 46 and 22, 700
+// 40 and 34, 1,000 42.4 and 41.7, 3,000 67 and 98.  So the line is a tile's size.
+constexpr uint64_t SHORT_RUN = TILE;
+// A batch of so many items (eight workgroups a compute unit) or fewer goes to
+// k_fused_items as a whole: the tiles of k_fused would leave compute units idle, and
+// two launches cost more than one.  Batches of 256 requests, 5.5e5 connections: 24 us,
+// 47 in two launches, 39 by calls alone.
+constexpr uint64_t ONE_LAUNCH = 1u << 19;
+
+bool by_items(const FusedReq& q, uint64_t items, const std::vector<TChunk>& chunks, size_t chunk_at) {
+    if (items < SHORT_RUN) return true;
+    const ChunkTab* t = q.kind == F_INDEGREE || q.kind == F_SYN_FILL ? &q.ind.ch
+                        : q.kind == F_OUTDEGREE                      ? &q.outd.ch
+                        : q.kind == F_ONE_TO_ONE                     ? &q.o2o.ch
+                                                                     : nullptr;
+    if (!t) return false;   // without runs, or (small Floyd samples) without turns for them
+    const uint64_t per_unit = q.kind == F_ONE_TO_ONE ? 1 : q.kind == F_OUTDEGREE ? q.outd.K : q.ind.K;
+    const TChunk* run = t->n <= CH_INLINE ? t->in : chunks.data() + chunk_at;
+    uint32_t n_short = 0;   // two at most: the tiles of k_fused meet few turns
+    for (uint32_t k = 0; k < t->n && n_short <= 2; ++k) n_short += run[k].n * per_unit < SHORT_RUN ? 1 : 0;
+    return n_short > 2;
+}
+
 void flush_batch(Ctx& c, const std::vector<uint32_t>& ids, hipEvent_t done) {
     std::vector<FusedReq> reqs;
     std::vector<size_t> chunk_at;
     std::vector<TChunk> chunks;
     std::vector<uint32_t> rest;
-    uint64_t total = 0;
     uint32_t first_fused = UINT32_MAX;
     for (uint32_t id : ids) {
         Call& cl = c.calls[id];
@@ -2285,8 +2350,7 @@ void flush_batch(Ctx& c, const std::vector<uint32_t>& ids, hipEvent_t done) {
             continue;
         }
         if (c.fuse_batches && fused_desc(c, cl, q, chunks, &at)) {
-            q.item_begin = total;
-            total += cl.gen_count;
+            q.item_begin = cl.gen_count;   // the number of items until the descriptors are in order
             reqs.push_back(q);
             chunk_at.push_back(at);
             if (first_fused == UINT32_MAX) first_fused = id;
@@ -2306,12 +2370,14 @@ void flush_batch(Ctx& c, const std::vector<uint32_t>& ids, hipEvent_t done) {
     }
     c.gen_defer = nullptr;
     for (FusedReq& q : deferred) {
-        const uint64_t items = q.item_begin;
-        q.item_begin = total;
-        total += items;
         reqs.push_back(q);
         chunk_at.push_back(SIZE_MAX);
     }
+    std::vector<char> single(reqs.size());
+    uint64_t items = 0;
+    for (const FusedReq& q : reqs) items += q.item_begin;
+    for (size_t k = 0; k < reqs.size(); ++k)
+        single[k] = items <= ONE_LAUNCH || by_items(reqs[k], reqs[k].item_begin, chunks, chunk_at[k]);
     if (!chunks.empty()) {
         // the chunk tables of every fused call: one block, one copy (kept until Prepare)
         TChunk* dev = dalloc_n<TChunk>(c, chunks.size());
@@ -2351,12 +2417,34 @@ void flush_batch(Ctx& c, const std::vector<uint32_t>& ids, hipEvent_t done) {
             HIPCHK(hipGraphInstantiate(&c.fused_exec, g, nullptr, nullptr, 0));
             HIPCHK(hipGraphDestroy(g));
         }
-        FusedHdr h{reqs.size(), total, c.g_src, c.g_tgt, c.g_delay, c.g_weight, c.seed};
-        upload(c, c.fused_reqs, reqs.data(), reqs.size() * sizeof(FusedReq));
-        upload(c, c.fused_hdr, &h, sizeof h);
-        tstart(c, "gen_fused");
-        HIPCHK(hipGraphLaunch(c.fused_exec, c.stream));
-        tstop(c);
+        // the descriptors of k_fused, then those of k_fused_items, each with its own item space
+        std::vector<FusedReq> order;
+        order.reserve(reqs.size());
+        FusedHdr h[2];
+        for (int s = 0; s < 2; ++s) {
+            h[s] = FusedHdr{order.size(), 0, c.g_src, c.g_tgt, c.g_delay, c.g_weight, c.seed};
+            for (size_t k = 0; k < reqs.size(); ++k) {
+                if (single[k] != s) continue;
+                order.push_back(reqs[k]);
+                order.back().item_begin = h[s].total;
+                h[s].total += reqs[k].item_begin;
+            }
+            h[s].n_req = order.size() - h[s].n_req;
+        }
+        upload(c, c.fused_reqs, order.data(), order.size() * sizeof(FusedReq));
+        if (h[0].n_req) {
+            upload(c, c.fused_hdr, &h[0], sizeof h[0]);
+            tstart(c, "gen_fused");
+            HIPCHK(hipGraphLaunch(c.fused_exec, c.stream));
+            tstop(c);
+        }
+        if (h[1].n_req) {
+            tstart(c, "gen_fused_items");
+            hipLaunchKernelGGL(k_fused_items, dim3((unsigned)std::min<uint64_t>((h[1].total + NT - 1) / NT, 1u << 20)),
+                               dim3(NT), 0, c.stream, static_cast<const FusedReq*>(c.fused_reqs) + h[0].n_req, h[1]);
+            tstop(c);
+            HIPCHK(hipGetLastError());
+        }
     }
     HIPCHK(hipEventRecord(done, c.stream));
 }
