@@ -1103,11 +1103,20 @@ void place_memory_level(Ctx& c, uint32_t M_local) {
 // Intervals of targets covered by the same calls, and the calls' entries in
 // them (see TInterval), from the calls' runs (in call order).  False when some
 // call has no such runs, or they are short (fewer than 16 connections a run on
-// average: a run takes at least one step of a wave), or the tables would be long.
+// average: a run takes at least one step of a wave), or the entries are many for
+// the connections.  An entry takes the host 50 ns; the passes saved (two over 65,536
+// targets) are worth 10 us up to 1e6 connections, 38 us at 5.2e6 and 205 us at 2.1e7.
+// Prepare of 3.3e5 connections to targets in 1, 256, 1,024, 16,384 segments: 82, 99, 130,
+// 880 us in target order, 96 otherwise; of 2.1e7: 453, 476, 505, 1,269 and 663.
 bool target_major(const Ctx& c, const std::vector<uint32_t>& with_conns, const std::vector<SrcMap>& maps,
                   const std::vector<size_t>& seg_at, const std::vector<int64_t>& seg_add,
                   const std::vector<uint64_t>& seg_ord, std::vector<TInterval>& iv, std::vector<TEntry>& ent) {
-    constexpr size_t MAX_ENTRIES = 1u << 16;
+    const size_t max_entries = (size_t)std::min<uint64_t>(128 + c.n_gen / 8192, 1u << 16);
+    size_t n_seg = 0;   // each of them a run at least: no need to look further where they are too many
+    for (uint32_t k : with_conns) {
+        for (auto& g : c.calls[k].T.seg) n_seg += g.host == c.P_local ? 1 : 0;
+        if (n_seg > max_entries) return false;
+    }
     struct Run {
         TargetRun r;
         uint32_t call;
@@ -1119,7 +1128,7 @@ bool target_major(const Ctx& c, const std::vector<uint32_t>& with_conns, const s
         if (!target_runs(c, c.calls[with_conns[k]], tmp)) return false;
         for (auto& r : tmp)
             if (r.n && r.K) runs.push_back(Run{r, k});
-        if (runs.size() > MAX_ENTRIES) return false;
+        if (runs.size() > max_entries) return false;
     }
     std::vector<uint64_t> cuts;
     for (auto& x : runs) {
@@ -1137,14 +1146,14 @@ bool target_major(const Ctx& c, const std::vector<uint32_t>& with_conns, const s
             it = (uint64_t)it->second.first + it->second.n <= cuts[i] ? active.erase(it) : std::next(it);
         for (; next < runs.size() && runs[next].r.first <= cuts[i]; ++next) active[runs[next].call] = runs[next].r;
         if (active.empty()) continue;
-        if (ent.size() + active.size() > MAX_ENTRIES) return false;
+        if (ent.size() + active.size() > max_entries) return false;
         uint64_t D = 0;
         for (auto& kv : active) D += kv.second.K;
         if (D > 0x7fffffffull) return false;
         const uint64_t max_n = 0x7fffffffull / D;   // positions inside an interval stay below 2^31
         for (uint64_t t = cuts[i]; t < cuts[i + 1];) {
             const uint64_t n = std::min(max_n, cuts[i + 1] - t);
-            if (ent.size() + active.size() > MAX_ENTRIES) return false;
+            if (ent.size() + active.size() > max_entries) return false;
             TInterval v{};
             v.q0 = q;
             v.q1 = q + n * D;
