@@ -416,6 +416,8 @@ constexpr Variant VARIANTS[] = {{512, 16, true},  {256, 8, false},  {512, 8, fal
                                 {256, 16, false}, {256, 12, false}, {1024, 8, false}, {1024, 8, true},
                                 {512, 8, true},   {512, 12, true},  {256, 16, true},  {512, 11, true},
                                 {1024, 16, true}, {768, 12, true}};
+constexpr int LARGE_TILE_VARIANT = 12;
+constexpr uint64_t LARGE_TILE = (uint64_t)VARIANTS[LARGE_TILE_VARIANT].nt * VARIANTS[LARGE_TILE_VARIANT].ipt;
 constexpr int N_VARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
 
 // autotuner results for the process: (pass algorithm, tile shape) per size
@@ -512,7 +514,7 @@ SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits, bool fixed) {
         // many: double-size ones, whose runs fill whole lines (8 bits, 2^26, 2^27, 2^28 pairs: 339, 674,
         // 1334 us against 335, 678, 1363; 9 bits, 2^23, 2^25, 2^28: 60, 197, 1470 against 55, 213, 1716)
         const bool nine = (bits + 8) / 9 < (bits + 7) / 8;
-        if (p.variant == 0 && n >= (nine ? 1ull << 25 : 1ull << 27) && !fixed) p.variant = 12;
+        if (p.variant == 0 && n >= (nine ? 1ull << 25 : 1ull << 27) && !fixed) p.variant = LARGE_TILE_VARIANT;
         auto it = tune_cache().find(TuneKey{log2_floor(std::max<uint64_t>(n, 1)), bits});
         if (it != tune_cache().end()) {
             p.mode = it->second.first;
@@ -607,7 +609,8 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
     const Digits& dg = plan.d;
     const uint32_t passes = dg.passes;
     // the reduce-then-scan passes allocate per-tile counts: fixed scratch takes onesweep passes
-    const int variant = plan.variant, mode = fs ? 0 : plan.mode;
+    int variant = plan.variant;
+    const int mode = fs ? 0 : plan.mode;
     const uint32_t rb = dg.stride;
     if (passes > 8) raise(SNNC_EUNSUPPORTED, "radix sort over more than 64 bits");
     if (!n) {   // no tile to launch
@@ -660,7 +663,16 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
             HIPCHK(hipGetLastError());
             if (wait_for_plan) download(c, hh, hist, (size_t)passes * dg.stride * 8);
             if (!fs) {
-                ensure_lookback(c, (size_t)tiles * rb * 8);
+                try {
+                    ensure_lookback(c, (size_t)tiles * rb * 8);
+                } catch (const Error&) {
+                    // no room for this table (0.5 or 1 B a pair with 4,096-pair tiles): that of the
+                    // largest tiles is a quarter of it, and the order is the same
+                    const uint64_t large = (n + LARGE_TILE - 1) / LARGE_TILE;
+                    if (large >= tiles) throw;
+                    ensure_lookback(c, (size_t)large * rb * 8);
+                    variant = LARGE_TILE_VARIANT;
+                }
                 lookback = c.lookback;
             }
         }
