@@ -471,6 +471,7 @@ uint32_t hist_grid(uint64_t n);
 int sort_variant_count();
 
 void ensure_lookback(Ctx& c, size_t need);
+void release_lookback(Ctx& c);
 void next_epoch(Ctx& c);
 // the call's runs of targets on P_local, in generation order: target first + t
 // (t < n) has the K connections at begin + t K; false for rules without such runs

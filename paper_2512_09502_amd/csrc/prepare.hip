@@ -1479,6 +1479,7 @@ void prepare_all(Ctx& c) {
                     return fo;
                 },
                 N > (1u << 22));   // the wait for the histograms pays where a skipped pass would be long
+            if (c.budget) release_lookback(c);   // room for what follows, which needs a small table at most
             if (unpack_in_sort) {
                 const uint64_t n_rows = (uint64_t)M_local + n_img;
                 row_ptr = result<uint64_t>(c, SNNC_ROW_PTR, n_rows + 1);

@@ -477,11 +477,15 @@ void launch_variant(Ctx& c, int v, const PassArgs& a, bool final, bool wide) {
 }  // namespace
 
 // look-back table of the lane: tiles x buckets status words, zeroed once when (re)allocated
-void ensure_lookback(Ctx& c, size_t need) {
-    if (c.lookback_bytes >= need) return;
+void release_lookback(Ctx& c) {
     dfree(c, c.lookback);
     c.lookback = nullptr;
     c.lookback_bytes = 0;
+}
+
+void ensure_lookback(Ctx& c, size_t need) {
+    if (c.lookback_bytes >= need) return;
+    release_lookback(c);
     c.lookback = dalloc(c, need);
     c.lookback_bytes = need;
     HIPCHK(hipMemsetAsync(c.lookback, 0, need, c.stream));

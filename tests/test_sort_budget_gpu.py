@@ -1,6 +1,7 @@
-"""Device-memory budgets that hold the sort with large tiles hold it with any
-tile: where the look-back table of the chosen tiles does not fit, the sort
-takes larger ones.  Same arrays."""
+"""Device-memory budgets that hold a network with large sort tiles hold it with
+any tile: where the look-back table of the chosen tiles does not fit, the sort
+takes larger ones, and the table does not stay for the steps after it.  Same
+arrays."""
 import pytest
 
 from gpu_util import PREP_ARRAYS, compare, log
@@ -9,11 +10,12 @@ from paper_2512_09502_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("size", [(2000, 500, 800, 200), (4000, 1000, 200, 50), (3200, 800, 960, 240), (8000, 2000, 1600, 400)])
+@pytest.mark.parametrize("P,size", [(7, (2000, 500, 800, 200)), (7, (4000, 1000, 200, 50)), (7, (3200, 800, 960, 240)),
+                                    (7, (8000, 2000, 1600, 400)), (64, (1600, 400, 2400, 600))])
 @pytest.mark.parametrize("gen_blocks", [0, 1])
-def test_budget_of_large_tiles(size, gen_blocks):
+def test_budget_of_large_tiles(P, size, gen_blocks):
     import paper_2512_09502_amd as snnc
-    script = W.balanced_collective(7, *size)
+    script = W.balanced_collective(P, *size)
     script["tune"] = {"gen_blocks": gen_blocks}
     large = snnc.run_script(dict(script, tune={"gen_blocks": gen_blocks, "sort_variant": 12}), 3, torch_allocator=False)
     peak = large.stats()["bytes_peak"]
