@@ -563,7 +563,9 @@ snnc_status snnc_tune(snnc_ctx* ctx, const char* key, int64_t value);
  * Prepare; 0: arrays grown by doubling; set before the first connection,
  * SNNC_EUNSUPPORTED for 1 without support) and "lookback_spins" (0 .. 2^22,
  * default 4096: polls of an earlier tile's counts before a workgroup of a radix
- * or image-numbering pass counts that tile itself).  Every setting gives the same arrays. */
+ * or image-numbering pass counts that tile itself) and "lookback_recount" (0,
+ * default, or 1: for checks, no earlier tile's counts are taken, so every one is
+ * counted; time grows with the square of the size).  Every setting gives the same arrays. */
 
 /* Autotuner of the source-major sort: times every pass algorithm and tile
  * shape (sort_mode x sort_variant) on n synthetic keys with `bits` sorted

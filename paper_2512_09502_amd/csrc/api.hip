@@ -1860,6 +1860,9 @@ snnc_status snnc_tune(snnc_ctx* c, const char* key, int64_t value) {
         } else if (!strcmp(key, "lookback_spins")) {
             if (value < 0 || value > (1ll << 22)) raise(SNNC_EINVAL, "lookback_spins out of range");
             c->lookback_spins = (uint32_t)value;
+        } else if (!strcmp(key, "lookback_recount")) {
+            if (value < 0 || value > 1) raise(SNNC_EINVAL, "lookback_recount must be 0 or 1");
+            c->lookback_recount = value != 0;
         } else if (!strcmp(key, "digit_bits")) {
             if (value != 0 && value != 8 && value != 9) raise(SNNC_EINVAL, "digit_bits must be 0, 8 or 9");
             c->digit_bits = (int)value;

@@ -253,6 +253,7 @@ struct Ctx {
     int number_variant = 10;             // tile shape of the image-numbering pass (tunable; 1024 x 10, payload early)
     int sort_mode = 0;                   // 0: onesweep (look-back), 1: reduce-then-scan (tunable)
     uint32_t lookback_spins = 4096;      // polls of an earlier tile before a pass counts it itself (tunable)
+    bool lookback_recount = false;       // checks: every earlier tile counts as missing
     bool sort_pinned = false;            // set by hand: the autotuner's process-wide choice is not used
     int digit_bits = 0;                  // 0: 9-bit digits when they save a pass; 8 or 9: forced
     // map policy: image numbering (0 canonical, 1 call order), image sources

@@ -455,8 +455,9 @@ __device__ __forceinline__ P last_lane(P v) {   // lane 63's value
 
 template <int XNT, int XIPT, class P>
 __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, uint64_t n, uint32_t M_local,
-                                                uint64_t* lookback, uint32_t epoch, uint32_t spin_limit, int32_t* o_src,
-                                                uint64_t* img_key, uint64_t* row_ptr, uint64_t* n_img_out) {
+                                                uint64_t* lookback, uint32_t epoch, uint32_t taken_epoch,
+                                                uint32_t spin_limit, int32_t* o_src, uint64_t* img_key,
+                                                uint64_t* row_ptr, uint64_t* n_img_out) {
     __shared__ uint64_t wave_tot[XNT / 64];
     __shared__ uint64_t s_excl;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -510,8 +511,8 @@ __global__ __launch_bounds__(XNT) void k_number(const P* __restrict__ prefix, ui
         while (pred >= 0) {
             const int64_t t = pred - lane;
             const uint64_t st = t >= 0 ? __hip_atomic_load(lookback + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                       : XFLAG_INC | ep;
-            const bool ready = (st >> 62) != 0 && ((st >> 40) & XEPOCH_MASK) == epoch;
+                                       : XFLAG_INC | (uint64_t)taken_epoch << 40;
+            const bool ready = (st >> 62) != 0 && ((st >> 40) & XEPOCH_MASK) == taken_epoch;
             const uint64_t m_ready = __ballot(ready), m_inc = __ballot(ready && (st >> 62) == 2);
             const uint32_t stop = m_inc ? (uint32_t)__ffsll((unsigned long long)m_inc) : 64u;   // lanes to take
             const uint64_t need = ~0ull >> (64 - stop);
@@ -1503,15 +1504,16 @@ void prepare_all(Ctx& c) {
                 ensure_lookback(c, tiles * 8);
                 next_epoch(c);
                 tstart(c, "prep_number");
+                const uint32_t taken = c.lookback_recount ? 0u : c.sort_epoch;
                 auto number = [&](auto kern32, auto kern64, int nt) {
                     if (wide_prefix)
                         hipLaunchKernelGGL(kern64, dim3((unsigned)tiles), dim3(nt), 0, c.stream,
                                            (const uint64_t*)prefix, N, M_local, (uint64_t*)c.lookback,
-                                           c.sort_epoch, c.lookback_spins, o_src, img_key, row_ptr, d_nimg);
+                                           c.sort_epoch, taken, c.lookback_spins, o_src, img_key, row_ptr, d_nimg);
                     else
                         hipLaunchKernelGGL(kern32, dim3((unsigned)tiles), dim3(nt), 0, c.stream,
                                            reinterpret_cast<const uint32_t*>(prefix), N, M_local, (uint64_t*)c.lookback,
-                                           c.sort_epoch, c.lookback_spins, o_src, img_key, row_ptr, d_nimg);
+                                           c.sort_epoch, taken, c.lookback_spins, o_src, img_key, row_ptr, d_nimg);
                 };
 #define NUMBER(nt, ipt) number(k_number<nt, ipt, uint32_t>, k_number<nt, ipt, uint64_t>, nt)
                 switch (shape.nt * 100 + shape.ipt) {

@@ -115,7 +115,9 @@ __device__ __forceinline__ uint32_t pass_tile(uint32_t b, uint32_t grid) {
 // LB = true: onesweep (decoupled look-back, digit_off = exclusive digit totals).
 // A workgroup whose look-back meets a tile without counts waits for spin_limit
 // polls and then counts its digit in that tile itself, so no order in which
-// workgroups start (another kernel may hold a die) can keep it waiting.  LB = false: the scatter of a reduce-then-scan pass
+// workgroups start (another kernel may hold a die) can keep it waiting.
+// taken_epoch: epoch of the counts it takes (the pass's own; 0, which no pass has,
+// where a check wants every earlier tile counted).  LB = false: the scatter of a reduce-then-scan pass
 // (tile = block index, digit_off = exclusive scan of the per-tile counts laid
 // out digit-major, so entry d * tiles + t is the tile's global base for d).
 // RB: buckets of the digit (256, or 512 for 9-bit digits).  SPLIT: stage the
@@ -132,7 +134,8 @@ template <int NT, int IPT, bool FINAL, bool LB, int RB, bool SPLIT>
 __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                  uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, uint64_t n,
                                                  uint32_t shift, uint32_t dbits, const uint64_t* __restrict__ digit_off,
-                                                 uint64_t* lookback, uint32_t epoch, uint32_t spin_limit, FinalOut fo) {
+                                                 uint64_t* lookback, uint32_t epoch, uint32_t taken_epoch,
+                                                 uint32_t spin_limit, FinalOut fo) {
     constexpr int TILE = NT * IPT;
     constexpr int WAVES = NT / 64;
     static_assert(NT >= RB, "one thread per digit");
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(NT) void k_onesweep(const uint64_t* __restrict__ ki
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) {
                         const uint64_t flag = st[u] & (3ull << 62);
-                        ready = ready && !found && pred >= 0 && flag != 0 && (uint32_t)((st[u] >> 40) & EPOCH_MAX) == epoch;
+                        ready = ready && !found && pred >= 0 && flag != 0 && (uint32_t)((st[u] >> 40) & EPOCH_MAX) == taken_epoch;
                         if (ready) {
                             excl += st[u] & VALUE_MASK;
                             found = flag == FLAG_INC;
@@ -341,7 +344,7 @@ struct PassArgs {
     uint32_t shift, dbits;
     const uint64_t* off;
     uint64_t* lookback;
-    uint32_t epoch;
+    uint32_t epoch, taken_epoch;
     uint32_t spin_limit;
     FinalOut fo;
     int mode;   // 0: onesweep, 1: reduce-then-scan
@@ -375,7 +378,7 @@ template <int NT, int IPT, bool FINAL, bool LB, int RB, bool SPLIT>
 void launch_onesweep(Ctx& c, const PassArgs& a, const uint64_t* off) {
     const uint64_t tiles = (a.n + (uint64_t)NT * IPT - 1) / ((uint64_t)NT * IPT);
     hipLaunchKernelGGL((k_onesweep<NT, IPT, FINAL, LB, RB, SPLIT>), dim3((unsigned)tiles), dim3(NT), 0, c.stream, a.kin,
-                       a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.spin_limit, a.fo);
+                       a.vin, a.kout, a.vout, a.n, a.shift, a.dbits, off, a.lookback, a.epoch, a.taken_epoch, a.spin_limit, a.fo);
 }
 
 template <int NT, int IPT, int RB, bool SPLIT = false>
@@ -696,8 +699,8 @@ int radix_sort_impl(Ctx& c, uint64_t* keys0, uint32_t* vals0, uint64_t* keys1, u
             const bool last = (li + 1 == n_live) && final_out;
             const uint32_t shift = dg.shift(bit_lo, p), width = std::min(bit_hi - shift, dg.width(p));
             PassArgs a{kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], n, shift, width,
-                       off + (size_t)p * dg.stride, (uint64_t*)lookback, epoch, c.lookback_spins,
-                       last ? final_out(cur) : FinalOut{}, mode};
+                       off + (size_t)p * dg.stride, (uint64_t*)lookback, epoch, c.lookback_recount ? 0u : epoch,
+                       c.lookback_spins, last ? final_out(cur) : FinalOut{}, mode};
             tstart(c, sort_timer(c, last ? "pass_final" : "pass").c_str());
             launch_variant(c, variant, a, last, width > 8);
             tstop(c);
