@@ -292,10 +292,15 @@ __global__ __launch_bounds__(KNT) void k_keys(GenSource g, uint64_t n, uint32_t 
 constexpr uint32_t TM_UNIT = 2048;   // at most; fewer (whole steps of a wave) where 2048 would leave compute units idle:
                                      // 1e5 connections 53.6 us with units of 2048, 10.6 with units of 128
 
-// Segment addends read from LDS, at most so many: a gather from memory takes a
-// cycle a lane in the address unit (2.25e9 connections, 2 x 1,024 segments: 11.3
-// ms through memory, 10.0 through LDS).
-constexpr uint32_t SEG_LDS = 2048;
+// Segment addends are read from LDS where they and the histograms fit a sixth of
+// a compute unit's 160 KB: the kernel's 78 registers allow six workgroups.  A gather
+// from memory takes a cycle a lane in the address unit (2.25e9 connections, 2 x 1,024
+// segments: 11.3 ms through memory, 10.0 through LDS).
+constexpr uint32_t TM_LDS = 26 << 10;
+
+__host__ __device__ __forceinline__ bool adds_in_lds(const Digits& dg, uint32_t n_seg) {
+    return (uint64_t)dg.passes * dg.stride * 4 + (uint64_t)n_seg * 8 <= TM_LDS;
+}
 
 uint32_t tm_unit(uint64_t n) {
     return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n / 8192 / 64 * 64, 128), TM_UNIT);
@@ -307,7 +312,7 @@ __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, ui
     extern __shared__ __align__(8) uint32_t h[];   // a histogram a pass, then the segments' addends if they are few
     for (uint32_t i = threadIdx.x; i < dg.passes * dg.stride; i += PNT) h[i] = 0;
     int64_t* adds = nullptr;
-    if (g.n_seg <= SEG_LDS) {
+    if (adds_in_lds(dg, g.n_seg)) {
         adds = reinterpret_cast<int64_t*>(h + dg.passes * dg.stride);
         for (uint32_t i = threadIdx.x; i < g.n_seg; i += PNT) adds[i] = g.seg_add[i];
     }
@@ -1445,7 +1450,7 @@ void prepare_all(Ctx& c) {
             if (by_source)
                 hipLaunchKernelGGL(k_keys_tmajor,
                                    dim3((unsigned)std::min<uint64_t>((N + unit * 4 - 1) / (unit * 4), 8192)), dim3(PNT),
-                                   n_hist * 4 + (gs.n_seg <= SEG_LDS ? gs.n_seg * 8 : 0), c.stream, gs, N, bit_lo, dg, unit,
+                                   n_hist * 4 + (adds_in_lds(dg, gs.n_seg) ? gs.n_seg * 8 : 0), c.stream, gs, N, bit_lo, dg, unit,
                                    keys0, moved, hist);
             else
                 hipLaunchKernelGGL(k_keys, dim3(hist_grid(N)), dim3(KNT), n_hist * 4, c.stream, gs, N, bit_lo, dg, keys0,
