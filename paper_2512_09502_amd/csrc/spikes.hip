@@ -400,6 +400,37 @@ uint32_t bits_for_values(uint64_t n_values) {
     return b;
 }
 
+// Packets of tiles of at least 8 spikes, at most max_tiles of them.
+void packets_tiled(Ctx& c, const Spikes& sp, uint64_t max_tiles, uint32_t d_bits, uint64_t cap, uint64_t* off,
+                   uint32_t* pos_out, uint32_t* mult_out, const Bad& bad) {
+    const uint64_t tile = std::max<uint64_t>(8, (sp.n + max_tiles - 1) / max_tiles);
+    const uint32_t n_tiles = (uint32_t)((sp.n + tile - 1) / tile), nd = std::min(sp.n_dest, DEST_RANGE);
+    const dim3 grid(n_tiles, (sp.n_dest + DEST_RANGE - 1) / DEST_RANGE);
+    const uint64_t cells = (uint64_t)n_tiles * sp.n_dest;
+    uint32_t* cnt = dalloc_n<uint32_t>(c, cells);
+    uint64_t* first = nullptr;
+    try {
+        first = dalloc_n<uint64_t>(c, cells + 1);
+        tstart(c, "spike_records");
+        hipLaunchKernelGGL(k_packet_count, grid, dim3(64), nd * 4, c.stream, sp, tile, n_tiles, cnt, bad);
+        tstop(c);
+        HIPCHK(hipGetLastError());
+        scan_u32_u64_to(c, cnt, first, cells, c.tot_pin_dev);
+        tstart(c, "spike_packets");
+        hipLaunchKernelGGL(k_packet_place, grid, dim3(64), nd * 8, c.stream, sp, tile, n_tiles, d_bits,
+                           (const uint64_t*)first, cap, off, pos_out, mult_out, bad);
+        tstop(c);
+        HIPCHK(hipGetLastError());
+        sync(c);
+    } catch (...) {
+        dfree(c, cnt);
+        dfree(c, first);
+        throw;
+    }
+    dfree(c, cnt);
+    dfree(c, first);
+}
+
 }  // namespace
 
 uint64_t spike_packets(Ctx& c, int kind, const uint32_t* spikes, const uint32_t* mult, uint64_t n, uint64_t* off,
@@ -431,36 +462,20 @@ uint64_t spike_packets(Ctx& c, int kind, const uint32_t* spikes, const uint32_t*
         HIPCHK(hipGetLastError());
         sync(c);
     } else {
-        // tiles of at least 8 spikes; no more counts than a quarter of the records to expect, or 2^18
+        // no more counts than four times the records to expect, or 2^18: with fewer tiles a wave has more
+        // than one batch of 64 spikes to walk.  4,096 destinations, 50,000 spikes of 8 records: 296 us with
+        // 2^18 counts, 222 with one a record, 134 with four
         const double expected = (double)n * (double)c.counts[kind == 0 ? SNNC_T_VAL : SNNC_Q_VAL] / std::max(M, 1u);
-        const uint64_t max_cells = std::max<uint64_t>(1ull << 18, (uint64_t)(expected / 4));
-        const uint64_t max_tiles = std::max<uint64_t>(1, std::min<uint64_t>(1024, max_cells / n_dest));
-        const uint64_t tile = std::max<uint64_t>(8, (n + max_tiles - 1) / max_tiles);
-        const uint32_t n_tiles = (uint32_t)((n + tile - 1) / tile);
-        const dim3 grid(n_tiles, (n_dest + DEST_RANGE - 1) / DEST_RANGE);
-        const uint64_t cells = (uint64_t)n_tiles * n_dest;
-        uint32_t* cnt = dalloc_n<uint32_t>(c, cells);
-        uint64_t* first = nullptr;
-        try {
-            first = dalloc_n<uint64_t>(c, cells + 1);
-            tstart(c, "spike_records");
-            hipLaunchKernelGGL(k_packet_count, grid, dim3(64), nd * 4, c.stream, sp, tile, n_tiles, cnt, bad);
-            tstop(c);
-            HIPCHK(hipGetLastError());
-            scan_u32_u64_to(c, cnt, first, cells, c.tot_pin_dev);
-            tstart(c, "spike_packets");
-            hipLaunchKernelGGL(k_packet_place, grid, dim3(64), nd * 8, c.stream, sp, tile, n_tiles, d_bits,
-                               (const uint64_t*)first, cap, off, pos_out, mult_out, bad);
-            tstop(c);
-            HIPCHK(hipGetLastError());
-            sync(c);
-        } catch (...) {
-            dfree(c, cnt);
-            dfree(c, first);
-            throw;
+        const uint64_t max_cells = std::max<uint64_t>(1ull << 18, (uint64_t)(4 * expected));
+        uint64_t max_tiles = std::max<uint64_t>(1, std::min<uint64_t>(1024, max_cells / n_dest));
+        for (;; max_tiles = std::max<uint64_t>(1, max_tiles / 8)) {
+            try {
+                packets_tiled(c, sp, max_tiles, d_bits, cap, off, pos_out, mult_out, bad);
+                break;
+            } catch (const Error& e) {   // no room for the counts: fewer tiles
+                if ((e.code != SNNC_EBUDGET && e.code != SNNC_ENOMEM) || max_tiles == 1) throw;
+            }
         }
-        dfree(c, cnt);
-        dfree(c, first);
     }
     if (*reinterpret_cast<volatile uint32_t*>(c.tot_pin + 2)) raise(SNNC_EINVAL, "spike id is not a local neuron");
     return *reinterpret_cast<volatile uint64_t*>(c.tot_pin);   // above cap: the caller reports the small capacity

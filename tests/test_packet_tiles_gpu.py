@@ -1,0 +1,73 @@
+"""Packets of very many spikes for thousands of destinations: parity, no more
+time than a small multiple of what as many records for few destinations take,
+and fewer tiles where a memory budget does not hold the tiles' counts."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+SYN = {"weight": {"kind": "const", "mean": 0.1}, "delay": {"kind": "const", "mean": 0.3}}
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(np.asarray(a, dtype=np.uint32)).view(np.int32)).cuda()
+
+
+def _script(P, M, K):
+    """M neurons here, two on every other host, each with K draws from here."""
+    conn = {"rule": "fixed_indegree", "n": K, "autapses": True, "multapses": True}
+    ops = [("create", 0, M)] + [("create", h, 2) for h in range(1, P)]
+    ops += [("connect", [(0, 0, M)], [(h, 0, 2)], conn, SYN, -1) for h in range(1, P)]
+    return {"P": P, "seed": 3, "dt": 0.1, "ops": ops}
+
+
+def _seconds(net, spikes):
+    best = 1e9
+    for _ in range(9):
+        t0 = time.perf_counter()
+        net.spike_packets(0, spikes)
+        best = min(best, time.perf_counter() - t0)
+    return best
+
+
+def test_time_of_many_destinations():
+    """9e5 records of 50,000 spikes: to 8,999 hosts at most 3.5 times as long as to 63 hosts, and 50 us."""
+    import paper_2512_09502_amd as snnc
+    spikes = _dev(np.random.default_rng(1).permutation(50_000))
+    t = {}
+    for P, K in ((64, 8400), (9000, 50)):
+        net = snnc.run_script(_script(P, 50_000, K), 0)
+        t[P] = _seconds(net, spikes)
+        log(f"{P} hosts: {net.count('t_val')} records, {t[P] * 1e6:.0f} us")
+        net.close()
+    assert t[9000] <= 3.5 * t[64] + 50e-6
+
+
+@pytest.mark.parametrize("P,M,K,n", [(4097, 3000, 6, 40_000), (4096, 20_000, 9, 20_000), (300, 20_000, 90, 20_000)])
+@pytest.mark.parametrize("spare", [None, 1 << 19, 3 << 20])
+def test_budget(P, M, K, n, spare):
+    """spare: bytes left to the library after Prepare (its 8 MiB slab aside); None: no budget."""
+    import paper_2512_09502_amd as snnc
+    script = dict(_script(P, M, K), tune={"gen_blocks": 0})
+    ref = oracle.run_script(script, 0)
+    rng = np.random.default_rng(P)
+    spikes, mult = rng.integers(0, M, size=n), rng.integers(1, 4, size=n)
+    kw = {"torch_allocator": False}
+    if spare is not None:
+        net = snnc.run_script(script, 0, **kw)
+        st = net.stats()
+        net.close()
+        kw["budget_bytes"] = max(st["bytes_peak"], st["bytes_live"] + (8 << 20) + spare)
+    log(f"P={P} n={n} spare={spare} {kw}")
+    net = snnc.run_script(script, 0, **kw)
+    got, want = net.spike_packets(0, _dev(spikes), _dev(mult)), ref.spike_packets(0, spikes, mult)
+    np.testing.assert_array_equal(got["off"].cpu().numpy().view(np.uint64), want["off"])
+    np.testing.assert_array_equal(got["pos"].cpu().numpy().view(np.uint32), want["pos"])
+    np.testing.assert_array_equal(got["mult"].cpu().numpy().view(np.uint32), want["mult"])
+    net.close()
