@@ -753,10 +753,16 @@ static void upload_meta_batch(Ctx& c, std::vector<Call*>& calls) {
     }
 }
 
+// What a refused call took goes back, its distribution's table too where no
+// other call uses it (the context's cache holds the other reference).
 static void free_meta(Ctx& c, Call& cl) {
     if (!cl.meta_shared) dfree(c, cl.meta);
     cl.meta = nullptr;
     cl.has_meta = false;
+    if (cl.dtab && cl.dtab->dev && cl.dtab.use_count() <= 2) {
+        dfree(c, cl.dtab->dev);
+        cl.dtab->dev = nullptr;
+    }
 }
 
 // ------------------------------------------------------------------ generation store in blocks
