@@ -539,8 +539,9 @@ snnc_status snnc_tune(snnc_ctx* ctx, const char* key, int64_t value);
  * default map policy, the path the other policies take) and "digit_bits"
  * (0: 9-bit digits, 512 buckets, when they save a pass and the tile has at
  * least 512 threads; 8 or 9: forced where the tile allows), "number_variant"
- * (tile shape of the image-numbering pass after the sort, 0 .. 11; default 10 =
- * 1024 threads x 10 items) and
+ * (tile shape of the image-numbering pass after the sort, 0 .. 11: 1024, 512,
+ * 256, 512, 256 threads x 12 items, 256 x 16, 256 x 8, 256 x 6, 512 x 8, 1024 x 12,
+ * 1024 x 10, 1024 x 8; 0 and 9, 1 and 3, 2 and 4 are the same; default 10) and
  * "mark_in_lds" (1, default: regeneration for the point-to-point lists marks
  * its bit row in LDS when the row has at most 2^19 neurons; 0: a global
  * atomic per draw) and "floyd_wave_max" (0 .. 8192, default 1024: Floyd's

@@ -250,7 +250,7 @@ struct Ctx {
     size_t lookback_bytes = 0;           // per lane
     int sort_variant = 0;                // tile shape of the radix passes (tunable)
     bool mark_in_lds = true;             // regeneration marks bit rows in LDS when they fit (tunable)
-    int number_variant = 10;             // tile shape of the image-numbering pass (tunable; 1024 x 10, payload early)
+    int number_variant = 10;             // tile shape of the image-numbering pass (tunable; 1024 x 10)
     int sort_mode = 0;                   // 0: onesweep (look-back), 1: reduce-then-scan (tunable)
     uint32_t lookback_spins = 4096;      // polls of an earlier tile before a pass counts it itself (tunable)
     bool lookback_recount = false;       // checks: every earlier tile counts as missing

@@ -439,7 +439,8 @@ __global__ __launch_bounds__(PNT) void k_keys_tmajor(GenSource g, uint64_t n, ui
 // connection its source'.  The same pass records each image's prefix and writes
 // the first-index array.  4 B read and written per connection (the last radix
 // pass has written the other arrays).
-// Tile shapes: threads, items per thread.
+// Tile shapes: threads, items per thread.  The settings 0 and 9, 1 and 3, 2 and 4
+// stand for the same shape (they once differed in when a payload was loaded).
 struct NumberShape {
     int nt, ipt;
 };

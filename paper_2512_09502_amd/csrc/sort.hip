@@ -508,7 +508,8 @@ int sort_variant_count() { return N_VARIANTS; }
 // bits: as few passes as the tile shape's digits allow, of equal or nearly equal
 // width (a pass costs more the wider its digit).  9-bit digits (512 buckets)
 // need a tile of at least 512 threads; 10-bit ones were not worth it (passes over
-// 2^28 pairs with the largest tile: 8 bits 1501, 9 bits 1642, 10 bits 2070 us).
+// 2^28 pairs with the largest tile, when the look-back still came before the staging:
+// 8 bits 1501, 9 bits 1642, 10 bits 2070 us; the first two take 1334 and 1470 since).
 // The scratch of fixed size (`fixed`) keeps to the tiles its limits are stated for.
 SortPlan plan_sort(const Ctx& c, uint64_t n, uint32_t bits, bool fixed) {
     SortPlan p;
