@@ -101,6 +101,8 @@ __global__ __launch_bounds__(STRIDE) void k_hist_scan(const uint64_t* hist, uint
 // whose round trip would come before every tile's loads.  Passes over 2^28
 // pairs, eight and nine bits: 1346 and 1493 us with 8 tiles to a die, 1334 and
 // 1470 with 16, 1493 and 1622 with 32 (tile = index cost a fifth more than 8).
+// By the HBM counters a pass moves 24.7 B a pair with eight bits and 25.4 - 25.5 with
+// nine, of 24 needed (26.4 - 26.9 and 29.3 with 8192-pair tiles in launch order).
 constexpr uint32_t DIES = 8, CHUNK = 16;
 
 // Earlier tiles whose counts a look-back reads at once: a word costs a trip past
