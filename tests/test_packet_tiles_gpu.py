@@ -37,7 +37,8 @@ def _seconds(net, spikes):
 
 
 def test_time_of_many_destinations():
-    """9e5 records of 50,000 spikes: to 8,999 hosts at most 3.5 times as long as to 63 hosts, and 50 us."""
+    """9e5 records of 50,000 spikes: to 8,999 hosts at most six times as long as to 63 hosts, and 100 us
+    (measured 235 and 66; with too few tiles 930)."""
     import paper_2512_09502_amd as snnc
     spikes = _dev(np.random.default_rng(1).permutation(50_000))
     t = {}
@@ -46,7 +47,7 @@ def test_time_of_many_destinations():
         t[P] = _seconds(net, spikes)
         log(f"{P} hosts: {net.count('t_val')} records, {t[P] * 1e6:.0f} us")
         net.close()
-    assert t[9000] <= 3.5 * t[64] + 50e-6
+    assert t[9000] <= 6 * t[64] + 100e-6
 
 
 @pytest.mark.parametrize("P,M,K,n", [(4097, 3000, 6, 40_000), (4096, 20_000, 9, 20_000), (300, 20_000, 90, 20_000)])
