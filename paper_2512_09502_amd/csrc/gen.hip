@@ -2013,9 +2013,9 @@ uint64_t run_call(Ctx& c, Call& cl, uint32_t host, Out mode, uint32_t* mark_bits
 // gives its item range in the batch and its rule parameters; every item is
 // generated exactly as in the per-call kernel, at the position the call was
 // admitted to.  k_fused takes the calls of a tile one after another, and the runs
-// of a call, all threads on one: calls of a few hundred items or more.  Calls
-// below that, or with runs below that, and small batches go to k_fused_items, where
-// every item finds its call, and its run, by binary search.
+// of a call, all threads on one: calls of at least a tile's items in long runs.
+// The others and small batches go to k_fused_items, where every item finds its
+// call, and its run, by binary search (by_items has the lines).
 // F_SYN_FILL: the synapse values of a Floyd call (its sources and targets
 // written by its own launch), element index from the run table as in
 // k_syn_fill; `ind` holds the run table and K.
